@@ -330,7 +330,10 @@ int monc_stream_probe(int kind, void* a, void* b, void* c, void* d, size_t bytes
  *   out[0] = x-FFT elements per thread (runtime-length FFTs only),
  *   out[1] = y-FFT elements per thread (runtime-length FFTs only),
  *   out[2] = y-FFT columns per workgroup,
- *   out[3] = tridiagonal lanes per column (power of 2, <= 64),
+ *   out[3] = tridiagonal lanes per column (power of 2, <= 64; on grids whose
+ *            columns are solved by the kernel with a wave per chunk of rows,
+ *            mostly those of many columns and more than 96 levels, out[3] and
+ *            out[4] have no effect),
  *   out[4] = tridiagonal columns per workgroup (power of 2, times out[3]
  *            at most 1024 threads),
  *   out[5] = x-direction transforms (row pairs) per workgroup of the

@@ -122,6 +122,38 @@ static int tri_rows(int nz, int P) {
   return 0;
 }
 
+// Waves and rows per wave of the wave-per-chunk tridiagonal kernel, or 0 where
+// the lanes-per-column kernel is the better one. Measured (default tiles, us,
+// lanes-per-column / wave-per-chunk):
+//   above 96 levels the former's default tiles are 8 or 4 columns wide, 64 or
+//   32 bytes of an FP32 level: 128^2 x 128 16.8 / 14.5, 256^2 x 128 31.2 / 23.3,
+//   512^2 x 128 92 / 55, 1024^2 x 256 1161 / 464; but 64^2 x 128 (40 tiles of 64
+//   columns) 10.1 / 12.8: the longer chain of few workgroups. In FP64 (twice
+//   the bytes) only spectra beyond the 256 MB Infinity Cache gain: 512^2 x 128
+//   126 / 118, 512^2 x 256 320 / 245, 256^2 x 128 33.8 / 36.5.
+//   up to 32 levels and over 512 tiles: 256^2 x 16 10.8 / 10.0 (FP32) and 13.3 /
+//   12.0 (FP64), 512^2 x 32 27.4 / 19.3 and 29.2 / 27.9; 192^2 x 32 equal.
+//   between: 256^2 x 64 17.3 / 18.1 and 18.1 / 20.7, 512^2 x 96 41.9 / 43.2; FP32
+//   beyond the Infinity Cache 131 / 109 (1024^2 x 64), FP64 no gain.
+// Rows per wave: the fewest waves (2, 4, 8 or 16) whose rows stay within a
+// limit. More rows mean fewer interface rows and more, smaller workgroups on a
+// CU, whose loads overlap each other's elimination (512^2 x 128 FP32 8 waves of
+// 16 rows 55 us, 16 of 8 75; 1024^2 x 64 4 of 16 109, 8 of 8 116, 16 of 4 196).
+// FP64 storage stops at 14 rows, where its registers spill (1024^2 x 64 FP64 8
+// of 8 196 us, 4 of 16 234; 256^2 x 110 8 of 14 28.8, 16 of 7 34.2).
+static void tricol_shape(int nz, long long tiles, bool fp64, int* waves, int* rows) {
+  *waves = *rows = 0;
+  if (nz > kTriColMax) return;
+  const bool beyond_cache = (double)tiles * 64 * nz * (fp64 ? 16 : 8) > 256.0 * (1 << 20);
+  const bool use = nz > 96 ? (fp64 ? beyond_cache : tiles > 128) : tiles > 512 && (nz <= 32 || (!fp64 && beyond_cache));
+  if (!use) return;
+  const int most = fp64 ? 14 : 16;
+  int P = 2;
+  while (P < 16 && (nz + P - 1) / P > most) P *= 2;
+  *waves = P;
+  *rows = std::max(2, (nz + P - 1) / P);
+}
+
 // Derive FFT plans and tile parameters from (ex, ey, ymt, triP, tricw, xpw,
 // yept); 0 = default.
 static int configure_tiles(monc_plan* pl, int ex, int ey, int ymt, int triP, int tricw, int xpw, int yept) {
@@ -211,6 +243,7 @@ static int configure_tiles(monc_plan* pl, int ex, int ey, int ymt, int triP, int
   h.triP = triP;
   h.tris = s;
   h.tricw = cw;
+  tricol_shape(pl->nz, ((long long)pl->ny * h.nxp + 63) / 64, pl->dtype == MONC_FP64, &h.tcwaves, &h.tcrows);
   return MONC_OK;
 }
 
@@ -594,7 +627,7 @@ static bool is_yphase(Phase ph) { return ph == PH_YFWD || ph == PH_YINV; }
 // the runtime-length kernel) and `block` its workgroup size.
 struct Shape {
   int variant = 0;   // compile-time length, or 0 for the runtime-length kernel
-  int sub = 0;       // kernel instance within the variant (tridiagonal: column pairs)
+  int sub = 0;       // kernel instance within the variant (tridiagonal: 1 column pairs, 2 wave per chunk)
   int block = 256;
   size_t lds = 0;
   long long blocks = 0;       // tiles of the phase
@@ -665,6 +698,12 @@ static Shape member_shape(const MemberDesc& d, Phase ph, bool fp64) {
       s.lds = (size_t)d.ny * d.ymt * cb;
       s.blocks = (long long)d.nz * ((d.nxh + d.ymt - 1) / d.ymt);
     }
+  } else if (ph == PH_TRI && d.tcwaves) {
+    s.variant = d.tcrows;
+    s.sub = 2;
+    s.block = 64 * d.tcwaves;
+    s.lds = (size_t)tricol_lds(d.tcwaves) * sizeof(double);
+    s.blocks = ((long long)d.ny * d.nxp + 63) / 64;
   } else if (ph == PH_TRI) {
     s.variant = d.tris;
     s.sub = tri_pairs(d.tris, d.tricw, !fp64) ? 1 : 0;
@@ -725,7 +764,9 @@ static int launch_one(const Group& g, const std::vector<int>& idx, Phase ph, con
     case PH_RESID: launch_xfwd(a, grid, block, lds, false, 1, v, stream); break;
     case PH_YFWD: launch_ffty(a, grid, block, lds, g.fp64, false, v, g.mem[idx[0]].h->yept, stream); break;
     case PH_YINV: launch_ffty(a, grid, block, lds, g.fp64, true, v, g.mem[idx[0]].h->yept, stream); break;
-    case PH_TRI: launch_tridiag(a, grid, block, lds, g.fp64, v, sh.sub != 0, stream); break;
+    case PH_TRI:
+      if (sh.sub == 2) launch_tricol(a, grid, block, lds, g.fp64, v, stream);
+      else launch_tridiag(a, grid, block, lds, g.fp64, v, sh.sub != 0, stream); break;
     case PH_XINV: launch_xinv(a, grid, block, lds, g.fp64, 0, v, stream); break;
     case PH_XINV_P1: launch_xinv(a, grid, block, lds, false, 2, v, stream); break;
     case PH_XINV_CORR: launch_xinv(a, grid, block, lds, false, 1, v, stream); break;
@@ -1647,7 +1688,7 @@ static int tune_plan(monc_plan* pl, void* stream) {
     for (int k = 0; k < MONC_K_COUNT; ++k) cost += ms[k];
     return MONC_OK;
   };
-  int best[MONC_NPARAMS] = {pl->ex, pl->ey, pl->ymt, pl->triP, pl->tricw, pl->h.xpw, pl->h.yept};
+  int best[MONC_NPARAMS] = {pl->ex, pl->ey, pl->ymt, pl->triP, pl->h.tricw, pl->h.xpw, pl->h.yept};
   {
     double whole = 0.0;
     const int r = measure(best, (1u << MONC_K_COUNT) - 1, whole);
@@ -1684,8 +1725,10 @@ static int tune_plan(monc_plan* pl, void* stream) {
     else axes.push_back({6, {8, 16}, ymask | xmask});
   }
   axes.push_back({2, {1, 2, 4, 8, 16, 32}, ymask | xmask});
-  axes.push_back({3, pvals, tmask});
-  axes.push_back({4, {4, 8, 16, 32}, tmask});
+  if (!pl->h.tcwaves) {  // the lanes-per-column tridiagonal kernel
+    axes.push_back({3, pvals, tmask});
+    axes.push_back({4, {4, 8, 16, 32}, tmask});
+  }
   if (ct_supported(pl->nx)) axes.push_back({5, {1, 2, 4}, xmask});
   for (const auto& ax : axes) {
     double best_cost = 1e300;

@@ -8,6 +8,7 @@ namespace monc {
 
 // Raise the dynamic-LDS limit of every kernel to the CU's 160 KB.
 void init_kernel_attributes();
+void init_tridiag_attributes();  // the tridiagonal kernels' part of it
 
 // Transform lengths with a compile-time FFT kernel (others take the
 // runtime-length kernels); such kernels use n/8 threads per transform (1 if
@@ -30,6 +31,9 @@ void launch_ffty(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64
                  void* stream);
 // rows: rows per lane, one of kTriRows (the member's tris)
 void launch_tridiag(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int rows, bool pairs, void* stream);
+// the wave-per-chunk kernel (up to kTriColMax levels): rows per wave (the
+// member's tcrows), block = 64 times the member's tcwaves
+void launch_tricol(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int rows, void* stream);
 // the result goes to io.p (mode 0), io.s1 (mode 1, float only: the
 // correction delta) or io.s2 (mode 2, float only: the first-pass pressure)
 void launch_xinv(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int mode, int ct_n, void* stream);

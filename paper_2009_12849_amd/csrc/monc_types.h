@@ -33,6 +33,11 @@ constexpr int tri_lane_slots(int s, bool f32) {
 // instance): half the memory instructions for the same runs; narrower tiles
 // measured slower that way.
 constexpr bool tri_pairs(int s, int cw, bool f32) { return f32 && s % 2 == 0 && cw >= 8; }
+// The wave-per-chunk tridiagonal kernel: at most 16 waves of at most 16 rows.
+constexpr int kTriColMax = 256;
+// LDS doubles of a workgroup of P waves: the interface rows (5), the chunks'
+// last rows (4) and the interface solution (2), P x 64 each
+constexpr int tricol_lds(int P) { return 11 * P * 64; }
 // Threads per compile-time transform (shared by the kernels and the host's
 // launch shapes), and so the radix plan (16 elements per thread take radix-16
 // passes): along x sixteen elements each from length 512 on, eight below;
@@ -137,6 +142,8 @@ struct MemberDesc {
   int triP;               // tridiagonal lanes per column (power of 2)
   int tris;               // rows per lane (>= 2)
   int tricw;              // columns per workgroup (blockDim / triP)
+  int tcwaves;            // waves of the wave-per-chunk kernel (0: more than kTriColMax levels)
+  int tcrows;             // its rows per wave
   int ptk;                // levels per (level, row pair) tile of the stencil kernels (1 = row order)
   int ptj;                // row pairs per such tile of the x-forward kernels (8 to 64)
   int xpw;                // x-direction transforms (row pairs) per workgroup of the compile-time kernels

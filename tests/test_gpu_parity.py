@@ -568,6 +568,30 @@ def test_mixed_tridiagonal_tiles_give_identical_bits(nz, lanes):
             assert np.array_equal(a, b)
 
 
+# both column kernels and the lines between them: 96 / 97 and 256 / 257 levels
+# at 183 tiles of 64 columns (128 x 162: 11664 entries, the last tile ragged),
+# 122 tiles (128 x 108) and 517 (256 x 243: 33048 entries); rows per wave from 2
+# to 16 on 2 to 16 waves
+@pytest.mark.parametrize("shape", [(128, 162, n) for n in (96, 97, 112, 113, 129, 160, 161, 241, 256, 257)]
+                         + [(128, 108, 97)] + [(256, 243, n) for n in (1, 2, 3, 5, 28, 29, 31, 32, 33)])
+@pytest.mark.parametrize("dtype", ["f64", "mixed"])
+def test_column_solve_row_chunks(shape, dtype):
+    g, u, v, w = _case(shape, 37)
+    B = oracle.forward_spectrum(oracle.divergence(u, v, w, g.dx, g.dy, g.dz, g.rho0))
+    if dtype == "mixed":
+        B = B.astype(np.complex64).astype(np.complex128)
+    ref = oracle.solve_columns(B, g.dz, g.rho0, g.dx, g.dy, g.nx, g.ny) / (g.nx * g.ny)
+    plan = monc.Plan.from_grid(g, dtype)
+    spec = plan.spectral_buffer()
+    plan.spectral_set(spec, torch.from_numpy(B))
+    plan.debug_stage(monc.STAGE_SOLVE, [spec])
+    torch.cuda.synchronize()
+    got = plan.spectral_get(spec).cpu().numpy().astype(np.complex128)
+    # FP32 storage: the solve is FP64, the result rounded once (2^-24 a part)
+    tol = p_tolerance(g) + (0.0 if dtype == "f64" else 2.0 ** -23)
+    assert relerr(got, ref) <= tol
+
+
 @pytest.mark.parametrize("params", [[8, 8, 8, 16, 3], [8, 8, 8, 32, 32], [8, 8, 8, 64, 16], [8, 8, 8, 3, 0]])
 def test_plan_rejects_bad_tridiagonal_tiles(params):
     g, u, v, w = _case((32, 16, 130), 19)

@@ -17,6 +17,11 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmonc.so")
 SOURCES = ["kernels.hip", "tridiag.hip", "krylov.hip", "api.hip", "probe.hip", "plan_math.cpp"]
+# the FFT kernels' compile-time lengths, one object per group (kernels.h)
+FFT_GROUPS = 8
+# (source, object, extra flags)
+UNITS = [("fft_inst.hip", f"fft_inst_{k}.o", [f"-DMONC_FFT_GROUP={k}"]) for k in range(FFT_GROUPS)] + [
+    (s, os.path.splitext(s)[0] + ".o", []) for s in SOURCES]
 
 # No packed FP32 instructions (v_pk_*_f32) in any HIP object.
 HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -34,9 +39,10 @@ def hipcc() -> str:
     return path
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [hipcc()] + HIP_FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(unit) -> str:
+    src, obj, flags = unit
+    obj = os.path.join(BUILD, obj)
+    cmd = [hipcc()] + HIP_FLAGS + flags + ["-c", os.path.join(CSRC, src), "-o", obj]
     if src.endswith(".cpp"):
         cmd = [hipcc(), "-O3", "-std=c++17", "-fPIC", "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -47,8 +53,8 @@ def _compile(src: str) -> str:
 
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
-        objs = list(ex.map(_compile, SOURCES))
+    with cf.ThreadPoolExecutor(max_workers=min(len(UNITS), os.cpu_count() or 1)) as ex:
+        objs = list(ex.map(_compile, UNITS))
     tmp = LIB + ".tmp"
     cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -217,6 +217,9 @@ static int configure_tiles(monc_plan* pl, int ex, int ey, int ymt, int triP, int
     const int nt = ct_threads_host(pl->nx);
     const size_t per = (size_t)xlds_len(pl->nx, (int)cb) * cb;
     xeff = xpw > 0 ? xpw : std::max(1, 256 / nt);
+    // lengths with a radix plan of their own take any request, clamped
+    if (ct_plan_index(pl->nx) >= 0)
+      xeff = (int)std::min<size_t>(xeff, std::max<size_t>(1, std::min<size_t>(512 / nt, (160 * 1024) / per)));
     if (xeff * nt > 512 || xeff * per > 160 * 1024)
       return fail(MONC_EINVAL, "%d x transforms of %d points per workgroup exceed 512 threads or 160 KB of LDS", xeff,
                   pl->nx);

@@ -1,5 +1,5 @@
-// Device FFT building blocks for gfx950: complex helpers, radix-2/3/4/8
-// butterflies, and two Stockham engines sharing them:
+// Device FFT building blocks for gfx950: complex helpers, butterflies of radix
+// 2, 3, 4, 6, 8, 9, 12, 16 and 18, and two Stockham engines sharing them:
 //   * CtFft<T, N, NT, INV>: length fixed at compile time, NT threads per
 //     transform, every index folded to constants; values stay in registers
 //     inside a pass and cross threads through LDS between passes. The first
@@ -149,16 +149,71 @@ template <bool INV, typename C> __device__ __forceinline__ void dft16(C* v) {
   }
 }
 
+// a * W36^E (forward: exp(-2 pi i E/36); inverse: its conjugate), E = 0..35
+template <int E, bool INV, typename C> __device__ __forceinline__ C w36(C a) {
+  using T = decltype(a.x);
+  constexpr double q[10] = {1.0,  // cos(10 deg i)
+                            0.984807753012208059367, 0.939692620785908384054, 0.866025403784438646764,
+                            0.766044443118978035202, 0.642787609686539326323, 0.5, 0.342020143325668733044,
+                            0.173648177666930348852, 0.0};
+  if constexpr (E == 0) return a;
+  else if constexpr (E == 9) return INV ? mul_pi(a) : mul_mi(a);
+  else if constexpr (E == 18) return C{-a.x, -a.y};
+  else if constexpr (E == 27) return INV ? mul_mi(a) : mul_pi(a);
+  else {
+    constexpr double c0 = E < 9 ? q[E] : E < 18 ? -q[18 - E] : E < 27 ? -q[E - 18] : q[36 - E];
+    constexpr double s0 = E < 9 ? q[9 - E] : E < 18 ? q[E - 9] : E < 27 ? -q[27 - E] : -q[E - 27];
+    const T c = (T)c0, sv = INV ? (T)s0 : -(T)s0;  // multiply by c + i sv
+    return C{a.x * c - a.y * sv, a.x * sv + a.y * c};
+  }
+}
+
+template <int R, bool INV, typename C> __device__ __forceinline__ void dft_small(C* v);
+
+// Twiddles W_R^(n2 k1) of the composite butterfly, unrolled over n2 and k1
+template <int R1, int R2, int I, bool INV, typename C> __device__ __forceinline__ void dft_twiddle(C (*y)[R1]) {
+  if constexpr (I < R1 * R2) {
+    y[I / R1][I % R1] = w36<(I / R1) * (I % R1) * (36 / (R1 * R2)) % 36, INV>(y[I / R1][I % R1]);
+    dft_twiddle<R1, R2, I + 1, INV>(y);
+  }
+}
+
+// DFT of R1 R2 points (6, 9, 12, 18): R1-point DFTs over n1 of x[R2 n1 + n2],
+// twiddles, R2-point DFTs over n2; output k1 + R1 k2 in natural order.
+template <int R1, int R2, bool INV, typename C> __device__ __forceinline__ void dft_composite(C* v) {
+  C y[R2][R1];
+#pragma unroll
+  for (int n2 = 0; n2 < R2; ++n2) {
+#pragma unroll
+    for (int n1 = 0; n1 < R1; ++n1) y[n2][n1] = v[R2 * n1 + n2];
+    dft_small<R1, INV>(y[n2]);
+  }
+  dft_twiddle<R1, R2, 0, INV>(y);
+#pragma unroll
+  for (int k1 = 0; k1 < R1; ++k1) {
+    C t[R2];
+#pragma unroll
+    for (int n2 = 0; n2 < R2; ++n2) t[n2] = y[n2][k1];
+    dft_small<R2, INV>(t);
+#pragma unroll
+    for (int k2 = 0; k2 < R2; ++k2) v[k1 + R1 * k2] = t[k2];
+  }
+}
+
 template <int R, bool INV, typename C> __device__ __forceinline__ void dft_small(C* v) {
   if constexpr (R == 2) dft2<INV>(v);
   else if constexpr (R == 3) dft3<INV>(v);
   else if constexpr (R == 4) dft4<INV>(v[0], v[1], v[2], v[3]);
+  else if constexpr (R == 6) dft_composite<3, 2, INV>(v);
   else if constexpr (R == 8) dft8<INV>(v);
+  else if constexpr (R == 9) dft_composite<3, 3, INV>(v);
+  else if constexpr (R == 12) dft_composite<3, 4, INV>(v);
+  else if constexpr (R == 18) dft_composite<9, 2, INV>(v);
   else dft16<INV>(v);
 }
 
 // ---------------------------------------------------------------------------
-// compile-time radix plan. With at least 16 elements per thread (r16): radix
+// compile-time radix plan: the length's own (kCtPlans), else, with at least 16 elements per thread (r16): radix
 // 16 as often as the power of two allows, then one 8, 4 or 2, then the 3s;
 // otherwise radix 8 as often as it allows, then one 4 or 2, then the 3s.
 // ---------------------------------------------------------------------------
@@ -173,11 +228,14 @@ constexpr int ct_exp3(int n) {
   return b;
 }
 constexpr bool ct_r16(int n, int nt) { return nt >= 1 && n / nt >= 16 && ct_exp2(n) >= 4; }
-constexpr int ct_npass(int n, bool r16) {
-  const int a = ct_exp2(n), w = r16 ? 4 : 3;
+constexpr int ct_npass(int n, int nt) {
+  if (ct_plan_index(n) >= 0) return kCtPlans[ct_plan_index(n)].np;
+  const int a = ct_exp2(n), w = ct_r16(n, nt) ? 4 : 3;
   return a / w + (a % w ? 1 : 0) + ct_exp3(n);
 }
-constexpr int ct_radix(int n, bool r16, int p) {
+constexpr int ct_radix(int n, int nt, int p) {
+  if (ct_plan_index(n) >= 0) return kCtPlans[ct_plan_index(n)].r[p];
+  const bool r16 = ct_r16(n, nt);
   const int a = ct_exp2(n), w = r16 ? 4 : 3, nb = a / w, rem = a % w;
   if (p < nb) return r16 ? 16 : 8;
   p -= nb;
@@ -187,16 +245,16 @@ constexpr int ct_radix(int n, bool r16, int p) {
   }
   return 3;
 }
-constexpr int ct_ns(int n, bool r16, int p) {
+constexpr int ct_ns(int n, int nt, int p) {
   int ns = 1;
-  for (int i = 0; i < p; ++i) ns *= ct_radix(n, r16, i);
+  for (int i = 0; i < p; ++i) ns *= ct_radix(n, nt, i);
   return ns;
 }
-constexpr int ct_bt(int n, int nt, bool r16, int p) { return (n / ct_radix(n, r16, p) + nt - 1) / nt; }
-constexpr int ct_vmax(int n, int nt, bool r16) {
+constexpr int ct_bt(int n, int nt, int p) { return (n / ct_radix(n, nt, p) + nt - 1) / nt; }
+constexpr int ct_vmax(int n, int nt) {
   int m = 0;
-  for (int p = 0; p < ct_npass(n, r16); ++p) {
-    const int x = ct_bt(n, nt, r16, p) * ct_radix(n, r16, p);
+  for (int p = 0; p < ct_npass(n, nt); ++p) {
+    const int x = ct_bt(n, nt, p) * ct_radix(n, nt, p);
     m = x > m ? x : m;
   }
   return m;
@@ -220,13 +278,12 @@ template <typename T, int N> __device__ __forceinline__ int xpad(int i) {
 // x[b + r N/R] again.
 template <typename T, int N, int NT, bool INV>
 struct CtFft {
-  static constexpr bool R16 = ct_r16(N, NT);
-  static constexpr int NP = ct_npass(N, R16);
-  static constexpr int VMAX = ct_vmax(N, NT, R16);
+  static constexpr int NP = ct_npass(N, NT);
+  static constexpr int VMAX = ct_vmax(N, NT);
 
-  template <int P> static constexpr int R() { return ct_radix(N, R16, P); }
-  template <int P> static constexpr int NB() { return N / ct_radix(N, R16, P); }
-  template <int P> static constexpr int BT() { return ct_bt(N, NT, R16, P); }
+  template <int P> static constexpr int R() { return ct_radix(N, NT, P); }
+  template <int P> static constexpr int NB() { return N / ct_radix(N, NT, P); }
+  template <int P> static constexpr int BT() { return ct_bt(N, NT, P); }
   template <int P> __device__ static __forceinline__ bool valid(int b) {
     return (NB<P>() % NT == 0) || b < NB<P>();
   }
@@ -240,7 +297,7 @@ struct CtFft {
   // of it in LDS)
   template <int P, class Tw>
   __device__ static __forceinline__ void butterflies(cx<T>* v, int q, const Tw& tw) {
-    constexpr int Rr = R<P>(), NS = ct_ns(N, R16, P), TSTEP = N / (NS * Rr);
+    constexpr int Rr = R<P>(), NS = ct_ns(N, NT, P), TSTEP = N / (NS * Rr);
 #pragma unroll
     for (int t = 0; t < BT<P>(); ++t) {
       const int b = q + t * NT;
@@ -261,7 +318,7 @@ struct CtFft {
   // outputs of pass P -> LDS -> inputs of pass P + 1
   template <int P, class Idx>
   __device__ static __forceinline__ void exchange(cx<T>* v, cx<T>* lds, const Idx& li, int q) {
-    constexpr int Rr = R<P>(), NS = ct_ns(N, R16, P);
+    constexpr int Rr = R<P>(), NS = ct_ns(N, NT, P);
 #pragma unroll
     for (int t = 0; t < BT<P>(); ++t) {
       const int b = q + t * NT;
@@ -308,16 +365,16 @@ struct CtFft {
     run_from<0>(v, lds, li, q, tw);
   }
 
-  static constexpr int RL = ct_radix(N, R16, NP - 1);
-  static constexpr int BTL = ct_bt(N, NT, R16, NP - 1);
-  static constexpr int NBL = N / ct_radix(N, R16, NP - 1);
+  static constexpr int RL = ct_radix(N, NT, NP - 1);
+  static constexpr int BTL = ct_bt(N, NT, NP - 1);
+  static constexpr int NBL = N / ct_radix(N, NT, NP - 1);
   __device__ static __forceinline__ bool valid_last(int b) { return (NBL % NT == 0) || b < NBL; }
   // element index of value v[t RL + r] at the output of the last pass
   __device__ static __forceinline__ int out_index(int q, int t, int r) { return q + t * NT + r * NBL; }
 
-  static constexpr int R0 = ct_radix(N, R16, 0);
-  static constexpr int BT0 = ct_bt(N, NT, R16, 0);
-  static constexpr int NB0 = N / ct_radix(N, R16, 0);
+  static constexpr int R0 = ct_radix(N, NT, 0);
+  static constexpr int BT0 = ct_bt(N, NT, 0);
+  static constexpr int NB0 = N / ct_radix(N, NT, 0);
   __device__ static __forceinline__ bool valid_first(int b) { return (NB0 % NT == 0) || b < NB0; }
 };
 

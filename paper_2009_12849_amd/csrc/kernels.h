@@ -10,11 +10,34 @@ namespace monc {
 void init_kernel_attributes();
 void init_tridiag_attributes();  // the tridiagonal kernels' part of it
 
-// Transform lengths with a compile-time FFT kernel (others take the
-// runtime-length kernels); such kernels use n/8 threads per transform (1 if
-// n < 8; along y n/16 from n = 2048 on) and need blockDim = (transforms or
-// columns per workgroup) * that.
+// Transform lengths with compile-time FFT kernels: every 2^a 3^b from 16 to
+// 4096 (others take the runtime-length kernels). The kernels need blockDim =
+// (transforms or columns per workgroup) * threads per transform (ct_threads_x_n,
+// ct_threads_y_n). Their instances are compiled in groups, one object each
+// (fft_inst.hip with MONC_FFT_GROUP = 0..7).
+#define MONC_FFT_GROUPS(Y) Y(0) Y(1) Y(2) Y(3) Y(4) Y(5) Y(6) Y(7)
+#define MONC_CT_GROUP_0(X) X(16) X(64) X(192) X(486) X(1024) X(2187)
+#define MONC_CT_GROUP_1(X) X(18) X(72) X(216) X(512) X(1152) X(2304)
+#define MONC_CT_GROUP_2(X) X(24) X(81) X(243) X(576) X(1296) X(2592)
+#define MONC_CT_GROUP_3(X) X(27) X(96) X(256) X(648) X(1458) X(2916)
+#define MONC_CT_GROUP_4(X) X(32) X(108) X(288) X(729) X(1536) X(3072)
+#define MONC_CT_GROUP_5(X) X(36) X(128) X(324) X(768) X(1728) X(3456)
+#define MONC_CT_GROUP_6(X) X(48) X(144) X(384) X(864) X(1944) X(3888)
+#define MONC_CT_GROUP_7(X) X(54) X(162) X(432) X(972) X(2048) X(4096)
+// lengths with two y-FFT radix plans (8 or 16 elements per thread)
+// are those without a plan of their own (ct_plan_index < 0)
+// One group's instances: false if the group does not hold the length.
+#define MONC_GROUP_DECL(K)                                                                                          \
+  void init_fft_group_##K();                                                                                        \
+  bool launch_xfwd_group_##K(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int mode, int ct_n,   \
+                             void* stream);                                                                         \
+  bool launch_ffty_group_##K(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, bool inverse, int ct_n, \
+                             int ept, void* stream);                                                                \
+  bool launch_xinv_group_##K(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int mode, int ct_n,   \
+                             void* stream);
+
 bool ct_supported(int n);
+MONC_FFT_GROUPS(MONC_GROUP_DECL)
 // lengths with the persistent FP32 y-FFT kernel (32 elements per thread)
 bool pp_supported(int n);
 inline int ct_threads_host(int n) { return ct_threads_x_n(n); }

@@ -1,1094 +1,11 @@
-// HIP kernels of the pressure projection for gfx950 (wave64, LDS-staged).
-//
-// Phases of one projection (the FFT pressure solver of the paper's Sec. 4:
-// forward FFT, vertical ODE per wavenumber in Fourier space, backward FFT):
-//   xfwd     divergence D(u*) (or the FP64 residual D(u*) - D(G p1) of the
-//            mixed path) computed straight into the first radix pass of the
-//            x-direction real FFT; two real rows ride in one complex
-//            transform and are separated afterwards
-//   ffty     y-direction complex FFT of every (level, m) column
-//   tridiag  FP64 tridiagonal solve in z of every (m, n) column, partitioned
-//            over lanes, (0,0) column with the gauge
-//   xinv     x-direction complex-to-real FFT, writes p (or p1 + delta)
-//   grad     pressure-gradient correction u -= G p, w lid = 0
-//
-// The FFT phases exist twice: with the transform length fixed at compile
-// time (CtFft, for the lengths listed in kernels.h) and with a runtime length
-// (fft_lds) for every other 2^a 3^b length.
-//
-// Every kernel serves a group of members: blockIdx.x is mapped to a member
-// through LaunchArgs::block_start, and each member's sizes and tables come
-// from its MemberDesc.
+// Gradient kernels of the pressure projection for gfx950, and the dispatch of
+// the FFT kernels' launches to the instances of fft_inst.hip.
 #include <hip/hip_runtime.h>
 
-#include "device_common.h"
-#include "kernels.h"
+#include "fft_kernels.h"
 #include "launch.h"
 
 namespace monc {
-
-// ---------------------------------------------------------------------------
-// per-row context of the stencils: offsets of the neighbouring rows and the
-// vertical metrics of the row's level
-// ---------------------------------------------------------------------------
-struct RowCtx {
-  long long off;    // row (k, j)
-  long long soff;   // row (k, j-1)
-  long long noff;   // row (k, j+1)
-  long long plane;  // ny * nx
-  int k;
-  bool top;         // k < nz-1: a w face above
-  bool bot;         // k > 0: a w face below
-  double rho0, rhow, rhowm, rdz, rdzc, rdzcm;
-  float rho0f, rhowf, rhowmf, rdzf;
-};
-
-__device__ __forceinline__ RowCtx make_row(const MemberDesc& d, long long row, bool valid) {
-  RowCtx c;
-  const int ny = d.ny, nz = d.nz;
-  const long long r = valid ? row : 0;
-  // rows (ny nz of them) and their level and row index fit 32 bits
-  const int k = (int)r / ny;
-  const int j = (int)r - k * ny;
-  c.k = k;
-  c.off = r * d.nx;
-  c.soff = ((long long)k * ny + (j == 0 ? ny - 1 : j - 1)) * d.nx;
-  c.noff = ((long long)k * ny + (j == ny - 1 ? 0 : j + 1)) * d.nx;
-  c.plane = (long long)ny * d.nx;
-  c.top = k < nz - 1;
-  c.bot = k > 0;
-  const int km = c.bot ? k - 1 : k;
-  c.rho0 = ldg(d.rho0 + k);
-  c.rdz = ldg(d.rdz + k);
-  c.rhow = ldg(d.rhow + k);    // 0 on the lid row
-  c.rdzc = ldg(d.rdzc + k);    // 0 on the lid row
-  c.rhowm = c.bot ? ldg(d.rhow + km) : 0.0;
-  c.rdzcm = c.bot ? ldg(d.rdzc + km) : 0.0;
-  c.rho0f = ldg(d.rho0f + k);
-  c.rdzf = ldg(d.rdzf + k);
-  c.rhowf = ldg(d.rhowf + k);
-  c.rhowmf = c.bot ? ldg(d.rhowf + km) : 0.0f;
-  return c;
-}
-
-__device__ __forceinline__ RowCtx wuni(const RowCtx& c) {
-  RowCtx r;
-  r.off = wuni(c.off);
-  r.soff = wuni(c.soff);
-  r.noff = wuni(c.noff);
-  r.plane = wuni(c.plane);
-  r.k = wuni(c.k);
-  r.top = wuni((int)c.top) != 0;
-  r.bot = wuni((int)c.bot) != 0;
-  r.rho0 = wuni(c.rho0);
-  r.rhow = wuni(c.rhow);
-  r.rhowm = wuni(c.rhowm);
-  r.rdz = wuni(c.rdz);
-  r.rdzc = wuni(c.rdzc);
-  r.rdzcm = wuni(c.rdzcm);
-  r.rho0f = wuni(c.rho0f);
-  r.rhowf = wuni(c.rhowf);
-  r.rhowmf = wuni(c.rhowmf);
-  r.rdzf = wuni(c.rdzf);
-  return r;
-}
-
-template <typename T>
-__device__ __forceinline__ T div_at(const MemberDesc& d, const RowCtx& c, const T* __restrict__ u,
-                                    const T* __restrict__ v, const T* __restrict__ w, int i);
-
-template <>
-__device__ __forceinline__ double div_at<double>(const MemberDesc& d, const RowCtx& c, const double* __restrict__ u,
-                                                 const double* __restrict__ v, const double* __restrict__ w, int i) {
-  const int im = (i == 0) ? d.nx - 1 : i - 1;
-  const double hor = (u[c.off + i] - u[c.off + im]) * d.rdx + (v[c.off + i] - v[c.soff + i]) * d.rdy;
-  const double ft = c.top ? c.rhow * w[c.off + i] : 0.0;
-  const double fb = c.bot ? c.rhowm * w[c.off - c.plane + i] : 0.0;
-  return c.rho0 * hor + (ft - fb) * c.rdz;
-}
-
-template <>
-__device__ __forceinline__ float div_at<float>(const MemberDesc& d, const RowCtx& c, const float* __restrict__ u,
-                                               const float* __restrict__ v, const float* __restrict__ w, int i) {
-  const int im = (i == 0) ? d.nx - 1 : i - 1;
-  const float hor = (u[c.off + i] - u[c.off + im]) * d.rdxf + (v[c.off + i] - v[c.soff + i]) * d.rdyf;
-  const float ft = c.top ? c.rhowf * w[c.off + i] : 0.0f;
-  const float fb = c.bot ? c.rhowmf * w[c.off - c.plane + i] : 0.0f;
-  return c.rho0f * hor + (ft - fb) * c.rdzf;
-}
-
-// FP64 operator L p1 = D(G p1) at one point from the float first-pass
-// pressure p1 and its six neighbours (pE, pW along x, pN, pS along y, pU, pD
-// along z; pU, pD ignored on the lid and bottom rows).
-__device__ __forceinline__ double lap_at(const MemberDesc& d, const RowCtx& c, double p0, double pE, double pW,
-                                         double pN, double pS, double pU, double pD) {
-  const double gxe = (pE - p0) * d.rdx, gxw = (p0 - pW) * d.rdx;
-  const double gyn = (pN - p0) * d.rdy, gys = (p0 - pS) * d.rdy;
-  const double ft = c.top ? c.rhow * ((pU - p0) * c.rdzc) : 0.0;
-  const double fb = c.bot ? c.rhowm * ((p0 - pD) * c.rdzcm) : 0.0;
-  return c.rho0 * ((gxe - gxw) * d.rdx + (gyn - gys) * d.rdy) + (ft - fb) * c.rdz;
-}
-
-// FP64 divergence D(u*) of float fields at one point
-__device__ __forceinline__ double div64_at(const MemberDesc& d, const RowCtx& c, const float* __restrict__ u,
-                                           const float* __restrict__ v, const float* __restrict__ w, int i) {
-  const int im = (i == 0) ? d.nx - 1 : i - 1;
-  const double hor = ((double)u[c.off + i] - (double)u[c.off + im]) * d.rdx +
-                     ((double)v[c.off + i] - (double)v[c.soff + i]) * d.rdy;
-  const double ft = c.top ? c.rhow * (double)w[c.off + i] : 0.0;
-  const double fb = c.bot ? c.rhowm * (double)w[c.off - c.plane + i] : 0.0;
-  return c.rho0 * hor + (ft - fb) * c.rdz;
-}
-
-// FP64 residual r = D(u*) - L p1 of the mixed path at one point, from the
-// float inputs u*, v*, w* and the first-pass pressure p1 (io.s2).
-__device__ __forceinline__ double resid_at(const MemberDesc& d, const RowCtx& c, const IoPtrs& io, int i) {
-  const float* __restrict__ p = io.s2;
-  const int nx = d.nx;
-  const int im = (i == 0) ? nx - 1 : i - 1;
-  const int ip = (i == nx - 1) ? 0 : i + 1;
-  const double pc = p[c.off + i];
-  const double pu = c.top ? (double)p[c.off + c.plane + i] : pc;
-  const double pd = c.bot ? (double)p[c.off - c.plane + i] : pc;
-  const double b = div64_at(d, c, reinterpret_cast<const float*>(io.u), reinterpret_cast<const float*>(io.v),
-                            reinterpret_cast<const float*>(io.w), i);
-  return b - lap_at(d, c, pc, p[c.off + ip], p[c.off + im], p[c.noff + i], p[c.soff + i], pu, pd);
-}
-
-// Sources of the x-forward transform: MODE 0 the divergence D(u*), MODE 1
-// the mixed path's FP64 residual D(u*) - L p1, MODE 2 a given FP64 field
-// (io.u) rounded to T, i.e. the spectral solve applied to an arbitrary
-// right-hand side (the preconditioner of the variable-density Krylov
-// solver).
-template <typename T, int MODE>
-__device__ __forceinline__ T source_at(const MemberDesc& d, const RowCtx& c, const IoPtrs& io, int i) {
-  if constexpr (MODE == 0) {
-    return div_at<T>(d, c, reinterpret_cast<const T*>(io.u), reinterpret_cast<const T*>(io.v),
-                     reinterpret_cast<const T*>(io.w), i);
-  } else if constexpr (MODE == 2) {
-    return (T)reinterpret_cast<const double*>(io.u)[c.off + i];
-  } else {
-    return (T)resid_at(d, c, io, i);
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Vector forms of the stencils: V = 16 bytes / sizeof(T) consecutive points
-// of one row from 16-byte loads (rows start 16-byte aligned: nx is a
-// multiple of V for every compile-time length). The x-neighbours outside
-// the vector come from scalar loads (cache hits).
-// ---------------------------------------------------------------------------
-template <typename T> struct Vec {
-  static constexpr int n = 16 / sizeof(T);
-  typedef T type __attribute__((ext_vector_type(16 / sizeof(T))));
-};
-
-template <typename T>
-__device__ __forceinline__ typename Vec<T>::type ldv(const T* p) {
-  return *reinterpret_cast<const typename Vec<T>::type*>(p);
-}
-
-template <typename T>
-__device__ __forceinline__ void stv(T* p, typename Vec<T>::type x) {
-  *reinterpret_cast<typename Vec<T>::type*>(p) = x;
-}
-
-// divergence D(u) at points i0 .. i0+V-1 of a row, arithmetic in T
-template <typename T>
-__device__ __forceinline__ void div_vec(const MemberDesc& d, const RowCtx& c, const IoPtrs& io, int i0, T* out) {
-  constexpr int V = Vec<T>::n;
-  using vt = typename Vec<T>::type;
-  const T* __restrict__ u = reinterpret_cast<const T*>(io.u);
-  const T* __restrict__ v = reinterpret_cast<const T*>(io.v);
-  const T* __restrict__ w = reinterpret_cast<const T*>(io.w);
-  const bool f64 = sizeof(T) == 8;
-  const T rdx = f64 ? (T)d.rdx : (T)d.rdxf, rdy = f64 ? (T)d.rdy : (T)d.rdyf;
-  const T rho0 = f64 ? (T)c.rho0 : (T)c.rho0f, rdz = f64 ? (T)c.rdz : (T)c.rdzf;
-  const T rhow = f64 ? (T)c.rhow : (T)c.rhowf, rhowm = f64 ? (T)c.rhowm : (T)c.rhowmf;
-  const vt uc = ldv(u + c.off + i0);
-  const T um = u[c.off + (i0 == 0 ? d.nx - 1 : i0 - 1)];
-  const vt vc = ldv(v + c.off + i0), vs = ldv(v + c.soff + i0);
-  vt wc = (vt)(T)0, wb = (vt)(T)0;
-  if constexpr (sizeof(T) == 8) {
-    // FP64: both w loads unconditional (level k clamped on the bottom row) so
-    // they issue with the others; the lid and bottom faces are selected away
-    const vt wcl = ldv(w + c.off + i0), wbl = ldv(w + c.off - (c.bot ? c.plane : 0) + i0);
-#pragma unroll
-    for (int e = 0; e < V; ++e) {
-      wc[e] = c.top ? wcl[e] : (T)0;
-      wb[e] = c.bot ? wbl[e] : (T)0;
-    }
-  } else {
-    // FP32: the branches keep fewer loads in flight and fewer registers live,
-    // which measures faster here
-    if (c.top) wc = ldv(w + c.off + i0);
-    if (c.bot) wb = ldv(w + c.off - c.plane + i0);
-  }
-#pragma unroll
-  for (int e = 0; e < V; ++e) {
-    const T uw = e ? uc[e - 1] : um;
-    out[e] = rho0 * ((uc[e] - uw) * rdx + (vc[e] - vs[e]) * rdy) + (rhow * wc[e] - rhowm * wb[e]) * rdz;
-  }
-}
-
-// Both rows of a pair (k, j) and (k, j+1) of one level: row j's v is row j+1's
-// southern neighbour, so 11 loads serve the two rows instead of 12. The
-// arithmetic is div_vec's, term for term.
-template <typename T>
-__device__ __forceinline__ void div_pair_vec(const MemberDesc& d, const RowCtx& c0, const RowCtx& c1,
-                                             const IoPtrs& io, int i0, T* out0, T* out1) {
-  constexpr int V = Vec<T>::n;
-  using vt = typename Vec<T>::type;
-  const T* __restrict__ u = reinterpret_cast<const T*>(io.u);
-  const T* __restrict__ v = reinterpret_cast<const T*>(io.v);
-  const T* __restrict__ w = reinterpret_cast<const T*>(io.w);
-  const bool f64 = sizeof(T) == 8;
-  const T rdx = f64 ? (T)d.rdx : (T)d.rdxf, rdy = f64 ? (T)d.rdy : (T)d.rdyf;
-  // one level: both rows share the vertical coefficients and lid flags
-  const T rho0 = f64 ? (T)c0.rho0 : (T)c0.rho0f, rdz = f64 ? (T)c0.rdz : (T)c0.rdzf;
-  const T rhow = f64 ? (T)c0.rhow : (T)c0.rhowf, rhowm = f64 ? (T)c0.rhowm : (T)c0.rhowmf;
-  const int iw = (i0 == 0) ? d.nx - 1 : i0 - 1;
-  const vt u0 = ldv(u + c0.off + i0), u1 = ldv(u + c1.off + i0);
-  const T um0 = u[c0.off + iw], um1 = u[c1.off + iw];
-  const vt vs = ldv(v + c0.soff + i0), v0 = ldv(v + c0.off + i0), v1 = ldv(v + c1.off + i0);
-  vt wc0 = (vt)(T)0, wb0 = (vt)(T)0, wc1 = (vt)(T)0, wb1 = (vt)(T)0;
-  if constexpr (sizeof(T) == 8) {
-    const long long bo = c0.bot ? c0.plane : 0;
-    const vt a0 = ldv(w + c0.off + i0), a1 = ldv(w + c1.off + i0);
-    const vt b0 = ldv(w + c0.off - bo + i0), b1 = ldv(w + c1.off - bo + i0);
-#pragma unroll
-    for (int e = 0; e < V; ++e) {
-      wc0[e] = c0.top ? a0[e] : (T)0;
-      wc1[e] = c0.top ? a1[e] : (T)0;
-      wb0[e] = c0.bot ? b0[e] : (T)0;
-      wb1[e] = c0.bot ? b1[e] : (T)0;
-    }
-  } else {
-    if (c0.top) {
-      wc0 = ldv(w + c0.off + i0);
-      wc1 = ldv(w + c1.off + i0);
-    }
-    if (c0.bot) {
-      wb0 = ldv(w + c0.off - c0.plane + i0);
-      wb1 = ldv(w + c1.off - c0.plane + i0);
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < V; ++e) {
-    const T uw0 = e ? u0[e - 1] : um0, uw1 = e ? u1[e - 1] : um1;
-    out0[e] = rho0 * ((u0[e] - uw0) * rdx + (v0[e] - vs[e]) * rdy) + (rhow * wc0[e] - rhowm * wb0[e]) * rdz;
-    out1[e] = rho0 * ((u1[e] - uw1) * rdx + (v1[e] - v0[e]) * rdy) + (rhow * wc1[e] - rhowm * wb1[e]) * rdz;
-  }
-}
-
-typedef float f4v __attribute__((ext_vector_type(4)));
-template <int W> using fwv = float __attribute__((ext_vector_type(W)));
-
-template <int W>
-__device__ __forceinline__ fwv<W> ldw(const float* p) {
-  return *reinterpret_cast<const fwv<W>*>(p);
-}
-
-// FP64 residual D(u*) - L p1 at points i0 .. i0+W-1 of a row from the loaded
-// neighbourhood (float data; pc: p1 of the row, pn/ps: rows j +- 1, pu/pd:
-// levels k +- 1, pe/pw: x-neighbours outside the vector, um: u west of the
-// vector; pu/pd, wc/wb ignored on the lid and bottom rows).
-// The same terms as div64_at - lap_at with the row's coefficients multiplied
-// out once (rho0/dx, rho0/dx^2, ...) and every pressure difference taken
-// before it is scaled: one FP64 fused multiply-add per term. The callers pass
-// wc = 0 and pu = pc on the lid row, wb = 0 and pd = pc on the bottom row,
-// where the row's rhow (lid) and rhowm (bottom) are 0 as well. A point's
-// value does not depend on W.
-template <int W>
-__device__ __forceinline__ void resid_core(const MemberDesc& d, const RowCtx& c, fwv<W> pc, fwv<W> pn, fwv<W> ps,
-                                           fwv<W> pu, fwv<W> pd, float pw, float pe, fwv<W> uc, float um,
-                                           fwv<W> vc, fwv<W> vs, fwv<W> wc, fwv<W> wb, float* out) {
-  const double bx = c.rho0 * d.rdx, by = c.rho0 * d.rdy;      // D(u*) horizontal
-  const double wt = c.rdz * c.rhow, wm = c.rdz * c.rhowm;     // D(u*) vertical
-  const double ax = bx * d.rdx, ay = by * d.rdy;              // L p1 horizontal
-  const double cu = wt * c.rdzc, cd = wm * c.rdzcm;           // L p1 vertical
-#pragma unroll
-  for (int e = 0; e < W; ++e) {
-    const double uW = (e > 0) ? (double)uc[e > 0 ? e - 1 : 0] : (double)um;
-    const double p0 = pc[e];
-    const double pE = (e < W - 1) ? (double)pc[e < W - 1 ? e + 1 : 0] : (double)pe;
-    const double pW = (e > 0) ? (double)pc[e > 0 ? e - 1 : 0] : (double)pw;
-    const double dxx = (pE - p0) - (p0 - pW), dyy = ((double)pn[e] - p0) - (p0 - (double)ps[e]);
-    double r = bx * ((double)uc[e] - uW);
-    r = fma(by, (double)vc[e] - (double)vs[e], r);
-    r = fma(wt, (double)wc[e], r);
-    r = fma(-wm, (double)wb[e], r);
-    r = fma(-ax, dxx, r);
-    r = fma(-ay, dyy, r);
-    r = fma(-cu, (double)pu[e] - p0, r);
-    r = fma(cd, p0 - (double)pd[e], r);
-    out[e] = (float)r;
-  }
-}
-
-template <int W>
-__device__ __forceinline__ void resid_vec(const MemberDesc& d, const RowCtx& c, const IoPtrs& io, int i0,
-                                          float* out) {
-  const float* __restrict__ u = reinterpret_cast<const float*>(io.u);
-  const float* __restrict__ v = reinterpret_cast<const float*>(io.v);
-  const float* __restrict__ w = reinterpret_cast<const float*>(io.w);
-  const float* __restrict__ p = io.s2;
-  const int nx = d.nx;
-  const int iw = (i0 == 0) ? nx - 1 : i0 - 1, ie = (i0 + W == nx) ? 0 : i0 + W;
-  const fwv<W> pc = ldw<W>(p + c.off + i0);
-  const float pw = p[c.off + iw], pe = p[c.off + ie];
-  const fwv<W> pn = ldw<W>(p + c.noff + i0), ps = ldw<W>(p + c.soff + i0);
-  const fwv<W> uc = ldw<W>(u + c.off + i0);
-  const float um = u[c.off + iw];
-  const fwv<W> vc = ldw<W>(v + c.off + i0), vs = ldw<W>(v + c.soff + i0);
-  fwv<W> pu = pc, pd = pc, wc = (fwv<W>)0.0f, wb = (fwv<W>)0.0f;
-  if (c.top) {
-    pu = ldw<W>(p + c.off + c.plane + i0);
-    wc = ldw<W>(w + c.off + i0);
-  }
-  if (c.bot) {
-    pd = ldw<W>(p + c.off - c.plane + i0);
-    wb = ldw<W>(w + c.off - c.plane + i0);
-  }
-  resid_core<W>(d, c, pc, pn, ps, pu, pd, pw, pe, uc, um, vc, vs, wc, wb, out);
-}
-
-// Both rows of a pair (k, j) and (k, j+1) of one level: they share p1 rows j
-// and j+1 and v row j, so 17 vector loads serve the two rows instead of 20.
-template <int W>
-__device__ __forceinline__ void resid_pair_vec(const MemberDesc& d, const RowCtx& c0, const RowCtx& c1,
-                                               const IoPtrs& io, int i0, float* out0, float* out1) {
-  const float* __restrict__ u = reinterpret_cast<const float*>(io.u);
-  const float* __restrict__ v = reinterpret_cast<const float*>(io.v);
-  const float* __restrict__ w = reinterpret_cast<const float*>(io.w);
-  const float* __restrict__ p = io.s2;
-  const int nx = d.nx;
-  const int iw = (i0 == 0) ? nx - 1 : i0 - 1, ie = (i0 + W == nx) ? 0 : i0 + W;
-  const fwv<W> ps = ldw<W>(p + c0.soff + i0), p0 = ldw<W>(p + c0.off + i0), p1 = ldw<W>(p + c1.off + i0);
-  const fwv<W> p2 = ldw<W>(p + c1.noff + i0);
-  const float pw0 = p[c0.off + iw], pe0 = p[c0.off + ie], pw1 = p[c1.off + iw], pe1 = p[c1.off + ie];
-  const fwv<W> u0 = ldw<W>(u + c0.off + i0), u1 = ldw<W>(u + c1.off + i0);
-  const float um0 = u[c0.off + iw], um1 = u[c1.off + iw];
-  const fwv<W> vs = ldw<W>(v + c0.soff + i0), v0 = ldw<W>(v + c0.off + i0), v1 = ldw<W>(v + c1.off + i0);
-  fwv<W> pu0 = p0, pd0 = p0, pu1 = p1, pd1 = p1;
-  fwv<W> wc0 = (fwv<W>)0.0f, wb0 = (fwv<W>)0.0f, wc1 = (fwv<W>)0.0f, wb1 = (fwv<W>)0.0f;
-  if (c0.top) {  // one level: c0.top == c1.top, c0.bot == c1.bot
-    pu0 = ldw<W>(p + c0.off + c0.plane + i0);
-    pu1 = ldw<W>(p + c1.off + c1.plane + i0);
-    wc0 = ldw<W>(w + c0.off + i0);
-    wc1 = ldw<W>(w + c1.off + i0);
-  }
-  if (c0.bot) {
-    pd0 = ldw<W>(p + c0.off - c0.plane + i0);
-    pd1 = ldw<W>(p + c1.off - c1.plane + i0);
-    wb0 = ldw<W>(w + c0.off - c0.plane + i0);
-    wb1 = ldw<W>(w + c1.off - c1.plane + i0);
-  }
-  resid_core<W>(d, c0, p0, p1, ps, pu0, pd0, pw0, pe0, u0, um0, v0, vs, wc0, wb0, out0);
-  resid_core<W>(d, c1, p1, p2, p0, pu1, pd1, pw1, pe1, u1, um1, v1, v0, wc1, wb1, out1);
-}
-
-template <typename T, int MODE>
-__device__ __forceinline__ void source_vec(const MemberDesc& d, const RowCtx& c, const IoPtrs& io, int i0, T* out) {
-  if constexpr (MODE == 0) {
-    div_vec<T>(d, c, io, i0, out);
-  } else if constexpr (MODE == 2) {
-    const double* __restrict__ r = reinterpret_cast<const double*>(io.u) + c.off + i0;
-#pragma unroll
-    for (int e = 0; e < Vec<T>::n; e += 2) {
-      const Vec<double>::type x = ldv(r + e);
-      out[e] = (T)x[0];
-      out[e + 1] = (T)x[1];
-    }
-  } else {
-    resid_vec<4>(d, c, io, i0, reinterpret_cast<float*>(out));
-  }
-}
-
-// Separate two real rows packed as z = a + i b:
-// A[m] = (Z[m] + conj Z[N-m])/2, B[m] = (Z[m] - conj Z[N-m])/(2i).
-// (row 0 gives A[m], row 1 gives B[m]; zr = Z[N-m])
-template <typename T>
-__device__ __forceinline__ cx<T> split_bin(cx<T> z, cx<T> zr, int row) {
-  const T h = (T)0.5;
-  return row ? cx<T>{h * (z.y + zr.y), h * (zr.x - z.x)} : cx<T>{h * (z.x + zr.x), h * (z.y - zr.y)};
-}
-
-// Spectral layout (column blocks of sbw bins, see MemberDesc): the value of
-// row r = k*ny + j at bin m sits at spec_row(r) + spec_col(m). Levels are
-// `plane` apart (padded so that the plane stride is an odd multiple of 256
-// bytes); inside a block the rows are sbw apart, so a y-FFT tile of sbw
-// columns is one contiguous run and a row pair writes 2 sbw adjacent values.
-__device__ __forceinline__ long long spec_row(const MemberDesc& d, long long r) {
-  const int k = (int)r / d.ny;
-  return (long long)k * d.plane + (long long)((int)r - k * d.ny) * d.sbw;
-}
-__device__ __forceinline__ long long spec_col(const MemberDesc& d, int m) {
-  return (long long)(m >> d.lbw) * d.bst + (m & (d.sbw - 1));
-}
-// A row pair's spectral values in slot order: slots walk the column blocks,
-// and inside a block first row 0's sbw bins, then row 1's. When the two rows
-// are adjacent (same level) that is their memory order, so consecutive lanes
-// touch consecutive addresses and a store or load covers 2 sbw values at a
-// time. Slot s holds bin m of row `row` at offset `off` from the row start.
-struct PairSlot {
-  int row, m;
-  long long off;
-};
-__device__ __forceinline__ PairSlot pair_slot(const MemberDesc& d, int s) {
-  const int blk = s >> (d.lbw + 1), w = s & (2 * d.sbw - 1);
-  return PairSlot{w >> d.lbw, (blk << d.lbw) | (w & (d.sbw - 1)), (long long)blk * d.bst + (w & (d.sbw - 1))};
-}
-// slots covering bins 0 .. nxh-1 (whole blocks)
-__device__ __forceinline__ int pair_slots(const MemberDesc& d) { return ((d.nxh + d.sbw - 1) >> d.lbw) << (d.lbw + 1); }
-
-// Row pairs of the stencil kernels in (level, pair) tiles: consecutive
-// pair slots walk d.ptj pairs of d.ptk consecutive levels before moving on, so
-// the rows a stencil re-reads (levels k +- 1, rows j +- 1) are read by
-// workgroups that run at about the same time on the same XCD and meet in its
-// L2. ptk = 1 or odd ny (pairs straddle levels) keeps the linear order.
-// Bijection of [0, nz * per) that walks tiles of TJ consecutive items of TK
-// consecutive levels (per items per level), ragged tiles at the edges;
-// identity for TK <= 1 and beyond the grid.
-// (32-bit arithmetic: nz * per, a count of rows or row pairs, fits 32 bits)
-__device__ __forceinline__ long long tiled_index(long long p, long long per, int nz, int TK, int TJ) {
-  if (TK <= 1 || p >= (long long)nz * per) return p;
-  const int pi = (int)p, pe = (int)per;
-  const int blk = TK * pe;
-  const int kb = pi / blk;
-  const int rem = pi - kb * blk;
-  const int tk = min(TK, nz - kb * TK);          // levels in this block
-  const int jt = rem / (tk * TJ);
-  const int tj = min(TJ, pe - jt * TJ);
-  const int in = rem - jt * tk * TJ;
-  const int k = kb * TK + in / tj;
-  const int jp = jt * TJ + in % tj;
-  return (long long)k * pe + jp;
-}
-
-__device__ __forceinline__ long long tiled_pair(const MemberDesc& d, long long p) {
-  if (d.ny & 1) return p;
-  return tiled_index(p, d.ny / 2, d.nz, d.ptk, d.ptj);
-}
-
-// ---------------------------------------------------------------------------
-// x-direction forward real FFT, compile-time length N (NT = ct_threads(N)
-// threads per transform: N/16 from 512 points, N/8 below; blockDim =
-// transforms per workgroup * NT)
-// ---------------------------------------------------------------------------
-// The residual variant at lengths whose transforms share a wave and whose
-// stencil does not walk whole rows per wave (lengths that are not a multiple
-// of 64, such as 16-48, 96, 144, 288, or whose whole-wave workgroups would
-// pass 512 threads: 576, 1152, 2304) keeps its row contexts in vector
-// registers: about 172 registers, 2 waves per SIMD. A budget for 3 spills 2-6
-// registers and measured about 1 % faster where it applied before the
-// whole-row stencil; a budget for 5 waves at the longer lengths spills 16 and
-// loses 6 %.
-template <typename T, int MODE, int N>
-__global__ void __launch_bounds__(512)
-    __attribute__((amdgpu_waves_per_eu(MODE == 1 && ct_threads(N) % 64 != 0 && !xres_wave_rows(N) ? 3 : 1, 8)))
-    k_xfwd_ct(LaunchArgs a) {
-  constexpr int NT = ct_threads(N);
-  using F = CtFft<T, N, NT, false>;
-  extern __shared__ unsigned char smem_raw[];
-  const int mi = find_member(a, blockIdx.x);
-  const MemberDesc& d = *a.mem[mi];
-  if (skipped(d)) return;
-  const IoPtrs io = a.io[mi];
-  // workgroups in launch order for the residual (1-7 % faster than grouped
-  // by XCD: 2048^2 x 160, 1024^2 x 256, 4096^2 x 64 and the ensemble), by XCD
-  // for the divergence (FP32 2 % faster that way at 2048^2 x 160; FP64 4 %
-  // slower there but 7 % faster at 4096^2 x 64) and the given-field mode
-  constexpr bool PLAIN = MODE == 1;
-  const int lb = PLAIN ? (int)blockIdx.x - a.block_start[mi] : xcd_local_block(a, mi);
-  const int ipw = blockDim.x / NT;
-  // scalar row contexts for the residual only, and only where a transform
-  // spans whole waves (NT a multiple of 64: then no wave holds lanes of two
-  // transforms): its registers fall from 174 to 126 and its occupancy rises
-  // from 2 to 4 waves per SIMD, and it gains; the divergence variants measure
-  // slower with scalar contexts
-  constexpr bool UNI = NT % 64 == 0 && MODE == 1;
-  const int inst = UNI ? wuni((int)(threadIdx.x / NT)) : (int)(threadIdx.x / NT);
-  const int q = threadIdx.x - inst * NT;
-  cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw) + inst * xlds_len(N, 2 * sizeof(T));
-  const long long pair = tiled_pair(d, (long long)lb * ipw + inst);
-  const long long r0 = 2 * pair, r1 = 2 * pair + 1;
-  const bool v0 = r0 < d.nrow, v1 = r1 < d.nrow;
-  RowCtx c0 = make_row(d, r0, v0), c1 = make_row(d, r1, v1);
-  if constexpr (UNI) {
-    c0 = wuni(c0);
-    c1 = wuni(c1);
-  }
-  // 1. vector phase: the stencil on 16-byte chunks of both rows, packed as
-  //    z = row0 + i row1 into LDS in natural order: chunk i0 of the rows with
-  //    contexts (c0, c1) and validity (v0, v1) into transform slot L
-  constexpr int V = Vec<T>::n;
-  auto stencil = [&](const RowCtx& c0, const RowCtx& c1, bool v0, bool v1, int i0, cx<T>* L) {
-    T s0[V], s1[V];
-    // a full pair within one level (even ny): the two rows share loads
-    const bool pair = !(d.ny & 1) && v1;
-    if constexpr (sizeof(T) == 8) {
-      if (MODE == 0 && pair) {
-        div_pair_vec<T>(d, c0, c1, io, i0, s0, s1);
-      } else {
-        // both rows unconditionally (an invalid row's context points at row
-        // 0), so all loads of the chunk issue together; invalid rows zeroed
-        source_vec<T, MODE>(d, c0, io, i0, s0);
-        source_vec<T, MODE>(d, c1, io, i0, s1);
-#pragma unroll
-        for (int e = 0; e < V; ++e) {
-          s0[e] = v0 ? s0[e] : (T)0;
-          s1[e] = v1 ? s1[e] : (T)0;
-        }
-      }
-    } else {
-      if (pair && MODE == 0) {
-        div_pair_vec<T>(d, c0, c1, io, i0, s0, s1);
-      } else if (pair && MODE == 1) {
-        resid_pair_vec<4>(d, c0, c1, io, i0, s0, s1);
-      } else {
-        if (v0) source_vec<T, MODE>(d, c0, io, i0, s0);
-        else
-          for (int e = 0; e < V; ++e) s0[e] = (T)0;
-        if (v1) source_vec<T, MODE>(d, c1, io, i0, s1);
-        else
-          for (int e = 0; e < V; ++e) s1[e] = (T)0;
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < V; ++e) L[xpad<T, N>(i0 + e)] = cx<T>{s0[e], s1[e]};
-  };
-  if constexpr (MODE == 1 && xres_wave_rows(N)) {
-    // residual with transforms narrower than a wave: each wave takes one
-    // transform's run of 64 chunks of W points at a time (the host launches
-    // whole waves), so the row contexts are wave-uniform, in scalar
-    // registers, as in the case above; this halves the registers and doubles
-    // the waves. Every point's value is the per-thread mapping's.
-    constexpr int W = xres_chunk(N);
-    constexpr int C = N / (64 * W);  // wave runs per transform
-    const int nw = blockDim.x / 64, wv = wuni((int)(threadIdx.x / 64)), ln = threadIdx.x & 63;
-    cx<T>* lds0 = reinterpret_cast<cx<T>*>(smem_raw);
-    for (int it = wv; it < ipw * C; it += nw) {
-      const int ins = it / C, ch = it - ins * C;
-      const long long pr = tiled_pair(d, (long long)lb * ipw + ins);
-      const bool w0 = 2 * pr < d.nrow, w1 = 2 * pr + 1 < d.nrow;
-      const RowCtx e0 = wuni(make_row(d, 2 * pr, w0)), e1 = wuni(make_row(d, 2 * pr + 1, w1));
-      const int i0 = (ch * 64 + ln) * W;
-      float s0[W], s1[W];
-      if (!(d.ny & 1) && w1) {
-        resid_pair_vec<W>(d, e0, e1, io, i0, s0, s1);
-      } else {
-        if (w0) resid_vec<W>(d, e0, io, i0, s0);
-        else
-          for (int e = 0; e < W; ++e) s0[e] = 0.0f;
-        if (w1) resid_vec<W>(d, e1, io, i0, s1);
-        else
-          for (int e = 0; e < W; ++e) s1[e] = 0.0f;
-      }
-      cx<T>* L = lds0 + ins * xlds_len(N, 2 * sizeof(T));
-#pragma unroll
-      for (int e = 0; e < W; ++e) L[xpad<T, N>(i0 + e)] = cx<T>{s0[e], s1[e]};
-    }
-  } else {
-#pragma unroll
-    for (int t = 0; t < N / (V * NT); ++t) stencil(c0, c1, v0, v1, (q + t * NT) * V, lds);
-  }
-  __syncthreads();
-  cx<T> v[F::VMAX];
-#pragma unroll
-  for (int t = 0; t < F::BT0; ++t) {
-    const int b = q + t * NT;
-    if (F::valid_first(b)) {
-#pragma unroll
-      for (int r = 0; r < F::R0; ++r) v[t * F::R0 + r] = lds[xpad<T, N>(b + r * F::NB0)];
-    }
-  }
-  __syncthreads();
-  auto li = [](int i) { return xpad<T, N>(i); };
-  F::run(v, lds, li, q, reinterpret_cast<const cx<T>*>(d.twx));
-#pragma unroll
-  for (int t = 0; t < F::BTL; ++t) {
-    const int b = q + t * NT;
-    if (F::valid_last(b)) {
-#pragma unroll
-      for (int r = 0; r < F::RL; ++r) lds[xpad<T, N>(F::out_index(q, t, r))] = v[t * F::RL + r];
-    }
-  }
-  __syncthreads();
-  cx<T>* S = reinterpret_cast<cx<T>*>(io.spec);
-  const long long so0 = spec_row(d, v0 ? r0 : 0), so1 = spec_row(d, v1 ? r1 : 0);
-  const int ns = pair_slots(d);
-  if (sizeof(T) == 4 && d.sbw >= 2) {
-    // FP32 with column blocks at least 2 wide: a lane takes two adjacent
-    // slots (bins m, m+1 of one row, adjacent in memory, 16-byte aligned:
-    // m, the block and row offsets and the plane are even) and stores them
-    // with one 16-byte access; a block's last valid bin may be alone. Half
-    // the store instructions of one slot per lane, which measured as the
-    // costliest phase of these kernels.
-    for (int s2 = q; s2 < ns / 2; s2 += NT) {
-      const PairSlot ps = pair_slot(d, 2 * s2);
-      if (ps.m < d.nxh && (ps.row ? v1 : v0)) {
-        const cx<T> b0 = split_bin<T>(lds[xpad<T, N>(ps.m)], lds[xpad<T, N>(ps.m == 0 ? 0 : N - ps.m)], ps.row);
-        cx<T>* dst = S + (ps.row ? so1 : so0) + ps.off;
-        if (ps.m + 1 < d.nxh) {
-          const cx<T> b1 = split_bin<T>(lds[xpad<T, N>(ps.m + 1)], lds[xpad<T, N>(N - ps.m - 1)], ps.row);
-          typedef T t4 __attribute__((ext_vector_type(4)));
-          t4 v;
-          v[0] = b0.x;
-          v[1] = b0.y;
-          v[2] = b1.x;
-          v[3] = b1.y;
-          *reinterpret_cast<t4*>(dst) = v;
-        } else {
-          *dst = b0;
-        }
-      }
-    }
-  } else {
-    for (int s = q; s < ns; s += NT) {
-      const PairSlot ps = pair_slot(d, s);
-      if (ps.m < d.nxh && (ps.row ? v1 : v0)) {
-        const cx<T> z = lds[xpad<T, N>(ps.m)];
-        const cx<T> zr = lds[xpad<T, N>(ps.m == 0 ? 0 : N - ps.m)];
-        S[(ps.row ? so1 : so0) + ps.off] = split_bin<T>(z, zr, ps.row);
-      }
-    }
-  }
-}
-
-// runtime length (fallback)
-template <typename T, int MODE>
-__global__ void __launch_bounds__(1024) k_xfwd_gen(LaunchArgs a) {
-  extern __shared__ unsigned char smem_raw[];
-  cx<T>* smem = reinterpret_cast<cx<T>*>(smem_raw);
-  const int mi = find_member(a, blockIdx.x);
-  const MemberDesc& d = *a.mem[mi];
-  if (skipped(d)) return;
-  const IoPtrs io = a.io[mi];
-  const int lb = xcd_local_block(a, mi);
-  const int N = d.nx, nt = d.fx.nt;
-  const int ipw = blockDim.x / nt;
-  const int inst = threadIdx.x / nt;
-  const bool active = inst < ipw;
-  const int q = active ? (int)(threadIdx.x - inst * nt) : kBig;
-  cx<T>* buf = smem + (active ? inst : 0) * N;
-  const long long pair = tiled_pair(d, (long long)lb * ipw + inst);
-  const long long r0 = 2 * pair, r1 = 2 * pair + 1;
-  const bool v0 = active && r0 < d.nrow, v1 = active && r1 < d.nrow;
-  const RowCtx c0 = make_row(d, r0, v0), c1 = make_row(d, r1, v1);
-  if (active) {
-    for (int i = q; i < N; i += nt) {
-      const T s0 = v0 ? source_at<T, MODE>(d, c0, io, i) : (T)0;
-      const T s1 = v1 ? source_at<T, MODE>(d, c1, io, i) : (T)0;
-      buf[i] = cx<T>{s0, s1};
-    }
-  }
-  __syncthreads();
-  fft_lds<T, false>(buf, 1, d.fx, reinterpret_cast<const cx<T>*>(d.twx), q);
-  if (active) {
-    cx<T>* S = reinterpret_cast<cx<T>*>(io.spec);
-    const long long so0 = spec_row(d, v0 ? r0 : 0), so1 = spec_row(d, v1 ? r1 : 0);
-    for (int m = q; m < d.nxh; m += nt) {
-      const cx<T> z = buf[m], zr = buf[m == 0 ? 0 : N - m];
-      const long long cm = spec_col(d, m);
-      if (v0) S[so0 + cm] = split_bin<T>(z, zr, 0);
-      if (v1) S[so1 + cm] = split_bin<T>(z, zr, 1);
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// y-direction complex FFT, in place on the spectral buffer. A workgroup takes
-// one level and MT = blockDim / NT consecutive m columns; LDS holds them as
-// [j][c] so that consecutive lanes touch consecutive columns (128-byte rows).
-// ---------------------------------------------------------------------------
-template <typename T, bool INV, int N, int EPT>
-__global__ void __launch_bounds__(1024) k_ffty_ct(LaunchArgs a) {
-  constexpr int NT = ct_threads_y(N, EPT);
-  using F = CtFft<T, N, NT, INV>;
-  extern __shared__ unsigned char smem_raw[];
-  cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
-  const int mi = find_member(a, blockIdx.x);
-  const MemberDesc& d = *a.mem[mi];
-  if (skipped(d)) return;
-  const IoPtrs io = a.io[mi];
-  const int lb = xcd_local_block(a, mi);
-  const int mt = blockDim.x / NT;
-  const int tiles = (d.nxh + mt - 1) / mt;
-  const int k = lb / tiles;
-  const int c = threadIdx.x % mt;
-  const int q = threadIdx.x / mt;
-  const int m = (lb - k * tiles) * mt + c;
-  const bool valid = m < d.nxh;
-  cx<T>* S = reinterpret_cast<cx<T>*>(io.spec) + (long long)k * d.plane + spec_col(d, valid ? m : 0);
-  const int rs = d.sbw;  // row stride inside a column block
-  cx<T> v[F::VMAX];
-  // FP32: unconditional loads (an invalid column reads column 0), zeroed
-  // after; FP64 keeps the guarded loads, which measure faster there
-#pragma unroll
-  for (int t = 0; t < F::BT0; ++t) {
-    const int b = q + t * NT;
-    if (F::valid_first(b)) {
-#pragma unroll
-      for (int r = 0; r < F::R0; ++r) {
-        if constexpr (sizeof(T) == 4) {
-          const cx<T> x = S[(b + r * F::NB0) * rs];
-          v[t * F::R0 + r] = valid ? x : cx<T>{0, 0};
-        } else {
-          v[t * F::R0 + r] = valid ? S[(b + r * F::NB0) * rs] : cx<T>{0, 0};
-        }
-      }
-    }
-  }
-  auto li = [mt, c](int i) { return i * mt + c; };
-  F::run(v, lds, li, q, reinterpret_cast<const cx<T>*>(d.twy));
-  if (valid) {
-#pragma unroll
-    for (int t = 0; t < F::BTL; ++t) {
-      const int b = q + t * NT;
-      if (F::valid_last(b)) {
-#pragma unroll
-        for (int r = 0; r < F::RL; ++r) S[F::out_index(q, t, r) * rs] = v[t * F::RL + r];
-      }
-    }
-  }
-}
-
-// y-direction complex FFT, persistent form (FP32, 32 elements per thread, so
-// that the 8 columns of a 2048-point tile take 512 threads and the prefetch
-// below fits the register budget of two waves per SIMD). The grid covers the
-// CUs once; workgroup w walks the launch's tiles w, w + gridDim.x, ... and
-// issues the loads of its next tile before transforming the current one, so
-// that the transform, its LDS exchanges and its stores overlap the next
-// tile's loads (a workgroup holds a CU's LDS alone, so nothing else would
-// cover them). Twiddles come from an LDS copy of the table: a global load
-// issued during the transform would wait behind the prefetched tile.
-template <bool INV, int N>
-__global__ void __launch_bounds__(512) k_ffty_pp(LaunchArgs a) {
-  using T = float;
-  constexpr int NT = ct_threads_y(N, 32);
-  constexpr int MT = pp_columns(N);  // columns per tile
-  using F = CtFft<T, N, NT, INV>;
-  extern __shared__ unsigned char smem_raw[];
-  cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
-  cx<T>* twl = lds + N * MT;
-  const int total = a.block_start[a.nmem];
-  if ((int)blockIdx.x >= total) return;
-  // every member of a launch has the same length N, hence the same table
-  {
-    const cx<T>* tw = reinterpret_cast<const cx<T>*>(a.mem[0]->twy);
-    for (int i = threadIdx.x; i < N; i += blockDim.x) twl[i] = load_tw(tw + i);
-  }
-  // Tile tb of the launch: a workgroup-uniform base (the tile's first column
-  // in its level) and this lane's 32-bit element offset from it, so that every
-  // access is a scalar base plus one vector offset. A column past nxh takes
-  // the level's last column (transformed, never stored).
-  struct Tile {
-    cx<T>* base;
-    unsigned off;
-    int rs;
-    bool valid, live;
-  };
-  auto tile = [&](int tb, int c) {
-    const int mi = find_member(a, tb);
-    const MemberDesc& d = *a.mem[mi];
-    const int lb = tb - a.block_start[mi];
-    const int tiles = (d.nxh + MT - 1) / MT;
-    const int k = lb / tiles;
-    const int m0 = (lb - k * tiles) * MT;
-    const int m = m0 + c;
-    Tile t;
-    t.valid = m < d.nxh;
-    t.live = !skipped(d);
-    t.rs = wuni(d.sbw);
-    const long long b0 = (long long)k * d.plane + spec_col(d, m0);
-    t.base = reinterpret_cast<cx<T>*>(a.io[mi].spec) + b0;
-    t.off = (unsigned)(spec_col(d, t.valid ? m : d.nxh - 1) - spec_col(d, m0));
-    return t;
-  };
-  // element i of the lane's column (global-address-space accesses through
-  // the two-float vector type)
-  typedef T pair __attribute__((ext_vector_type(2)));
-  auto ld = [](const Tile& t, int i) -> cx<T> {
-    const pair x = ((const __attribute__((address_space(1))) pair*)t.base)[t.off + (unsigned)(i * t.rs)];
-    return cx<T>{x.x, x.y};
-  };
-  auto st = [](const Tile& t, int i, cx<T> x) {
-    ((__attribute__((address_space(1))) pair*)t.base)[t.off + (unsigned)(i * t.rs)] = pair{x.x, x.y};
-  };
-  cx<T> v[F::VMAX], nx[F::VMAX];
-  // The lane's column and row index are re-read through an empty asm at every
-  // tile: the LDS and twiddle addresses derived from them are then computed
-  // where they are used instead of being hoisted out of the loop, where they
-  // would hold registers the prefetched tile needs.
-  auto lane = [](int& c, int& q) {
-    int t = threadIdx.x;
-    asm volatile("" : "+v"(t));
-    c = t % MT;
-    q = t / MT;
-  };
-  int cur = blockIdx.x, c, q;
-  lane(c, q);
-  Tile tc = tile(cur, c);
-  auto load = [&](const Tile& t, int q, cx<T>* dst) {
-#pragma unroll
-    for (int u = 0; u < F::BT0; ++u) {
-      const int b = q + u * NT;
-      if (F::valid_first(b)) {
-#pragma unroll
-        for (int r = 0; r < F::R0; ++r) dst[u * F::R0 + r] = ld(t, b + r * F::NB0);
-      }
-    }
-  };
-  if (tc.live) load(tc, q, v);
-  __syncthreads();  // the twiddle table
-  while (true) {
-    const int nxt = cur + gridDim.x;
-    Tile tn;
-    tn.live = false;
-    lane(c, q);
-    if (nxt < total) {
-      tn = tile(nxt, c);
-      if (tn.live) load(tn, q, nx);
-    }
-    if (tc.live) {  // uniform over the workgroup (one member per tile)
-      lane(c, q);
-      F::run_tw(v, lds, [c](int i) { return i * MT + c; }, q, [twl](int i) { return twl[i]; });
-      if (tc.valid) {
-#pragma unroll
-        for (int u = 0; u < F::BTL; ++u) {
-          const int b = q + u * NT;
-          if (F::valid_last(b)) {
-#pragma unroll
-            for (int r = 0; r < F::RL; ++r) st(tc, F::out_index(q, u, r), v[u * F::RL + r]);
-          }
-        }
-      }
-    }
-    if (nxt >= total) break;
-    cur = nxt;
-    tc = tn;
-#pragma unroll
-    for (int i = 0; i < F::VMAX; ++i) v[i] = nx[i];
-  }
-}
-
-template <typename T, bool INV>
-__global__ void __launch_bounds__(1024) k_ffty_gen(LaunchArgs a) {
-  extern __shared__ unsigned char smem_raw[];
-  cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
-  const int mi = find_member(a, blockIdx.x);
-  const MemberDesc& d = *a.mem[mi];
-  if (skipped(d)) return;
-  const IoPtrs io = a.io[mi];
-  const int lb = xcd_local_block(a, mi);
-  const int mt = d.ymt, ny = d.ny, nt = d.fy.nt;
-  const int tiles = (d.nxh + mt - 1) / mt;
-  const int k = lb / tiles;
-  const int m0 = (lb - k * tiles) * mt;
-  const int c = threadIdx.x % mt;
-  int q = threadIdx.x / mt;
-  if (q >= nt) q = kBig;
-  cx<T>* S = reinterpret_cast<cx<T>*>(io.spec) + (long long)k * d.plane;
-  const int tot = ny * mt;
-  for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-    const int j = idx / mt, cc = idx - j * mt, m = m0 + cc;
-    buf[idx] = (m < d.nxh) ? S[(long long)j * d.sbw + spec_col(d, m)] : cx<T>{0, 0};
-  }
-  __syncthreads();
-  fft_lds<T, INV>(buf + c, mt, d.fy, reinterpret_cast<const cx<T>*>(d.twy), q);
-  for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-    const int j = idx / mt, cc = idx - j * mt, m = m0 + cc;
-    if (m < d.nxh) S[(long long)j * d.sbw + spec_col(d, m)] = buf[idx];
-  }
-}
-
-// ---------------------------------------------------------------------------
-// x-direction inverse (complex-to-real) FFT of row pairs, written to
-// MODE 0: io.p (storage type T), the pressure;
-// MODE 1 (mixed, T = float): io.s1, the refinement's correction delta;
-// MODE 2 (mixed, T = float): io.s2, the first-pass pressure p1.
-// Z[m] = X_a[m] + i X_b[m], Z[N-m] = conj X_a[m] + i conj X_b[m]; the
-// imaginary parts of the self-conjugate bins (m = 0, m = N/2) are dropped.
-// ---------------------------------------------------------------------------
-template <typename T, class Idx>
-__device__ __forceinline__ void pack_bins(cx<T>* buf, const Idx& idx, cx<T> xa, cx<T> xb, int N, int m) {
-  const bool selfconj = (m == 0) || (2 * m == N);
-  if (selfconj) {
-    xa.y = 0;
-    xb.y = 0;
-  }
-  buf[idx(m)] = cx<T>{xa.x - xb.y, xa.y + xb.x};
-  if (!selfconj) buf[idx(N - m)] = cx<T>{xa.x + xb.y, xb.x - xa.y};
-}
-
-template <typename T, class Idx>
-__device__ __forceinline__ void pack_rows(cx<T>* buf, const Idx& idx, const cx<T>* __restrict__ S, long long o0,
-                                          long long o1, bool v0, bool v1, int N, int m, long long cm) {
-  cx<T> xa = v0 ? S[o0 + cm] : cx<T>{0, 0};
-  cx<T> xb = v1 ? S[o1 + cm] : cx<T>{0, 0};
-  const bool selfconj = (m == 0) || (2 * m == N);
-  if (selfconj) {
-    xa.y = 0;
-    xb.y = 0;
-  }
-  buf[idx(m)] = cx<T>{xa.x - xb.y, xa.y + xb.x};
-  if (!selfconj) buf[idx(N - m)] = cx<T>{xa.x + xb.y, xb.x - xa.y};
-}
-
-template <typename T, int MODE>
-__device__ __forceinline__ __attribute__((address_space(1))) T* xinv_dest(const IoPtrs& io) {
-  if constexpr (MODE == 0) return gptr(reinterpret_cast<T*>(io.p));
-  else if constexpr (MODE == 1) return gptr(reinterpret_cast<T*>(io.s1));
-  else return gptr(reinterpret_cast<T*>(io.s2));
-}
-
-template <typename T, int MODE>
-__device__ __forceinline__ void store_rows(const MemberDesc& d, const IoPtrs& io, long long r0, long long r1, bool v0,
-                                           bool v1, int i, cx<T> z) {
-  const int N = d.nx;
-  auto p = xinv_dest<T, MODE>(io);
-  if (v0) p[r0 * N + i] = z.x;
-  if (v1) p[r1 * N + i] = z.y;
-}
-
-template <typename T, int MODE, int N>
-__global__ void __launch_bounds__(512) k_xinv_ct(LaunchArgs a) {
-  constexpr int NT = ct_threads(N);
-  using F = CtFft<T, N, NT, true>;
-  extern __shared__ unsigned char smem_raw[];
-  const int mi = find_member(a, blockIdx.x);
-  const MemberDesc& d = *a.mem[mi];
-  if (skipped(d)) return;
-  const IoPtrs io = a.io[mi];
-  const int lb = blockIdx.x - a.block_start[mi];
-  const int ipw = blockDim.x / NT;
-  const int inst = threadIdx.x / NT;
-  const int q = threadIdx.x - inst * NT;
-  cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw) + inst * xlds_len(N, 2 * sizeof(T));
-  const long long pair = (long long)lb * ipw + inst;
-  const long long r0 = 2 * pair, r1 = 2 * pair + 1;
-  const bool v0 = r0 < d.nrow, v1 = r1 < d.nrow;
-  const cx<T>* S = reinterpret_cast<const cx<T>*>(io.spec);
-  auto li = [](int i) { return xpad<T, N>(i); };
-  if (sizeof(T) == 4 && d.sbw >= 2) {
-    // FP32 with column blocks at least 2 wide: bins m, m+1 (m even) of a row
-    // are adjacent and 16-byte aligned in memory, so a lane loads both with
-    // one access (half the load instructions). Pairs m = 0, 2, .. up to nx/2
-    // over NT threads; the slot after bin nx/2 (a padding slot of the row's
-    // last block: nx/2 + 1 is odd, the padded row length a multiple of 8) is
-    // read and dropped. Loads first and unconditional, as below.
-    typedef T t4 __attribute__((ext_vector_type(4)));
-    constexpr int NP = N / 4 + 1;  // pairs (m even, m <= N/2)
-    constexpr int RND2 = (NP + NT - 1) / NT;
-    const long long so0 = spec_row(d, v0 ? r0 : 0), so1 = spec_row(d, v1 ? r1 : 0);
-    t4 ya[RND2], yb[RND2];
-#pragma unroll
-    for (int t = 0; t < RND2; ++t) {
-      const int m = 2 * (q + t * NT);
-      const bool in = m <= N / 2;
-      const long long cm = spec_col(d, in ? m : 0);
-      const t4 a = *reinterpret_cast<const t4*>(S + so0 + cm), b = *reinterpret_cast<const t4*>(S + so1 + cm);
-      ya[t] = (in && v0) ? a : (t4)(T)0;
-      yb[t] = (in && v1) ? b : (t4)(T)0;
-    }
-#pragma unroll
-    for (int t = 0; t < RND2; ++t) {
-      const int m = 2 * (q + t * NT);
-      if (m <= N / 2) {
-        pack_bins<T>(lds, li, cx<T>{ya[t][0], ya[t][1]}, cx<T>{yb[t][0], yb[t][1]}, N, m);
-        if (m + 1 <= N / 2) pack_bins<T>(lds, li, cx<T>{ya[t][2], ya[t][3]}, cx<T>{yb[t][2], yb[t][3]}, N, m + 1);
-      }
-    }
-  } else {
-    // nx/2 + 1 bins over NT threads: N/(2 NT) + 1 rounds, loads issued first
-    // and unconditional (clamped bin; a missing row reads row 0), selected after
-    constexpr int RND = N / (2 * NT) + 1;
-    const long long so0 = spec_row(d, v0 ? r0 : 0), so1 = spec_row(d, v1 ? r1 : 0);
-    cx<T> xa[RND], xb[RND];
-#pragma unroll
-    for (int t = 0; t < RND; ++t) {
-      const int m = q + t * NT;
-      const bool in = m <= N / 2;
-      const long long cm = spec_col(d, in ? m : N / 2);
-      const cx<T> a = S[so0 + cm], b = S[so1 + cm];
-      xa[t] = (in && v0) ? a : cx<T>{0, 0};
-      xb[t] = (in && v1) ? b : cx<T>{0, 0};
-    }
-#pragma unroll
-    for (int t = 0; t < RND; ++t) {
-      const int m = q + t * NT;
-      if (m <= N / 2) pack_bins<T>(lds, li, xa[t], xb[t], N, m);
-    }
-  }
-  __syncthreads();
-  cx<T> v[F::VMAX];
-#pragma unroll
-  for (int t = 0; t < F::BT0; ++t) {
-    const int b = q + t * NT;
-    if (F::valid_first(b)) {
-#pragma unroll
-      for (int r = 0; r < F::R0; ++r) v[t * F::R0 + r] = lds[xpad<T, N>(b + r * F::NB0)];
-    }
-  }
-  __syncthreads();
-  F::run(v, lds, li, q, reinterpret_cast<const cx<T>*>(d.twx));
-#pragma unroll
-  for (int t = 0; t < F::BTL; ++t) {
-    const int b = q + t * NT;
-    if (F::valid_last(b)) {
-#pragma unroll
-      for (int r = 0; r < F::RL; ++r) lds[xpad<T, N>(F::out_index(q, t, r))] = v[t * F::RL + r];
-    }
-  }
-  __syncthreads();
-  // vector phase: 16-byte chunks of both rows
-  constexpr int V = Vec<T>::n;
-  using vt = typename Vec<T>::type;
-  auto p = reinterpret_cast<__attribute__((address_space(1))) vt*>(xinv_dest<T, MODE>(io));
-#pragma unroll
-  for (int t = 0; t < N / (V * NT); ++t) {
-    const int i0 = (q + t * NT) * V;
-    vt a0, a1;
-#pragma unroll
-    for (int e = 0; e < V; ++e) {
-      const cx<T> z = lds[xpad<T, N>(i0 + e)];
-      a0[e] = z.x;
-      a1[e] = z.y;
-    }
-    if (v0) p[(r0 * N + i0) / V] = a0;
-    if (v1) p[(r1 * N + i0) / V] = a1;
-  }
-}
-
-template <typename T, int MODE>
-__global__ void __launch_bounds__(1024) k_xinv_gen(LaunchArgs a) {
-  extern __shared__ unsigned char smem_raw[];
-  cx<T>* smem = reinterpret_cast<cx<T>*>(smem_raw);
-  const int mi = find_member(a, blockIdx.x);
-  const MemberDesc& d = *a.mem[mi];
-  if (skipped(d)) return;
-  const IoPtrs io = a.io[mi];
-  const int lb = blockIdx.x - a.block_start[mi];
-  const int N = d.nx, nt = d.fx.nt;
-  const int ipw = blockDim.x / nt;
-  const int inst = threadIdx.x / nt;
-  const bool active = inst < ipw;
-  const int q = active ? (int)(threadIdx.x - inst * nt) : kBig;
-  cx<T>* buf = smem + (active ? inst : 0) * N;
-  const long long pair = (long long)lb * ipw + inst;
-  const long long r0 = 2 * pair, r1 = 2 * pair + 1;
-  const bool v0 = active && r0 < d.nrow, v1 = active && r1 < d.nrow;
-  const cx<T>* S = reinterpret_cast<const cx<T>*>(io.spec);
-  auto ident = [](int i) { return i; };
-  const long long so0 = spec_row(d, v0 ? r0 : 0), so1 = spec_row(d, v1 ? r1 : 0);
-  if (active)
-    for (int m = q; m < d.nxh; m += nt) pack_rows<T>(buf, ident, S, so0, so1, v0, v1, N, m, spec_col(d, m));
-  __syncthreads();
-  fft_lds<T, true>(buf, 1, d.fx, reinterpret_cast<const cx<T>*>(d.twx), q);
-  if (active)
-    for (int i = q; i < N; i += nt) store_rows<T, MODE>(d, io, r0, r1, v0, v1, i, buf[i]);
-}
 
 // ---------------------------------------------------------------------------
 // Pressure-gradient correction u -= G p, evaluated in FP64 from an FP64
@@ -1286,14 +203,12 @@ __global__ void __launch_bounds__(256) k_grad(LaunchArgs a) {
 // ---------------------------------------------------------------------------
 // host-side launchers
 // ---------------------------------------------------------------------------
-#define MONC_CT_SIZES(X) X(16) X(32) X(64) X(96) X(128) X(192) X(256) X(384) X(512) X(768) X(1024) X(1536) X(2048) X(4096)
-// lengths with the persistent FP32 y kernel (32 elements per thread)
-#define MONC_PP_SIZES(X) X(1024) X(1536) X(2048) X(4096)
-
 bool ct_supported(int n) {
   switch (n) {
 #define MONC_CASE(N) case N:
-    MONC_CT_SIZES(MONC_CASE)
+#define MONC_GROUP_CASES(K) MONC_CT_GROUP_##K(MONC_CASE)
+    MONC_FFT_GROUPS(MONC_GROUP_CASES)
+#undef MONC_GROUP_CASES
 #undef MONC_CASE
     return true;
     default:
@@ -1301,19 +216,13 @@ bool ct_supported(int n) {
   }
 }
 
-bool pp_supported(int n) {
-  switch (n) {
-#define MONC_CASE(N) case N:
-    MONC_PP_SIZES(MONC_CASE)
-#undef MONC_CASE
-    return true;
-    default:
-      return false;
-  }
-}
+bool pp_supported(int n) { return pp_length(n); }
 
 void init_kernel_attributes() {
   init_tridiag_attributes();
+#define MONC_GROUP_INIT(K) init_fft_group_##K();
+  MONC_FFT_GROUPS(MONC_GROUP_INIT)
+#undef MONC_GROUP_INIT
   set_lds_limit(k_xfwd_gen<double, 0>);
   set_lds_limit(k_xfwd_gen<float, 0>);
   set_lds_limit(k_xfwd_gen<float, 1>);
@@ -1327,121 +236,53 @@ void init_kernel_attributes() {
   set_lds_limit(k_xinv_gen<float, 0>);
   set_lds_limit(k_xinv_gen<float, 1>);
   set_lds_limit(k_xinv_gen<float, 2>);
-#define MONC_ATTR(N)                          \
-  set_lds_limit(k_xfwd_ct<double, 0, N>);     \
-  set_lds_limit(k_xfwd_ct<float, 0, N>);      \
-  set_lds_limit(k_xfwd_ct<float, 1, N>);      \
-  set_lds_limit(k_xfwd_ct<double, 2, N>);     \
-  set_lds_limit(k_xfwd_ct<float, 2, N>);      \
-  set_lds_limit(k_ffty_ct<double, false, N, 8>); \
-  set_lds_limit(k_ffty_ct<double, true, N, 8>);  \
-  set_lds_limit(k_ffty_ct<float, false, N, 8>);  \
-  set_lds_limit(k_ffty_ct<float, true, N, 8>);   \
-  set_lds_limit(k_ffty_ct<double, false, N, 16>); \
-  set_lds_limit(k_ffty_ct<double, true, N, 16>);  \
-  set_lds_limit(k_ffty_ct<float, false, N, 16>);  \
-  set_lds_limit(k_ffty_ct<float, true, N, 16>);   \
-  set_lds_limit(k_xinv_ct<double, 0, N>);     \
-  set_lds_limit(k_xinv_ct<float, 0, N>);      \
-  set_lds_limit(k_xinv_ct<float, 1, N>);      \
-  set_lds_limit(k_xinv_ct<float, 2, N>);
-  MONC_CT_SIZES(MONC_ATTR)
-#undef MONC_ATTR
-#define MONC_PP_ATTR(N)                  \
-  set_lds_limit(k_ffty_pp<false, N>);    \
-  set_lds_limit(k_ffty_pp<true, N>);
-  MONC_PP_SIZES(MONC_PP_ATTR)
-#undef MONC_PP_ATTR
 }
 
-
 void launch_xfwd(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int mode, int ct_n, void* stream) {
-  switch (ct_n) {
-#define MONC_CASE(N)                                        \
-  case N:                                                   \
-    if (fp64 && mode == 2) MONC_GO((k_xfwd_ct<double, 2, N>)); \
-    else if (fp64) MONC_GO((k_xfwd_ct<double, 0, N>));      \
-    else if (mode == 0) MONC_GO((k_xfwd_ct<float, 0, N>));  \
-    else if (mode == 1) MONC_GO((k_xfwd_ct<float, 1, N>));  \
-    else MONC_GO((k_xfwd_ct<float, 2, N>));                 \
+  if (ct_n) {
+#define MONC_GROUP_TRY(K) \
+  if (launch_xfwd_group_##K(a, grid, block, lds, fp64, mode, ct_n, stream)) return;
+    MONC_FFT_GROUPS(MONC_GROUP_TRY)
+#undef MONC_GROUP_TRY
     return;
-    MONC_CT_SIZES(MONC_CASE)
-#undef MONC_CASE
-    default:
-      if (fp64 && mode == 2) MONC_GO((k_xfwd_gen<double, 2>));
-      else if (fp64) MONC_GO((k_xfwd_gen<double, 0>));
-      else if (mode == 0) MONC_GO((k_xfwd_gen<float, 0>));
-      else if (mode == 1) MONC_GO((k_xfwd_gen<float, 1>));
-      else MONC_GO((k_xfwd_gen<float, 2>));
   }
+  if (fp64 && mode == 2) MONC_GO((k_xfwd_gen<double, 2>));
+  else if (fp64) MONC_GO((k_xfwd_gen<double, 0>));
+  else if (mode == 0) MONC_GO((k_xfwd_gen<float, 0>));
+  else if (mode == 1) MONC_GO((k_xfwd_gen<float, 1>));
+  else MONC_GO((k_xfwd_gen<float, 2>));
 }
 
 void launch_ffty(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, bool inverse, int ct_n, int ept,
                  void* stream) {
-  if (ept == 32 && !fp64) {
-    switch (ct_n) {
-#define MONC_CASE(N)                                  \
-  case N:                                             \
-    if (inverse) MONC_GO((k_ffty_pp<true, N>));       \
-    else MONC_GO((k_ffty_pp<false, N>));              \
-    return;
-      MONC_PP_SIZES(MONC_CASE)
-#undef MONC_CASE
-      default: break;  // rejected by the plan's tile check
-    }
+  if (ct_n) {
+#define MONC_GROUP_TRY(K) \
+  if (launch_ffty_group_##K(a, grid, block, lds, fp64, inverse, ct_n, ept, stream)) return;
+    MONC_FFT_GROUPS(MONC_GROUP_TRY)
+#undef MONC_GROUP_TRY
     return;
   }
-  switch (ct_n) {
-#define MONC_CASE(N)                                                                  \
-  case N:                                                                             \
-    if (ept == 16) {                                                                  \
-      if (fp64) {                                                                     \
-        if (inverse) MONC_GO((k_ffty_ct<double, true, N, 16>));                       \
-        else MONC_GO((k_ffty_ct<double, false, N, 16>));                              \
-      } else {                                                                        \
-        if (inverse) MONC_GO((k_ffty_ct<float, true, N, 16>));                        \
-        else MONC_GO((k_ffty_ct<float, false, N, 16>));                               \
-      }                                                                               \
-    } else {                                                                          \
-      if (fp64) {                                                                     \
-        if (inverse) MONC_GO((k_ffty_ct<double, true, N, 8>));                        \
-        else MONC_GO((k_ffty_ct<double, false, N, 8>));                               \
-      } else {                                                                        \
-        if (inverse) MONC_GO((k_ffty_ct<float, true, N, 8>));                         \
-        else MONC_GO((k_ffty_ct<float, false, N, 8>));                                \
-      }                                                                               \
-    }                                                                                 \
-    return;
-    MONC_CT_SIZES(MONC_CASE)
-#undef MONC_CASE
-    default:
-      if (fp64) {
-        if (inverse) MONC_GO((k_ffty_gen<double, true>));
-        else MONC_GO((k_ffty_gen<double, false>));
-      } else {
-        if (inverse) MONC_GO((k_ffty_gen<float, true>));
-        else MONC_GO((k_ffty_gen<float, false>));
-      }
+  if (fp64) {
+    if (inverse) MONC_GO((k_ffty_gen<double, true>));
+    else MONC_GO((k_ffty_gen<double, false>));
+  } else {
+    if (inverse) MONC_GO((k_ffty_gen<float, true>));
+    else MONC_GO((k_ffty_gen<float, false>));
   }
 }
 
 void launch_xinv(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int mode, int ct_n, void* stream) {
-  switch (ct_n) {
-#define MONC_CASE(N)                                        \
-  case N:                                                   \
-    if (fp64) MONC_GO((k_xinv_ct<double, 0, N>));           \
-    else if (mode == 0) MONC_GO((k_xinv_ct<float, 0, N>));  \
-    else if (mode == 1) MONC_GO((k_xinv_ct<float, 1, N>));  \
-    else MONC_GO((k_xinv_ct<float, 2, N>));                 \
+  if (ct_n) {
+#define MONC_GROUP_TRY(K) \
+  if (launch_xinv_group_##K(a, grid, block, lds, fp64, mode, ct_n, stream)) return;
+    MONC_FFT_GROUPS(MONC_GROUP_TRY)
+#undef MONC_GROUP_TRY
     return;
-    MONC_CT_SIZES(MONC_CASE)
-#undef MONC_CASE
-    default:
-      if (fp64) MONC_GO((k_xinv_gen<double, 0>));
-      else if (mode == 0) MONC_GO((k_xinv_gen<float, 0>));
-      else if (mode == 1) MONC_GO((k_xinv_gen<float, 1>));
-      else MONC_GO((k_xinv_gen<float, 2>));
   }
+  if (fp64) MONC_GO((k_xinv_gen<double, 0>));
+  else if (mode == 0) MONC_GO((k_xinv_gen<float, 0>));
+  else if (mode == 1) MONC_GO((k_xinv_gen<float, 1>));
+  else MONC_GO((k_xinv_gen<float, 2>));
 }
 
 void launch_grad(const LaunchArgs& a, int grid, bool fp64, int vec, bool red, void* stream) {

@@ -42,8 +42,65 @@ constexpr int tricol_lds(int P) { return 11 * P * 64; }
 // launch shapes), and so the radix plan (16 elements per thread take radix-16
 // passes): along x sixteen elements each from length 512 on, eight below;
 // along y sixteen from length 2048 on, so that a 1024-thread workgroup still
-// holds several columns of the longest transforms, eight below.
-constexpr int ct_threads_x_n(int n) { return n >= 512 ? n / 16 : (n >= 8 ? n / 8 : 1); }
+// holds several columns of the longest transforms, eight below (lengths of
+// kCtPlans aside).
+// Lengths with a factor 3 that have a radix plan of their own: threads per
+// transform and the radices, along x and y alike. Radices 6, 9, 12, 16 and 18
+// leave two passes up to 324 points and three up to 3888 (an LDS round trip
+// and two barriers each), and the threads are chosen so that the passes'
+// butterflies fill them: a thread holds 6 to 18 values, 24 where the last pass
+// is a third idle. The runtime-length kernels, which hold their butterflies in
+// scratch memory and read the fields point by point, took 573 us for a whole
+// 432 x 288 x 75 FP64 projection and 473 us for a 243 x 324 x 61 mixed one
+// against 311 and 210 us.
+struct CtPlan {
+  int n, nt, np, r[4];
+};
+constexpr CtPlan kCtPlans[] = {
+    {18, 3, 2, {6, 3}},
+    {24, 2, 2, {6, 4}},
+    {27, 3, 2, {9, 3}},
+    {36, 6, 2, {6, 6}},
+    {48, 4, 2, {12, 4}},
+    {54, 6, 2, {9, 6}},
+    {72, 6, 2, {12, 6}},
+    {81, 9, 2, {9, 9}},
+    {108, 6, 2, {18, 6}},
+    {144, 12, 2, {12, 12}},
+    {162, 9, 2, {18, 9}},
+    {216, 18, 2, {18, 12}},
+    {243, 27, 3, {9, 9, 3}},
+    {288, 18, 2, {16, 18}},
+    {324, 18, 2, {18, 18}},
+    {432, 36, 3, {12, 12, 3}},
+    {486, 27, 3, {9, 9, 6}},
+    {576, 48, 3, {12, 12, 4}},
+    {648, 36, 3, {18, 6, 6}},
+    {729, 81, 3, {9, 9, 9}},
+    {864, 72, 3, {12, 12, 6}},
+    {972, 54, 3, {18, 18, 3}},
+    {1152, 72, 3, {16, 18, 4}},
+    {1296, 72, 3, {18, 18, 4}},
+    {1458, 81, 3, {18, 9, 9}},
+    {1728, 144, 3, {12, 12, 12}},
+    {1944, 108, 3, {18, 18, 6}},
+    {2187, 243, 4, {9, 9, 9, 3}},
+    {2304, 144, 3, {16, 16, 9}},
+    {2592, 216, 3, {18, 12, 12}},
+    {2916, 162, 3, {18, 18, 9}},
+    {3072, 256, 3, {16, 16, 12}},
+    {3456, 288, 3, {16, 18, 12}},
+    {3888, 216, 3, {18, 18, 12}},
+};
+constexpr int ct_plan_index(int n) {  // its place in kCtPlans, or -1
+  for (int i = 0; i < (int)(sizeof(kCtPlans) / sizeof(CtPlan)); ++i)
+    if (kCtPlans[i].n == n) return i;
+  return -1;
+}
+constexpr int ct_threads_x_n(int n) {
+  const int i = ct_plan_index(n);
+  return i >= 0 ? kCtPlans[i].nt : n >= 512 ? n / 16 : (n >= 8 ? n / 8 : 1);
+}
 // Fewest transforms of nt threads that fill whole waves (64 lanes).
 constexpr int wave_transforms(int nt) {
   int m = 1;
@@ -60,10 +117,18 @@ constexpr bool xres_wave_rows(int n) {
   return ct_threads_x_n(n) % 64 != 0 && n % 64 == 0 && wave_transforms(ct_threads_x_n(n)) * ct_threads_x_n(n) <= 512;
 }
 constexpr int xres_chunk(int n) { return n % 256 == 0 ? 4 : (n % 128 == 0 ? 2 : 1); }
+// Points a lane takes at once of a row of n points in storage type of eb
+// bytes: 16 bytes' worth where the row divides by it, else fewer.
+constexpr int x_chunk(int n, int eb) { return n % (16 / eb) == 0 ? 16 / eb : n % 2 == 0 && eb == 4 ? 2 : 1; }
 // Along y the elements per thread (8: radix-8 passes, 16: radix-16 passes)
 // are a tile parameter: default sixteen from length 2048 on, eight below.
 constexpr int ct_yept_default(int n) { return n >= 2048 ? 16 : 8; }
-constexpr int ct_threads_y_n(int n, int ept) { return n >= ept ? n / ept : 1; }
+constexpr int ct_threads_y_n(int n, int ept) {
+  const int i = ct_plan_index(n);
+  return i >= 0 ? kCtPlans[i].nt : n >= ept ? n / ept : 1;
+}
+// lengths with the persistent FP32 y kernel (32 elements per thread)
+constexpr bool pp_length(int n) { return n == 1024 || n == 1536 || n == 2048 || n == 4096; }
 // columns per tile of the persistent FP32 y kernel (32 elements per thread,
 // at most 512 threads)
 constexpr int pp_columns(int n) { return n >= 32 ? 512 / (n / 32) : 1; }

@@ -172,6 +172,28 @@ def test_fp64_ragged_and_extreme_shapes(shape):
     check_fp64(g, u, v, w)
 
 
+# every length with a radix plan of its own (2^a 3^b without the powers of two
+# and three times a power of two that the other plans cover), along x and along
+# y: even rows pair inside a level, odd ny across levels; odd and twice odd
+# lengths take the 1- and 2-point row chunks
+PLANNED = [18, 24, 27, 36, 48, 54, 72, 81, 108, 144, 162, 216, 243, 288, 324, 432, 486, 576, 648, 729, 864, 972, 1152,
+           1296, 1458, 1728, 1944, 2187, 2304, 2592, 2916, 3072, 3456, 3888]
+
+
+@pytest.mark.parametrize("n", PLANNED)
+def test_planned_lengths(n):
+    # the layers are 1 km thick and the other spacing 50 m, as in
+    # test_size_limits, so that the tolerances test the kernels and not the
+    # conditioning of a long shallow domain
+    rng = np.random.default_rng(n)
+    for shape in ((n, 3, 3), (n, 16, 2), (6, n, 3), (24, n, 2)):
+        g = synth.Grid(*shape, 50.0, 40.0, 1000.0 * rng.uniform(0.8, 1.2, shape[2]), rng.uniform(0.5, 1.5, shape[2]))
+        u, v, w = synth.random_fields(rng, g)
+        check_fp64(g, u, v, w)
+        errs, out, ref = mixed_case(g, u, v, w)
+        assert max(errs) <= TOL_MIXED, (shape, errs)
+
+
 @pytest.mark.parametrize("shape", [(8192, 2, 3), (2, 8192, 2), (6561, 3, 2), (4, 6561, 3)])
 @pytest.mark.parametrize("dtype", ["f64", "mixed"])
 def test_size_limits(shape, dtype):

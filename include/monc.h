@@ -130,11 +130,13 @@ int monc_project_noalloc(monc_plan* plan, void* u, void* v, void* w, void* p, vo
  * plan; u[i], v[i], w[i], p[i] are its arrays as in monc_project. All plans
  * must share one dtype and one device. The whole batch is validated before
  * anything is enqueued (all or nothing). The first call for a given set of
- * plans and pointers builds a schedule (grouped per-phase launches covering
- * every member, in the member order and grouping that monc_autotune chose
- * for this set of grids, else largest first in one group) and captures it in
- * a HIP graph; later calls with the same plans and pointers replay the
- * graph, others re-capture. The batch is the ensemble workload of the
+ * plans and pointers launches the phases directly (grouped per-phase launches
+ * covering every member, in the member order and grouping that monc_autotune
+ * chose for this set of grids, else largest first in one group); the second
+ * captures them in a HIP graph, members of different lengths on up to
+ * MONC_MAX_BRANCHES concurrent branches, and it and later calls with the same
+ * plans and pointers replay the graph. A call on a stream that the caller is
+ * capturing always launches directly. The batch is the ensemble workload of the
  * paper's self-tuning proposal (Sec. 5): many independent solves scheduled
  * together on one device.
  */

@@ -1255,14 +1255,12 @@ extern "C" int monc_debug_stage(monc_plan* pl, int stage, void* const* bufs, int
 struct BatchEntry {
   std::vector<unsigned long long> key;
   std::vector<unsigned long long> plan_ids;
-  MemberDesc* d_array = nullptr;
   hipGraphExec_t exec = nullptr;
   hipGraph_t graph = nullptr;
   unsigned long long last_use = 0;
   ~BatchEntry() {
     if (exec) (void)hipGraphExecDestroy(exec);
     if (graph) (void)hipGraphDestroy(graph);
-    if (d_array) (void)hipFree(d_array);
   }
 };
 
@@ -1366,8 +1364,7 @@ static std::vector<int> batch_order(monc_plan* const* plans, int count, int orde
 }
 
 static void build_groups(monc_plan* const* plans, int count, void* const* u, void* const* v, void* const* w,
-                         void* const* p, const MemberDesc* d_array, const std::vector<int>& ord,
-                         const BatchSchedule& sc, std::vector<Group>& groups) {
+                         void* const* p, const std::vector<int>& ord, const BatchSchedule& sc, std::vector<Group>& groups) {
   groups.clear();
   const size_t budget = (size_t)sc.budget_mb << 20;
   Group g;
@@ -1382,21 +1379,58 @@ static void build_groups(monc_plan* const* plans, int count, void* const* u, voi
       g.fp64 = plans[0]->dtype == MONC_FP64;
       used = 0;
     }
-    g.mem.push_back({&plans[i]->h, d_array + t, plan_io(plans[i], u[i], v[i], w[i], p[i])});
+    g.mem.push_back({&plans[i]->h, plans[i]->d_desc, plan_io(plans[i], u[i], v[i], w[i], p[i])});
     used += mb;
   }
   groups.push_back(std::move(g));
 }
 
-// Every phase over all groups (phase-major), or all phases of each group in
-// turn (group-major, the grouped schedules). With side streams (a capture in
-// progress on `stream`), group-major group g goes to branch
-// g mod (1 + side.size()): the captured graph then holds that many
-// independent chains, which the device runs concurrently, so that one
-// chain's small launches fill the tails and gaps another leaves.
-static int run_batch(const std::vector<Group>& groups, const std::vector<Phase>& seq, bool group_major,
-                     void* stream, Profiler* prof, const std::vector<hipStream_t>& side = {}) {
-  if (!group_major) return run_phases(groups, seq, stream, prof);
+// Members dealt to at most MONC_MAX_BRANCHES independent chains of about equal
+// points, members of one (nx, ny) together (they share every launch), in the
+// members' order. A phase is one launch per kernel instance, and an ensemble
+// of uneven grids has one for most of its lengths: one after the other they
+// leave a tail each, which for small members is most of their time (six
+// members between 72 x 54 x 33 and 162 x 128 x 41 in FP64: 281 -> 204 us).
+static std::vector<Group> deal_chains(const Group& g) {
+  struct Class {
+    int nx, ny;
+    double points;
+    std::vector<int> mem;
+  };
+  std::vector<Class> cls;
+  for (int i = 0; i < (int)g.mem.size(); ++i) {
+    const MemberDesc& h = *g.mem[i].h;
+    size_t c = 0;
+    while (c < cls.size() && (cls[c].nx != h.nx || cls[c].ny != h.ny)) ++c;
+    if (c == cls.size()) cls.push_back({h.nx, h.ny, 0.0, {}});
+    cls[c].mem.push_back(i);
+    cls[c].points += (double)h.nx * h.ny * h.nz;
+  }
+  std::stable_sort(cls.begin(), cls.end(), [](const Class& a, const Class& b) { return a.points > b.points; });
+  const size_t nb = std::min<size_t>(cls.size(), MONC_MAX_BRANCHES);
+  std::vector<double> load(nb, 0.0);
+  std::vector<std::vector<int>> pick(nb);
+  for (const Class& c : cls) {
+    const size_t b = std::min_element(load.begin(), load.end()) - load.begin();
+    load[b] += c.points;
+    pick[b].insert(pick[b].end(), c.mem.begin(), c.mem.end());
+  }
+  std::vector<Group> out(nb);
+  for (size_t b = 0; b < nb; ++b) {
+    std::sort(pick[b].begin(), pick[b].end());
+    out[b].fp64 = g.fp64;
+    for (int i : pick[b]) out[b].mem.push_back(g.mem[i]);
+  }
+  return out;
+}
+
+// All phases of each group in turn. With side streams (a capture in progress
+// on `stream`), group g goes to branch g mod (1 + side.size()): the captured
+// graph then holds that many independent chains, which the device runs
+// concurrently, so that one chain's small launches fill the tails and gaps
+// another leaves. Without, the groups run one after the other on `stream`.
+static int run_batch(const std::vector<Group>& groups, const std::vector<Phase>& seq, void* stream, Profiler* prof,
+                     const std::vector<hipStream_t>& side = {}) {
   const size_t nb = 1 + std::min(side.size(), groups.size() ? groups.size() - 1 : 0);
   std::vector<hipEvent_t> ev;
   auto cleanup = [&]() {
@@ -1454,6 +1488,35 @@ static int check_batch(monc_plan* const* plans, int count, const char* what) {
   return MONC_OK;
 }
 
+// The streams that batches are captured on (nothing runs on them): created
+// once per device and used under g_batch_mu.
+static hipStream_t g_capture[kMaxDevices][MONC_MAX_BRANCHES] = {};
+
+static int capture_streams(int branches, hipStream_t* first, std::vector<hipStream_t>& side) {
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return fail(MONC_EHIP, "hipGetDevice failed");
+  for (int b = 0; b < std::max(1, branches); ++b) {
+    hipStream_t& s = g_capture[dev][b];
+    if (!s && hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) {
+      s = nullptr;
+      return fail(MONC_EHIP, "batch: stream creation failed");
+    }
+    if (b == 0) *first = s;
+    else side.push_back(s);
+  }
+  return MONC_OK;
+}
+
+// After a failed capture: its streams may be left in a broken state.
+static void drop_capture_streams() {
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return;
+  for (hipStream_t& s : g_capture[dev]) {
+    if (s) (void)hipStreamDestroy(s);
+    s = nullptr;
+  }
+}
+
 extern "C" int monc_project_batched(monc_plan* const* plans, int count, void* const* u, void* const* v,
                                     void* const* w, void* const* p, void* stream) {
   if (!plans || !u || !v || !w || !p) return fail(MONC_EINVAL, "null argument array");
@@ -1491,15 +1554,15 @@ extern "C" int monc_project_batched(monc_plan* const* plans, int count, void* co
   BatchEntry* ent = nullptr;
   for (auto& e : g_batches)
     if (e->key == key) ent = e.get();
-  if (!ent) {
+  // A graph pays for its capture (0.3 to 0.8 ms for a few members) only when it
+  // is replayed, so the first call over new pointers launches its phases
+  // directly: a batch that is called once, or on fields that move, never
+  // captures. So does a call while the caller captures the stream.
+  const bool first = !ent;
+  if (first) {
     auto e = std::make_unique<BatchEntry>();
     e->key = key;
     for (int i = 0; i < count; ++i) e->plan_ids.push_back(plans[i]->id);
-    if (hipMalloc((void**)&e->d_array, sizeof(MemberDesc) * count) != hipSuccess)
-      return fail(MONC_ENOMEM, "batch descriptor allocation failed");
-    std::vector<MemberDesc> hd(count);
-    for (int t = 0; t < count; ++t) hd[t] = plans[ord[t]]->h;
-    HIP_TRY(hipMemcpy(e->d_array, hd.data(), sizeof(MemberDesc) * count, hipMemcpyHostToDevice));
     if (g_batches.size() >= kBatchCacheSize) {
       auto oldest = std::min_element(g_batches.begin(), g_batches.end(),
                                      [](const std::unique_ptr<BatchEntry>& a, const std::unique_ptr<BatchEntry>& b) {
@@ -1512,31 +1575,39 @@ extern "C" int monc_project_batched(monc_plan* const* plans, int count, void* co
   }
   ent->last_use = ++g_batch_clock;
   std::vector<Group> groups;
-  build_groups(plans, count, u, v, w, p, ent->d_array, ord, sc, groups);
-  const bool group_major = sc.budget_mb > 0;
+  build_groups(plans, count, u, v, w, p, ord, sc, groups);
   const auto& seq = full_sequence(fp64);
-  if (prof) return run_batch(groups, seq, group_major, stream, prof);  // eager launches when timing kernels
+  bool eager = prof || first;  // kernels are timed around direct launches
+  if (!eager) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    eager = hipStreamIsCapturing((hipStream_t)stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
+    if (eager) (void)hipGetLastError();
+  }
+  if (eager) {
+    if (sc.budget_mb == 0) return run_phases(groups, seq, stream, prof);
+    return run_batch(groups, seq, stream, prof);
+  }
   if (!ent->exec) {
+    int branches = sc.branches;
+    if (sc.budget_mb == 0) {  // one group: its chains
+      groups = deal_chains(groups[0]);
+      branches = (int)groups.size();
+    }
+    // side streams of the capture: forked from the first and joined back into
+    // it, so they record into the same graph
+    std::vector<hipStream_t> side;
     hipStream_t cs = nullptr;
-    HIP_TRY(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
+    rc = capture_streams(branches, &cs, side);
+    if (rc != MONC_OK) return rc;
     hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) {
-      (void)hipStreamDestroy(cs);
+      drop_capture_streams();
       return fail(MONC_EHIP, "hipStreamBeginCapture failed: %s", hipGetErrorString(e));
     }
-    // side streams of the capture: forked from cs and joined back into it,
-    // so they record into the same graph
-    std::vector<hipStream_t> side;
-    for (int b = 1; b < sc.branches && rc == MONC_OK; ++b) {
-      hipStream_t s2 = nullptr;
-      if (hipStreamCreateWithFlags(&s2, hipStreamNonBlocking) != hipSuccess) rc = fail(MONC_EHIP, "batch: stream creation failed");
-      else side.push_back(s2);
-    }
-    if (rc == MONC_OK) rc = run_batch(groups, seq, group_major, cs, nullptr, side);
+    rc = run_batch(groups, seq, cs, nullptr, side);
     hipGraph_t graph = nullptr;
     e = hipStreamEndCapture(cs, &graph);
-    (void)hipStreamDestroy(cs);
-    for (hipStream_t s2 : side) (void)hipStreamDestroy(s2);
+    if (rc != MONC_OK || e != hipSuccess) drop_capture_streams();
     if (rc != MONC_OK) {
       if (graph) (void)hipGraphDestroy(graph);
       return rc;

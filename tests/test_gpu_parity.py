@@ -486,6 +486,41 @@ def test_batched_graph_replays():
                 assert np.array_equal(x, y)
 
 
+@pytest.mark.parametrize("calls", [0, 1, 2])
+def test_batch_inside_a_caller_capture(calls):
+    # a batch captured by its caller after none, one (launched directly) or two
+    # calls (captured and replayed) over the same fields: every replay gives
+    # the direct call's bits, with eager work in between
+    mem = _ensemble(5, [(32, 32, 16), (48, 24, 12), (54, 36, 9), (64, 64, 8), (27, 18, 6)], 61)
+    plans = [monc.Plan.from_grid(g, "f64") for g, *_ in mem]
+    base = [[to_dev(a, torch.float64) for a in (u, v, w)] for _, u, v, w in mem]
+    fields = [[t.clone() for t in b] + [torch.empty_like(b[0])] for b in base]
+
+    def restore():
+        for f, b in zip(fields, base):
+            for t, a in zip(f, b):
+                t.copy_(a)
+
+    def call():
+        monc.project_batched(plans, *[[f[i] for f in fields] for i in range(4)])
+
+    refs = [run_gpu(g, u, v, w, plan=pl) for (g, u, v, w), pl in zip(mem, plans)]
+    for _ in range(calls):
+        restore()
+        call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for _ in range(3):
+        restore()
+        graph.replay()
+        torch.cuda.synchronize()
+        for f, ref in zip(fields, refs):
+            for t, r in zip(f, ref):
+                assert np.array_equal(t.cpu().numpy(), r)
+
+
 def test_batched_rejects_mixed_dtypes():
     g, u, v, w = _case((16, 16, 8), 14)
     p64 = monc.Plan.from_grid(g, "f64")

@@ -375,6 +375,9 @@ extern "C" monc_plan* monc_plan_create(int nx, int ny, int nz, double dx, double
   h.nxp = (h.nxh + kSpecBlockMax - 1) / kSpecBlockMax * kSpecBlockMax;
   h.dtype = dtype;
   h.nrow = (long long)nz * ny;
+  div_magic((unsigned)nx, h.nx_mul, h.nx_shift);
+  div_magic((unsigned)ny, h.ny_mul, h.ny_shift);
+  div_magic((unsigned)nx * (unsigned)ny, h.nh_mul, h.nh_shift);
   // spectral level stride: an odd multiple of 256 bytes, so that the
   // tridiagonal solver's walk down a column does not revisit one HBM channel
   h.plane = (long long)ny * h.nxp;
@@ -444,13 +447,14 @@ extern "C" monc_plan* monc_plan_create(int nx, int ny, int nz, double dx, double
   std::vector<double> lamy = modified_wavenumbers(ny, ny, dy);
   std::vector<double> twx = twiddles(nx), twy = twiddles(ny);
 
-  // one device blob for the tables: 7 FP64 vertical, 3 FP32 vertical,
+  // one device blob for the tables: 7 FP64 vertical, the packed metrics,
   // lamx, lamy, twiddles in the storage precision
   const size_t eb = elem_bytes(dtype);
   auto al = [](size_t x) { return (x + 255) / 256 * 256; };
   size_t off = 0;
   const size_t o_v64 = off; off += al(7 * (size_t)nz * 8);
-  const size_t o_v32 = off; off += al(3 * (size_t)nz * 4);
+  const size_t o_lev = off; off += al((size_t)kLev64 * nz * 8);
+  const size_t o_levf = off; off += al((size_t)kLev32 * nz * 4);
   const size_t o_lx = off; off += al((size_t)h.nxh * 8);
   const size_t o_ly = off; off += al((size_t)ny * 8);
   const size_t o_tx = off; off += al((size_t)nx * 2 * eb);
@@ -461,11 +465,13 @@ extern "C" monc_plan* monc_plan_create(int nx, int ny, int nz, double dx, double
   double* v64 = reinterpret_cast<double*>(blob.data() + o_v64);
   const std::vector<double>* cols[7] = {&vt.rho0, &vt.rhow, &vt.rdz, &vt.rdzc, &vt.dz, &vt.ta, &vt.tc};
   for (int t = 0; t < 7; ++t) std::memcpy(v64 + (size_t)t * nz, cols[t]->data(), (size_t)nz * 8);
-  float* v32 = reinterpret_cast<float*>(blob.data() + o_v32);
+  double* lev = reinterpret_cast<double*>(blob.data() + o_lev);
+  float* levf = reinterpret_cast<float*>(blob.data() + o_levf);
   for (int k = 0; k < nz; ++k) {
-    v32[k] = (float)vt.rho0[k];
-    v32[nz + k] = (float)vt.rhow[k];
-    v32[2 * nz + k] = (float)vt.rdz[k];
+    const double l[kLev64] = {vt.rho0[k], vt.rdz[k], vt.rhow[k], k ? vt.rhow[k - 1] : 0.0,
+                              vt.rdzc[k], k ? vt.rdzc[k - 1] : 0.0};
+    for (int i = 0; i < kLev64; ++i) lev[kLev64 * k + i] = l[i];
+    for (int i = 0; i < kLev32; ++i) levf[kLev32 * k + i] = (float)l[i];
   }
   std::memcpy(blob.data() + o_lx, lamx.data(), lamx.size() * 8);
   std::memcpy(blob.data() + o_ly, lamy.data(), lamy.size() * 8);
@@ -538,10 +544,8 @@ extern "C" monc_plan* monc_plan_create(int nx, int ny, int nz, double dx, double
   h.tra = reinterpret_cast<const double*>(base + o_tr);
   h.trc = h.tra + nz + kTriPmax;
   h.trr = h.trc + nz + kTriPmax;
-  const float* d32 = reinterpret_cast<const float*>(base + o_v32);
-  h.rho0f = d32;
-  h.rhowf = d32 + nz;
-  h.rdzf = d32 + 2 * (size_t)nz;
+  h.lev = reinterpret_cast<const double*>(base + o_lev);
+  h.levf = reinterpret_cast<const float*>(base + o_levf);
   h.lamx = reinterpret_cast<const double*>(base + o_lx);
   h.lamy = reinterpret_cast<const double*>(base + o_ly);
   h.twx = base + o_tx;

@@ -43,12 +43,14 @@ struct RowCtx {
   float rho0f, rhowf, rhowmf, rdzf;
 };
 
+// (rows, ny nz of them, and their level and row index fit 31 bits)
+__device__ __forceinline__ int row_level(const MemberDesc& d, int r) { return (int)fast_div(r, d.ny_mul, d.ny_shift); }
+
 __device__ __forceinline__ RowCtx make_row(const MemberDesc& d, long long row, bool valid) {
   RowCtx c;
   const int ny = d.ny, nz = d.nz;
   const long long r = valid ? row : 0;
-  // rows (ny nz of them) and their level and row index fit 32 bits
-  const int k = (int)r / ny;
+  const int k = row_level(d, (int)r);
   const int j = (int)r - k * ny;
   c.k = k;
   c.off = r * d.nx;
@@ -57,17 +59,23 @@ __device__ __forceinline__ RowCtx make_row(const MemberDesc& d, long long row, b
   c.plane = (long long)ny * d.nx;
   c.top = k < nz - 1;
   c.bot = k > 0;
-  const int km = c.bot ? k - 1 : k;
-  c.rho0 = ldg(d.rho0 + k);
-  c.rdz = ldg(d.rdz + k);
-  c.rhow = ldg(d.rhow + k);    // 0 on the lid row
-  c.rdzc = ldg(d.rdzc + k);    // 0 on the lid row
-  c.rhowm = c.bot ? ldg(d.rhow + km) : 0.0;
-  c.rdzcm = c.bot ? ldg(d.rdzc + km) : 0.0;
-  c.rho0f = ldg(d.rho0f + k);
-  c.rdzf = ldg(d.rdzf + k);
-  c.rhowf = ldg(d.rhowf + k);
-  c.rhowmf = c.bot ? ldg(d.rhowf + km) : 0.0f;
+  // the level's metrics sit together (kLev64, kLev32 values a level): rhow and
+  // 1/dzc are 0 on the lid row, those of the level below 0 on the bottom row
+  typedef double d2 __attribute__((ext_vector_type(2)));
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  const d2* l64 = reinterpret_cast<const d2*>(d.lev + (long long)k * kLev64);
+  const d2 a = ldg(l64), b = ldg(l64 + 1), e = ldg(l64 + 2);
+  c.rho0 = a.x;
+  c.rdz = a.y;
+  c.rhow = b.x;
+  c.rhowm = b.y;
+  c.rdzc = e.x;
+  c.rdzcm = e.y;
+  const f4 l32 = ldg(reinterpret_cast<const f4*>(d.levf + (long long)k * kLev32));
+  c.rho0f = l32.x;
+  c.rdzf = l32.y;
+  c.rhowf = l32.z;
+  c.rhowmf = l32.w;
   return c;
 }
 
@@ -413,7 +421,7 @@ __device__ __forceinline__ cx<T> split_bin(cx<T> z, cx<T> zr, int row) {
 // bytes); inside a block the rows are sbw apart, so a y-FFT tile of sbw
 // columns is one contiguous run and a row pair writes 2 sbw adjacent values.
 __device__ __forceinline__ long long spec_row(const MemberDesc& d, long long r) {
-  const int k = (int)r / d.ny;
+  const int k = row_level(d, (int)r);
   return (long long)k * d.plane + (long long)((int)r - k * d.ny) * d.sbw;
 }
 __device__ __forceinline__ long long spec_col(const MemberDesc& d, int m) {
@@ -484,16 +492,17 @@ __global__ void __launch_bounds__(512)
   constexpr int NT = ct_threads(N);
   using F = CtFft<T, N, NT, false>;
   extern __shared__ unsigned char smem_raw[];
-  const int mi = find_member(a, blockIdx.x);
-  const MemberDesc& d = *a.mem[mi];
+  const Member mb = launch_member(a, blockIdx.x);
+  const MemberDesc d = load_desc(mb.desc);
+  keep_x(d);
   if (skipped(d)) return;
-  const IoPtrs io = a.io[mi];
+  const IoPtrs& io = mb.io;
   // workgroups in launch order for the residual (1-7 % faster than grouped
   // by XCD: 2048^2 x 160, 1024^2 x 256, 4096^2 x 64 and the ensemble), by XCD
   // for the divergence (FP32 2 % faster that way at 2048^2 x 160; FP64 4 %
   // slower there but 7 % faster at 4096^2 x 64) and the given-field mode
   constexpr bool PLAIN = MODE == 1;
-  const int lb = PLAIN ? (int)blockIdx.x - a.block_start[mi] : xcd_local_block(a, mi);
+  const int lb = PLAIN ? (int)blockIdx.x - mb.start : xcd_local_block(mb);
   const int ipw = blockDim.x / NT;
   // scalar row contexts for the residual only, and only where a transform
   // spans whole waves (NT a multiple of 64: then no wave holds lanes of two
@@ -655,11 +664,12 @@ template <typename T, int MODE>
 __global__ void __launch_bounds__(1024) k_xfwd_gen(LaunchArgs a) {
   extern __shared__ unsigned char smem_raw[];
   cx<T>* smem = reinterpret_cast<cx<T>*>(smem_raw);
-  const int mi = find_member(a, blockIdx.x);
-  const MemberDesc& d = *a.mem[mi];
+  const Member mb = launch_member(a, blockIdx.x);
+  const MemberDesc d = load_desc(mb.desc);
+  keep_x(d);
   if (skipped(d)) return;
-  const IoPtrs io = a.io[mi];
-  const int lb = xcd_local_block(a, mi);
+  const IoPtrs& io = mb.io;
+  const int lb = xcd_local_block(mb);
   const int N = d.nx, nt = d.fx.nt;
   const int ipw = blockDim.x / nt;
   const int inst = threadIdx.x / nt;
@@ -702,11 +712,12 @@ __global__ void __launch_bounds__(1024) k_ffty_ct(LaunchArgs a) {
   using F = CtFft<T, N, NT, INV>;
   extern __shared__ unsigned char smem_raw[];
   cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
-  const int mi = find_member(a, blockIdx.x);
-  const MemberDesc& d = *a.mem[mi];
+  const Member mb = launch_member(a, blockIdx.x);
+  const MemberDesc d = load_desc(mb.desc);
+  keep_y(d);
   if (skipped(d)) return;
-  const IoPtrs io = a.io[mi];
-  const int lb = xcd_local_block(a, mi);
+  const IoPtrs& io = mb.io;
+  const int lb = xcd_local_block(mb);
   const int mt = blockDim.x / NT;
   const int tiles = (d.nxh + mt - 1) / mt;
   const int k = lb / tiles;
@@ -871,11 +882,12 @@ template <typename T, bool INV>
 __global__ void __launch_bounds__(1024) k_ffty_gen(LaunchArgs a) {
   extern __shared__ unsigned char smem_raw[];
   cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
-  const int mi = find_member(a, blockIdx.x);
-  const MemberDesc& d = *a.mem[mi];
+  const Member mb = launch_member(a, blockIdx.x);
+  const MemberDesc d = load_desc(mb.desc);
+  keep_y(d);
   if (skipped(d)) return;
-  const IoPtrs io = a.io[mi];
-  const int lb = xcd_local_block(a, mi);
+  const IoPtrs& io = mb.io;
+  const int lb = xcd_local_block(mb);
   const int mt = d.ymt, ny = d.ny, nt = d.fy.nt;
   const int tiles = (d.nxh + mt - 1) / mt;
   const int k = lb / tiles;
@@ -951,11 +963,12 @@ __global__ void __launch_bounds__(512) k_xinv_ct(LaunchArgs a) {
   constexpr int NT = ct_threads(N);
   using F = CtFft<T, N, NT, true>;
   extern __shared__ unsigned char smem_raw[];
-  const int mi = find_member(a, blockIdx.x);
-  const MemberDesc& d = *a.mem[mi];
+  const Member mb = launch_member(a, blockIdx.x);
+  const MemberDesc d = load_desc(mb.desc);
+  keep_x(d);
   if (skipped(d)) return;
-  const IoPtrs io = a.io[mi];
-  const int lb = blockIdx.x - a.block_start[mi];
+  const IoPtrs& io = mb.io;
+  const int lb = blockIdx.x - mb.start;
   const int ipw = blockDim.x / NT;
   const int inst = threadIdx.x / NT;
   const int q = threadIdx.x - inst * NT;
@@ -1061,11 +1074,12 @@ template <typename T, int MODE>
 __global__ void __launch_bounds__(1024) k_xinv_gen(LaunchArgs a) {
   extern __shared__ unsigned char smem_raw[];
   cx<T>* smem = reinterpret_cast<cx<T>*>(smem_raw);
-  const int mi = find_member(a, blockIdx.x);
-  const MemberDesc& d = *a.mem[mi];
+  const Member mb = launch_member(a, blockIdx.x);
+  const MemberDesc d = load_desc(mb.desc);
+  keep_x(d);
   if (skipped(d)) return;
-  const IoPtrs io = a.io[mi];
-  const int lb = blockIdx.x - a.block_start[mi];
+  const IoPtrs& io = mb.io;
+  const int lb = blockIdx.x - mb.start;
   const int N = d.nx, nt = d.fx.nt;
   const int ipw = blockDim.x / nt;
   const int inst = threadIdx.x / nt;

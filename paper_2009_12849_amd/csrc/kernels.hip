@@ -77,10 +77,11 @@ template <typename T, int VEC, bool RED>
 __global__ void __launch_bounds__(256) k_grad(LaunchArgs a) {
   typedef T tv __attribute__((ext_vector_type(VEC)));
   typedef double dv __attribute__((ext_vector_type(VEC)));
-  const int mi = find_member(a, blockIdx.x);
-  const MemberDesc& d = *a.mem[mi];
-  const IoPtrs io = a.io[mi];
-  const int lb = xcd_local_block(a, mi);
+  const Member mb = launch_member(a, blockIdx.x);
+  const MemberDesc d = load_desc(mb.desc);
+  keep_grad(d);
+  const IoPtrs& io = mb.io;
+  const int lb = xcd_local_block(mb);
   const int nx = d.nx, ny = d.ny, nz = d.nz;
   const long long nh = (long long)nx * ny;
   // blocks walk (level, row) tiles like the stencil kernels when a row is a
@@ -106,13 +107,14 @@ __global__ void __launch_bounds__(256) k_grad(LaunchArgs a) {
   int k, j, i;
   if (rowblk) {
     const int rw = live ? row : 0;
-    k = rw / ny;
+    k = row_level(d, rw);
     j = rw - k * ny;
     i = live ? (int)(blk - (long long)row * bpr) * (int)blockDim.x * VEC + (int)threadIdx.x * VEC : 0;
   } else {
-    k = (int)(g / nh);
-    const int h = (int)(g - (long long)k * nh);  // nx ny fits 32 bits
-    j = h / nx;
+    // (a grid of 2^31 points or more: 64-bit division)
+    k = nh * nz < (1LL << 31) ? (int)fast_div((int)g, d.nh_mul, d.nh_shift) : (int)(g / nh);
+    const int h = (int)(g - (long long)k * nh);  // nx ny fits 31 bits
+    j = (int)fast_div(h, d.nx_mul, d.nx_shift);
     i = h - j * nx;
   }
   const long long base = (long long)k * nh;

@@ -156,6 +156,12 @@ constexpr int xlds_index(int i, int n, int cb) {
                        : i + (i >> (cb == 16 ? kXpadShift64 : kXpadShift32));
 }
 
+// values per level of the stencils' packed metrics: FP64 rho0, 1/dz, rhow of
+// the top face (0 at the lid), rhow of the bottom face (0 at the bottom), 1/dzc
+// above (0 at the lid) and below (0 at the bottom); FP32 the first four
+constexpr int kLev64 = 6;
+constexpr int kLev32 = 4;
+
 struct FftPlan {
   int n;                  // transform length (2^a 3^b)
   int npass;              // number of Stockham passes
@@ -176,6 +182,8 @@ struct MemberDesc {
   double rSr;             // 1 / sum(dz rho0), the near-null deflation of the column solves
   double lamdef;          // columns with a smaller horizontal eigenvalue are deflated
   float rdxf, rdyf;       // FP32 copies for the FP32 stencil
+  const double* lev;      // packed metrics (kLev64 doubles a level, 16-byte aligned)
+  const float* levf;      // their FP32 copies (kLev32 floats a level)
   // FP64 vertical tables, all of length nz
   const double* rho0;     // reference density at centres
   const double* rhow;     // density on the top face of cell k (0 at k = nz-1)
@@ -192,10 +200,6 @@ struct MemberDesc {
   const double* tra;
   const double* trc;
   const double* trr;
-  // FP32 copies for the FP32 stencil
-  const float* rho0f;
-  const float* rhowf;
-  const float* rdzf;
   // horizontal eigenvalues
   const double* lamx;     // [nxh]
   const double* lamy;     // [ny]
@@ -221,6 +225,8 @@ struct MemberDesc {
   int bst;                // elements per block of a level: ny * sbw
   unsigned bst_mul;       // x / bst = (umulhi(x, bst_mul) + x) >> bst_shift for 31-bit x
   int bst_shift;
+  unsigned nx_mul, ny_mul, nh_mul;    // the same for nx, ny and nx ny
+  int nx_shift, ny_shift, nh_shift;
   void* spec;             // spectral workspace, nz levels of `plane` complex values
   // null, or (the preconditioner's copy of the descriptor) the Krylov
   // solver's converged flag: while *skip != 0 the FFT and tridiagonal

@@ -486,10 +486,11 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(S <= 
 k_tridiag(LaunchArgs a) {
   extern __shared__ unsigned char smem_raw[];
   double2* stage = reinterpret_cast<double2*>(smem_raw);
-  const int mi = find_member(a, blockIdx.x);
-  const MemberDesc& d = *a.mem[mi];
+  const Member mb = launch_member(a, blockIdx.x);
+  const MemberDesc d = load_desc(mb.desc);
+  keep_tri(d);
   if (skipped(d)) return;
-  const IoPtrs io = a.io[mi];
+  const IoPtrs& io = mb.io;
   // a spectrum larger than the 256 MB Infinity Cache: tiles in launch order,
   // not grouped by XCD. A column is read once, so there is no L2 reuse to
   // group for, and the workgroups in flight then cover one contiguous run of
@@ -497,7 +498,7 @@ k_tridiag(LaunchArgs a) {
   // (2048^2 x 160, 1024^2 x 256, 4096^2 x 64: 2-7 % faster). Smaller members
   // keep the XCD grouping, which measured 3 % faster on an ensemble of them.
   const bool big = (double)d.plane * d.nz * sizeof(cx<TS>) > 256.0 * (1 << 20);
-  const int lb = big ? (int)blockIdx.x - a.block_start[mi] : xcd_local_block(a, mi);
+  const int lb = big ? (int)blockIdx.x - mb.start : xcd_local_block(mb);
   if (lb == 0)
     tri_tile<TS, S, true, PAIRS>(d, io, lb, stage);
   else
@@ -527,11 +528,6 @@ k_tridiag(LaunchArgs a) {
 // at 2048^2 x 160), and loading the next tile during the solve (a persistent
 // workgroup) gained 1 % there and lost up to 25 % at 384 x 256 x 96.
 // ---------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ T ldc(const T* p) {  // wave-uniform, read-only: a scalar load
-  return *(const __attribute__((address_space(4))) T*)p;
-}
-
 // sum over the waves of a workgroup of each lane's value (red: one row of 64
 // per wave); every thread must call it
 __device__ __forceinline__ double2 wave_rows_sum(double2 v, double2* red, int P) {
@@ -695,19 +691,6 @@ __device__ __forceinline__ void tri_interface_back(const double* Ib, double* Fb,
   }
 }
 
-// The descriptor is read through the constant address space, so that the
-// loads (and the addresses made from them) are scalar.
-typedef const __attribute__((address_space(4))) MemberDesc CDesc;
-
-// (n, m) of the level's entry x, as spec_nm
-__device__ __forceinline__ int column_n(CDesc& d, int x) {
-  return (x - (int)fast_div(x, d.bst_mul, d.bst_shift) * d.bst) >> d.lbw;
-}
-__device__ __forceinline__ int column_m(CDesc& d, int x) {
-  const int b = (int)fast_div(x, d.bst_mul, d.bst_shift);
-  return (b << d.lbw) | ((x - b * d.bst) & (d.sbw - 1));
-}
-
 template <typename TS, int S>
 __global__ void __launch_bounds__(1024) k_tricol(LaunchArgs a) {
   extern __shared__ double smem[];
@@ -716,15 +699,16 @@ __global__ void __launch_bounds__(1024) k_tricol(LaunchArgs a) {
   typedef TS cv __attribute__((ext_vector_type(2)));
   const int P = blockDim.x >> 6;                 // waves = row chunks
   const int q = wuni((int)(threadIdx.x >> 6)), c = threadIdx.x & 63;
-  const int mi = find_member(a, blockIdx.x);
-  CDesc& d = *(CDesc*)a.mem[mi];
-  if (d.skip && *d.skip != 0.0) return;
+  const Member mb = launch_member(a, blockIdx.x);
+  const MemberDesc d = load_desc(mb.desc);
+  keep_tri(d);
+  if (skipped(d)) return;
   // tiles in launch order or by XCD, as in k_tridiag
   const bool big = (double)d.plane * d.nz * sizeof(CS) > 256.0 * (1 << 20);
-  const int lb = wuni(big ? (int)blockIdx.x - a.block_start[mi] : xcd_local_block(a, mi));
+  const int lb = wuni(big ? (int)blockIdx.x - mb.start : xcd_local_block(mb));
   const int nz = d.nz, ncolp = d.ny * d.nxp;
   const long long plane = d.plane;
-  CS* const S0 = reinterpret_cast<CS*>(a.io[mi].spec) + (long long)lb * 64;  // the tile in level 0
+  CS* const S0 = reinterpret_cast<CS*>(mb.io.spec) + (long long)lb * 64;  // the tile in level 0
   const int col = lb * 64 + c;
   const int x = min(col, ncolp - 1), blk = (int)fast_div(x, d.bst_mul, d.bst_shift), rem = x - blk * d.bst;
   const int n = rem >> d.lbw, m = (blk << d.lbw) | (rem & (d.sbw - 1));  // as spec_nm

@@ -607,17 +607,18 @@ struct Group {
 };
 
 enum Phase {
-  PH_XFWD, PH_XPRE, PH_RESID, PH_YFWD, PH_TRI, PH_YINV, PH_XINV, PH_XINV_P1, PH_XINV_CORR, PH_GRAD, PH_GRAD_MIXED
+  PH_XFWD, PH_XPRE, PH_XPRE_UPDATE, PH_RESID, PH_YFWD, PH_TRI, PH_YINV, PH_XINV, PH_XINV_P1, PH_XINV_CORR,
+  PH_XINV_DOTS, PH_GRAD, PH_GRAD_MIXED
 };
 
 static int phase_kernel_id(Phase ph) {
   switch (ph) {
-    case PH_XFWD: case PH_XPRE: return MONC_K_DIV_FFTX;
+    case PH_XFWD: case PH_XPRE: case PH_XPRE_UPDATE: return MONC_K_DIV_FFTX;
     case PH_RESID: return MONC_K_RESID_FFTX;
     case PH_YFWD: return MONC_K_FFTY_FWD;
     case PH_TRI: return MONC_K_TRIDIAG;
     case PH_YINV: return MONC_K_FFTY_INV;
-    case PH_XINV: case PH_XINV_P1: case PH_XINV_CORR: return MONC_K_IFFTX;
+    case PH_XINV: case PH_XINV_P1: case PH_XINV_CORR: case PH_XINV_DOTS: return MONC_K_IFFTX;
     case PH_GRAD: return MONC_K_GRAD;
     case PH_GRAD_MIXED: return MONC_K_GRAD_FINAL;
   }
@@ -625,7 +626,8 @@ static int phase_kernel_id(Phase ph) {
 }
 
 static bool is_xphase(Phase ph) {
-  return ph == PH_XFWD || ph == PH_XPRE || ph == PH_RESID || ph == PH_XINV || ph == PH_XINV_P1 || ph == PH_XINV_CORR;
+  return ph == PH_XFWD || ph == PH_XPRE || ph == PH_XPRE_UPDATE || ph == PH_RESID || ph == PH_XINV ||
+         ph == PH_XINV_P1 || ph == PH_XINV_CORR || ph == PH_XINV_DOTS;
 }
 static bool is_yphase(Phase ph) { return ph == PH_YFWD || ph == PH_YINV; }
 
@@ -768,6 +770,7 @@ static int launch_one(const Group& g, const std::vector<int>& idx, Phase ph, con
   switch (ph) {
     case PH_XFWD: launch_xfwd(a, grid, block, lds, g.fp64, 0, v, stream); break;
     case PH_XPRE: launch_xfwd(a, grid, block, lds, g.fp64, 2, v, stream); break;
+    case PH_XPRE_UPDATE: launch_xfwd(a, grid, block, lds, g.fp64, 3, v, stream); break;
     case PH_RESID: launch_xfwd(a, grid, block, lds, false, 1, v, stream); break;
     case PH_YFWD: launch_ffty(a, grid, block, lds, g.fp64, false, v, g.mem[idx[0]].h->yept, stream); break;
     case PH_YINV: launch_ffty(a, grid, block, lds, g.fp64, true, v, g.mem[idx[0]].h->yept, stream); break;
@@ -776,6 +779,7 @@ static int launch_one(const Group& g, const std::vector<int>& idx, Phase ph, con
       else launch_tridiag(a, grid, block, lds, g.fp64, v, sh.sub != 0, stream); break;
     case PH_XINV: launch_xinv(a, grid, block, lds, g.fp64, 0, v, stream); break;
     case PH_XINV_P1: launch_xinv(a, grid, block, lds, false, 2, v, stream); break;
+    case PH_XINV_DOTS: launch_xinv(a, grid, block, lds, g.fp64, 3, v, stream); break;
     case PH_XINV_CORR: launch_xinv(a, grid, block, lds, false, 1, v, stream); break;
     case PH_GRAD:
     case PH_GRAD_MIXED: {
@@ -986,7 +990,10 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 static int var_workspace(monc_plan* pl, VarWs* ws) {
   const size_t n = (size_t)pl->nx * pl->ny * pl->nz;
-  const size_t nparts = (size_t)var_point_parts(pl->nx, pl->ny, pl->nz);  // the larger count
+  // partial sums: of the stencil kernels, the pointwise ones, and the x kernels
+  // (at most one workgroup per row pair, whatever the tile parameters)
+  const size_t nparts = (size_t)std::max({var_stencil_parts(pl->nx, pl->ny, pl->nz), var_point_parts(pl->nx, pl->ny, pl->nz),
+                                          (pl->h.nrow + 1) / 2});
   constexpr int kParts = 10;
   const size_t sizes[kParts] = {n * 8, n * 8, n * 8, n * elem_bytes(pl->dtype), nparts * 8, nparts * 8,
                                 (size_t)(kVarMaxIt + 2) * kVarSlots * 8, (size_t)pl->nz * 8, (size_t)pl->nz * 8,
@@ -1088,46 +1095,62 @@ extern "C" int monc_project_var(monc_plan* pl, const double* rho, double* u, dou
   // preconditioner z = M^-1 r: the plan's spectral solve with r as its
   // source, through a copy of the plan's descriptor that carries the
   // solver's done flag (queued iterations past convergence then cost only
-  // their launches)
+  // their launches). Its first kernel also takes the residual's step and sums
+  // <r, r>, its last one the inner products of z.
   pl->h_pre = pl->h;
   pl->h_pre.skip = ws.scal + kVarDone;
   if (hipMemcpyAsync(ws.desc, &pl->h_pre, sizeof(MemberDesc), hipMemcpyHostToDevice, (hipStream_t)stream) !=
       hipSuccess)
     return fail(MONC_EHIP, "monc_project_var: descriptor upload failed");
-  Group pre;
-  pre.fp64 = z64;
-  IoPtrs pio;
+  std::vector<Group> pre(1);
+  pre[0].fp64 = z64;
+  pre[0].mem.push_back({&pl->h_pre, ws.desc, IoPtrs()});
+  IoPtrs& pio = pre[0].mem[0].io;
   pio.u = ws.r;
   pio.p = ws.z;
   pio.spec = pl->d_spec;
-  pre.mem.push_back({&pl->h_pre, ws.desc, pio});
-  static const std::vector<Phase> pre_seq = {PH_XPRE, PH_YFWD, PH_TRI, PH_YINV, PH_XINV};
-  const std::vector<Group> pre_groups{pre};
-  // z_it = M^-1 r_it, <r_it, z_it>, <z_it, q_{it-1}>, then d_it
-  auto direction = [&](int i) {
-    int e = run_phases(pre_groups, pre_seq, stream, prof);
+  const long long np_up = member_shape(pl->h, PH_XPRE_UPDATE, z64).blocks;  // partials of the x kernels
+  const long long np_dot = member_shape(pl->h, PH_XINV_DOTS, z64).blocks;
+  const double tol2 = tol * tol;
+  static const std::vector<Phase> source_seq = {PH_XPRE}, update_seq = {PH_XPRE_UPDATE},
+                                  solve_seq = {PH_YFWD, PH_TRI, PH_YINV}, dots_seq = {PH_XINV_DOTS};
+  // r_it = r_{it-1} - alpha q and its norm (sets the done flag), on the way
+  // into the preconditioner's first transform; r_0 as it is
+  auto residual = [&](int i) {
+    if (i == 0) return run_phases(pre, source_seq, stream, prof);
+    pio.v = ws.q;
+    pio.w = ws.scal + var_slot(i - 1, kVarRZ);
+    pio.stats = ws.part0;
+    const int e = run_phases(pre, update_seq, stream, prof);
     if (e != MONC_OK) return e;
-    launch_var_dots(g, ws.scal, ws.r, ws.z, z64, ws.q, ws.part0, ws.part1, stream);
-    if ((e = var_launched("the inner products")) != MONC_OK) return e;
+    launch_var_finish_rr(ws.part0, np_up, ws.scal, i, tol2, stream);
+    return var_launched("the residual norm");
+  };
+  // the rest of z_it = M^-1 r_it, with <r_it, z_it> and <z_it, q_{it-1}>, then
+  // p_it and d_it
+  auto direction = [&](int i) {
+    int e = run_phases(pre, solve_seq, stream, prof);
+    if (e != MONC_OK) return e;
     // <z, q> only for the flexible update (FP32 preconditioner)
-    launch_var_finish(ws.part0, (i > 0 && !z64) ? ws.part1 : nullptr, np_pt, ws.scal, var_slot(i, kVarRZ),
-                      var_slot(i, kVarZQ), true, stream);
+    const bool flex = i > 0 && !z64;
+    pio.v = flex ? ws.q : nullptr;
+    pio.w = ws.part1;
+    pio.stats = ws.part0;
+    if ((e = run_phases(pre, dots_seq, stream, prof)) != MONC_OK) return e;
+    launch_var_finish(ws.part0, flex ? ws.part1 : nullptr, np_dot, ws.scal, var_slot(i, kVarRZ), var_slot(i, kVarZQ),
+                      true, stream);
     if ((e = var_launched("the partial-sum reduction")) != MONC_OK) return e;
-    launch_var_dir(g, ws.scal, i, ws.z, z64, ws.d, stream);
+    launch_var_dir(g, ws.scal, i, ws.z, z64, ws.d, p, stream);
     return var_launched("the direction update");
   };
-  // q = L d_it, alpha, p_{it+1}, r_{it+1} and its norm (sets the done flag)
-  const double tol2 = tol * tol;
+  // q = L d_it and <d_it, q>, then r_{it+1}
   auto step = [&](int i) {
     launch_var_apply(g, ws.scal, ws.d, ws.q, ws.part0, stream);
     int e = var_launched("the operator");
     if (e != MONC_OK) return e;
     launch_var_finish(ws.part0, nullptr, np_st, ws.scal, var_slot(i, kVarDQ), 0, true, stream);
     if ((e = var_launched("the partial-sum reduction")) != MONC_OK) return e;
-    launch_var_update(g, ws.scal, i, p, ws.r, ws.d, ws.q, ws.part0, stream);
-    if ((e = var_launched("the solution update")) != MONC_OK) return e;
-    launch_var_finish_rr(ws.part0, np_pt, ws.scal, i + 1, tol2, stream);
-    return var_launched("the residual norm");
+    return residual(i + 1);
   };
 
   launch_var_zero(ws.scal, (maxit + 2) * kVarSlots, stream);
@@ -1137,11 +1160,11 @@ extern "C" int monc_project_var(monc_plan* pl, const double* rho, double* u, dou
   // the done flag when the input is already divergence-free (or tol >= 1) and
   // flags a non-finite input, so the host needs no read before the first
   // batch; a done flag makes the queued work of that batch return at once
-  launch_var_finish_rr(ws.part0, np_st, ws.scal, 0, tol * tol, stream);
+  launch_var_finish_rr(ws.part0, np_st, ws.scal, 0, tol2, stream);
   if ((rc = var_launched("the partial-sum reduction")) != MONC_OK) return rc;
   int it = 0;
   double rel = 0.0;
-  if ((rc = direction(0)) != MONC_OK) return rc;
+  if ((rc = residual(0)) != MONC_OK || (rc = direction(0)) != MONC_OK) return rc;
   // Iterations are queued in batches and the status read once per batch;
   // the next batch's length is the iteration count that the convergence rate
   // seen so far predicts (at least 1, at most 32).
@@ -1167,13 +1190,13 @@ extern "C" int monc_project_var(monc_plan* pl, const double* rho, double* u, dou
     batch = krylov_batch(rel, rel_prev, nb, tol, 32);
     rel_prev = rel;
   }
-  // the gauge in FP64: subtract the dz-weighted mean of p (the constants are
+  // the last step of p, then the gauge in FP64: subtract the dz-weighted mean of p (the constants are
   // the operator's null space, so the residual does not change; an FP32
   // preconditioner's rounding would otherwise leave a small mean in p)
   if (it > 0) {
     double wsum = 0.0;
     for (int k = 0; k < pl->nz; ++k) wsum += pl->dz[k];
-    launch_var_wsum(g, p, ws.part0, stream);
+    launch_var_wsum(g, ws.scal, it, ws.d, p, ws.part0, stream);
     if ((rc = var_launched("the gauge sum")) != MONC_OK) return rc;
     launch_var_finish(ws.part0, nullptr, np_pt, ws.scal, kVarGauge, 0, false, stream);
     if ((rc = var_launched("the partial-sum reduction")) != MONC_OK) return rc;

@@ -19,6 +19,8 @@ static void init_length() {
   set_lds_limit(k_xfwd_ct<float, 1, N>);
   set_lds_limit(k_xfwd_ct<double, 2, N>);
   set_lds_limit(k_xfwd_ct<float, 2, N>);
+  set_lds_limit(k_xfwd_ct<double, 3, N>);
+  set_lds_limit(k_xfwd_ct<float, 3, N>);
   set_lds_limit(k_ffty_ct<double, false, N, 8>);
   set_lds_limit(k_ffty_ct<double, true, N, 8>);
   set_lds_limit(k_ffty_ct<float, false, N, 8>);
@@ -37,6 +39,8 @@ static void init_length() {
   set_lds_limit(k_xinv_ct<float, 0, N>);
   set_lds_limit(k_xinv_ct<float, 1, N>);
   set_lds_limit(k_xinv_ct<float, 2, N>);
+  set_lds_limit(k_xinv_ct<double, 3, N>);
+  set_lds_limit(k_xinv_ct<float, 3, N>);
 }
 
 void MONC_NAME(init_fft)() {
@@ -48,10 +52,12 @@ void MONC_NAME(init_fft)() {
 template <int N>
 static void xfwd_length(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int mode, void* stream) {
   if (fp64 && mode == 2) MONC_GO((k_xfwd_ct<double, 2, N>));
+  else if (fp64 && mode == 3) MONC_GO((k_xfwd_ct<double, 3, N>));
   else if (fp64) MONC_GO((k_xfwd_ct<double, 0, N>));
   else if (mode == 0) MONC_GO((k_xfwd_ct<float, 0, N>));
   else if (mode == 1) MONC_GO((k_xfwd_ct<float, 1, N>));
-  else MONC_GO((k_xfwd_ct<float, 2, N>));
+  else if (mode == 2) MONC_GO((k_xfwd_ct<float, 2, N>));
+  else MONC_GO((k_xfwd_ct<float, 3, N>));
 }
 
 // elements per thread (the radix plan) of a length without a plan of its own
@@ -87,10 +93,12 @@ static void ffty_length(const LaunchArgs& a, int grid, int block, size_t lds, bo
 
 template <int N>
 static void xinv_length(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int mode, void* stream) {
-  if (fp64) MONC_GO((k_xinv_ct<double, 0, N>));
+  if (fp64 && mode == 3) MONC_GO((k_xinv_ct<double, 3, N>));
+  else if (fp64) MONC_GO((k_xinv_ct<double, 0, N>));
   else if (mode == 0) MONC_GO((k_xinv_ct<float, 0, N>));
   else if (mode == 1) MONC_GO((k_xinv_ct<float, 1, N>));
-  else MONC_GO((k_xinv_ct<float, 2, N>));
+  else if (mode == 2) MONC_GO((k_xinv_ct<float, 2, N>));
+  else MONC_GO((k_xinv_ct<float, 3, N>));
 }
 
 bool MONC_NAME(launch_xfwd)(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int mode, int ct_n,

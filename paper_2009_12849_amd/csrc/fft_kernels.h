@@ -167,7 +167,10 @@ __device__ __forceinline__ double resid_at(const MemberDesc& d, const RowCtx& c,
 // the mixed path's FP64 residual D(u*) - L p1, MODE 2 a given FP64 field
 // (io.u) rounded to T, i.e. the spectral solve applied to an arbitrary
 // right-hand side (the preconditioner of the variable-density Krylov
-// solver).
+// solver), MODE 3 the Krylov solver's residual, updated on the way: r (io.u)
+// -= alpha q (io.v), alpha = rz / dq from the iteration's scalars (io.w:
+// <r, z> and <d, q>), and the workgroup's sum of dz r^2 into io.stats. The
+// update as a kernel of its own read and wrote r once more.
 template <typename T, int MODE>
 __device__ __forceinline__ T source_at(const MemberDesc& d, const RowCtx& c, const IoPtrs& io, int i) {
   if constexpr (MODE == 0) {
@@ -178,6 +181,35 @@ __device__ __forceinline__ T source_at(const MemberDesc& d, const RowCtx& c, con
   } else {
     return (T)resid_at(d, c, io, i);
   }
+}
+
+// MODE 3 at points i0 .. i0+V-1 of a row
+template <typename T, int V>
+__device__ __forceinline__ void update_vec(const RowCtx& c, const IoPtrs& io, int i0, double alpha, double dz,
+                                           double& acc, T* out);
+
+// alpha of a Krylov iteration from its scalars (kVarRZ, kVarDQ)
+__device__ __forceinline__ double krylov_alpha(const void* row) {
+  const double rz = ldc(static_cast<const double*>(row)), dq = ldc(static_cast<const double*>(row) + 1);
+  return dq != 0.0 ? rz / dq : 0.0;
+}
+
+// Sum of x over the workgroup (any size) in a fixed order, in thread 0. buf:
+// LDS of a double per thread, free for use; every thread calls it.
+__device__ __forceinline__ double group_sum(double x, double* buf) {
+  __syncthreads();
+  buf[threadIdx.x] = x;
+  __syncthreads();
+  double s = 0.0;
+  if (threadIdx.x < 16)
+    for (int i = threadIdx.x; i < (int)blockDim.x; i += 16) s += buf[i];
+  __syncthreads();
+  if (threadIdx.x < 16) buf[threadIdx.x] = s;
+  __syncthreads();
+  s = 0.0;
+  if (threadIdx.x == 0)
+    for (int i = 0; i < min(16, (int)blockDim.x); ++i) s += buf[i];
+  return s;
 }
 
 // ---------------------------------------------------------------------------
@@ -388,6 +420,27 @@ __device__ __forceinline__ void resid_pair_vec(const MemberDesc& d, const RowCtx
   resid_core<W>(d, c1, p1, p2, p0, pu1, pd1, pw1, pe1, u1, um1, v1, v0, wc1, wb1, out1);
 }
 
+template <typename T, int V>
+__device__ __forceinline__ void update_vec(const RowCtx& c, const IoPtrs& io, int i0, double alpha, double dz,
+                                           double& acc, T* out) {
+  constexpr int W = V % 2 == 0 ? 2 : 1;
+  using dv = typename Vec<double, W>::type;
+  double* r = reinterpret_cast<double*>(io.u) + c.off + i0;
+  const double* q = reinterpret_cast<const double*>(io.v) + c.off + i0;
+#pragma unroll
+  for (int e = 0; e < V; e += W) {
+    dv x = ldv<W>(r + e);
+    const dv y = ldv<W>(q + e);
+#pragma unroll
+    for (int h = 0; h < W; ++h) {
+      x[h] -= alpha * y[h];
+      acc += dz * x[h] * x[h];
+      out[e + h] = (T)x[h];
+    }
+    *reinterpret_cast<dv*>(r + e) = x;
+  }
+}
+
 template <typename T, int MODE, int V>
 __device__ __forceinline__ void source_vec(const MemberDesc& d, const RowCtx& c, const IoPtrs& io, int i0, T* out) {
   if constexpr (MODE == 0) {
@@ -525,11 +578,22 @@ __global__ void __launch_bounds__(512)
   //    z = row0 + i row1 into LDS in natural order: chunk i0 of the rows with
   //    contexts (c0, c1) and validity (v0, v1) into transform slot L
   constexpr int V = x_chunk(N, sizeof(T)), NCH = N / V;  // chunks of a row
+  double alpha = 0.0, dz0 = 0.0, dz1 = 0.0, rr = 0.0;     // MODE 3
+  if constexpr (MODE == 3) {
+    alpha = krylov_alpha(io.w);
+    dz0 = ldg(d.dz + c0.k);
+    dz1 = ldg(d.dz + c1.k);
+  }
   auto stencil = [&](const RowCtx& c0, const RowCtx& c1, bool v0, bool v1, int i0, cx<T>* L) {
     T s0[V], s1[V];
     // a full pair within one level (even ny): the two rows share loads
     const bool pair = !(d.ny & 1) && v1;
-    if constexpr (sizeof(T) == 8) {
+    if constexpr (MODE == 3) {
+#pragma unroll
+      for (int e = 0; e < V; ++e) s0[e] = s1[e] = (T)0;
+      if (v0) update_vec<T, V>(c0, io, i0, alpha, dz0, rr, s0);
+      if (v1) update_vec<T, V>(c1, io, i0, alpha, dz1, rr, s1);
+    } else if constexpr (sizeof(T) == 8) {
       if (MODE == 0 && pair) {
         div_pair_vec<T, V>(d, c0, c1, io, i0, s0, s1);
       } else {
@@ -657,6 +721,10 @@ __global__ void __launch_bounds__(512)
       }
     }
   }
+  if constexpr (MODE == 3) {
+    const double s = group_sum(rr, reinterpret_cast<double*>(smem_raw));
+    if (threadIdx.x == 0) io.stats[blockIdx.x] = s;
+  }
 }
 
 // runtime length (fallback)
@@ -680,10 +748,22 @@ __global__ void __launch_bounds__(1024) k_xfwd_gen(LaunchArgs a) {
   const long long r0 = 2 * pair, r1 = 2 * pair + 1;
   const bool v0 = active && r0 < d.nrow, v1 = active && r1 < d.nrow;
   const RowCtx c0 = make_row(d, r0, v0), c1 = make_row(d, r1, v1);
+  double alpha = 0.0, dz0 = 0.0, dz1 = 0.0, rr = 0.0;  // MODE 3
+  if constexpr (MODE == 3) {
+    alpha = krylov_alpha(io.w);
+    dz0 = ldg(d.dz + c0.k);
+    dz1 = ldg(d.dz + c1.k);
+  }
   if (active) {
     for (int i = q; i < N; i += nt) {
-      const T s0 = v0 ? source_at<T, MODE>(d, c0, io, i) : (T)0;
-      const T s1 = v1 ? source_at<T, MODE>(d, c1, io, i) : (T)0;
+      T s0 = 0, s1 = 0;
+      if constexpr (MODE == 3) {
+        if (v0) update_vec<T, 1>(c0, io, i, alpha, dz0, rr, &s0);
+        if (v1) update_vec<T, 1>(c1, io, i, alpha, dz1, rr, &s1);
+      } else {
+        if (v0) s0 = source_at<T, MODE>(d, c0, io, i);
+        if (v1) s1 = source_at<T, MODE>(d, c1, io, i);
+      }
       buf[i] = cx<T>{s0, s1};
     }
   }
@@ -698,6 +778,10 @@ __global__ void __launch_bounds__(1024) k_xfwd_gen(LaunchArgs a) {
       if (v0) S[so0 + cm] = split_bin<T>(z, zr, 0);
       if (v1) S[so1 + cm] = split_bin<T>(z, zr, 1);
     }
+  }
+  if constexpr (MODE == 3) {
+    const double s = group_sum(rr, reinterpret_cast<double*>(smem_raw));
+    if (threadIdx.x == 0) io.stats[blockIdx.x] = s;
   }
 }
 
@@ -913,7 +997,11 @@ __global__ void __launch_bounds__(1024) k_ffty_gen(LaunchArgs a) {
 // x-direction inverse (complex-to-real) FFT of row pairs, written to
 // MODE 0: io.p (storage type T), the pressure;
 // MODE 1 (mixed, T = float): io.s1, the refinement's correction delta;
-// MODE 2 (mixed, T = float): io.s2, the first-pass pressure p1.
+// MODE 2 (mixed, T = float): io.s2, the first-pass pressure p1;
+// MODE 3: io.p, the Krylov solver's z = M^-1 r, with the workgroup's sums of
+// dz r z (r: io.u) into io.stats and, for the flexible update (T = float, q
+// given in io.v), of dz z q into io.w: the inner products as a kernel of their
+// own read z again.
 // Z[m] = X_a[m] + i X_b[m], Z[N-m] = conj X_a[m] + i conj X_b[m]; the
 // imaginary parts of the self-conjugate bins (m = 0, m = N/2) are dropped.
 // ---------------------------------------------------------------------------
@@ -944,9 +1032,38 @@ __device__ __forceinline__ void pack_rows(cx<T>* buf, const Idx& idx, const cx<T
 
 template <typename T, int MODE>
 __device__ __forceinline__ __attribute__((address_space(1))) T* xinv_dest(const IoPtrs& io) {
-  if constexpr (MODE == 0) return gptr(reinterpret_cast<T*>(io.p));
+  if constexpr (MODE == 0 || MODE == 3) return gptr(reinterpret_cast<T*>(io.p));
   else if constexpr (MODE == 1) return gptr(reinterpret_cast<T*>(io.s1));
   else return gptr(reinterpret_cast<T*>(io.s2));
+}
+
+// MODE 3's inner products over values z of a row from point o on
+template <typename T, int V>
+__device__ __forceinline__ void dots_vec(const IoPtrs& io, long long o, const T* z, double dz, double& rz, double& zq) {
+  constexpr int W = V % 2 == 0 ? 2 : 1;
+  using dv = typename Vec<double, W>::type;
+  const double* r = reinterpret_cast<const double*>(io.u) + o;
+  const double* q = reinterpret_cast<const double*>(io.v) + o;
+#pragma unroll
+  for (int e = 0; e < V; e += W) {
+    const dv x = ldv<W>(r + e);
+#pragma unroll
+    for (int h = 0; h < W; ++h) rz += dz * x[h] * (double)z[e + h];
+    if (sizeof(T) == 4 && io.v) {
+      const dv y = ldv<W>(q + e);
+#pragma unroll
+      for (int h = 0; h < W; ++h) zq += dz * (double)z[e + h] * y[h];
+    }
+  }
+}
+template <typename T>
+__device__ __forceinline__ void dots_commit(const IoPtrs& io, double rz, double zq, unsigned char* smem) {
+  const double s = group_sum(rz, reinterpret_cast<double*>(smem));
+  if (threadIdx.x == 0) io.stats[blockIdx.x] = s;
+  if (sizeof(T) == 4 && io.v) {
+    const double t = group_sum(zq, reinterpret_cast<double*>(smem));
+    if (threadIdx.x == 0) reinterpret_cast<double*>(io.w)[blockIdx.x] = t;
+  }
 }
 
 template <typename T, int MODE>
@@ -1053,6 +1170,11 @@ __global__ void __launch_bounds__(512) k_xinv_ct(LaunchArgs a) {
   constexpr int V = x_chunk(N, sizeof(T)), NCH = N / V;
   using vt = typename Vec<T, V>::type;
   auto p = reinterpret_cast<__attribute__((address_space(1))) vt*>(xinv_dest<T, MODE>(io));
+  double dz0 = 0.0, dz1 = 0.0, rz = 0.0, zq = 0.0;  // MODE 3
+  if constexpr (MODE == 3) {
+    dz0 = ldg(d.dz + row_level(d, v0 ? (int)r0 : 0));
+    dz1 = ldg(d.dz + row_level(d, v1 ? (int)r1 : 0));
+  }
 #pragma unroll
   for (int t = 0; t < (NCH + NT - 1) / NT; ++t) {
     const int ch = q + t * NT;
@@ -1066,8 +1188,13 @@ __global__ void __launch_bounds__(512) k_xinv_ct(LaunchArgs a) {
       }
       if (v0) p[r0 * NCH + ch] = a0;
       if (v1) p[r1 * NCH + ch] = a1;
+      if constexpr (MODE == 3) {
+        if (v0) dots_vec<T, V>(io, r0 * N + ch * V, reinterpret_cast<const T*>(&a0), dz0, rz, zq);
+        if (v1) dots_vec<T, V>(io, r1 * N + ch * V, reinterpret_cast<const T*>(&a1), dz1, rz, zq);
+      }
     }
   }
+  if constexpr (MODE == 3) dots_commit<T>(io, rz, zq, smem_raw);
 }
 
 template <typename T, int MODE>
@@ -1098,6 +1225,17 @@ __global__ void __launch_bounds__(1024) k_xinv_gen(LaunchArgs a) {
   fft_lds<T, true>(buf, 1, d.fx, reinterpret_cast<const cx<T>*>(d.twx), q);
   if (active)
     for (int i = q; i < N; i += nt) store_rows<T, MODE>(d, io, r0, r1, v0, v1, i, buf[i]);
+  if constexpr (MODE == 3) {
+    const double dz0 = ldg(d.dz + row_level(d, v0 ? (int)r0 : 0)), dz1 = ldg(d.dz + row_level(d, v1 ? (int)r1 : 0));
+    double rz = 0.0, zq = 0.0;
+    if (active)
+      for (int i = q; i < N; i += nt) {
+        const cx<T> z = buf[i];
+        if (v0) dots_vec<T, 1>(io, r0 * N + i, &z.x, dz0, rz, zq);
+        if (v1) dots_vec<T, 1>(io, r1 * N + i, &z.y, dz1, rz, zq);
+      }
+    dots_commit<T>(io, rz, zq, smem_raw);
+  }
 }
 
 }  // namespace monc

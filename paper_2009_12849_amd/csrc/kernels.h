@@ -46,7 +46,9 @@ inline int ct_threads_y_host(int n, int ept) { return ct_threads_y_n(n, ept); }
 // ct_n: the compile-time length, or 0 for the runtime-length kernel.
 // mode 0: divergence of (u, v, w); mode 1 (float only): the FP64 residual
 // D(u) - D(G p1) with the first-pass pressure p1 in io.s2; mode 2: the FP64
-// field at io.u (nz, ny, nx), rounded to the storage type.
+// field at io.u (nz, ny, nx), rounded to the storage type; mode 3 (one member):
+// that field after io.u -= alpha io.v, alpha from the two scalars at io.w, with
+// one partial sum of dz io.u^2 per workgroup into io.stats.
 void launch_xfwd(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int mode, int ct_n, void* stream);
 // ept: elements per thread of the compile-time kernel (8 or 16; 32 = the
 // persistent FP32 kernel, whose grid covers the CUs once)
@@ -58,7 +60,9 @@ void launch_tridiag(const LaunchArgs& a, int grid, int block, size_t lds, bool f
 // member's tcrows), block = 64 times the member's tcwaves
 void launch_tricol(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int rows, void* stream);
 // the result goes to io.p (mode 0), io.s1 (mode 1, float only: the
-// correction delta) or io.s2 (mode 2, float only: the first-pass pressure)
+// correction delta) or io.s2 (mode 2, float only: the first-pass pressure);
+// mode 3 (one member): io.p, with one partial sum per workgroup of dz io.u io.p
+// into io.stats and (float, io.v given) of dz io.p io.v into io.w
 void launch_xinv(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int mode, int ct_n, void* stream);
 // fp64: pressure from io.p (FP64); else (mixed path) p1 + delta summed in
 // FP64 from io.s2 + io.s1, and written rounded to io.p. vec: points per

@@ -230,6 +230,8 @@ void init_kernel_attributes() {
   set_lds_limit(k_xfwd_gen<float, 1>);
   set_lds_limit(k_xfwd_gen<double, 2>);
   set_lds_limit(k_xfwd_gen<float, 2>);
+  set_lds_limit(k_xfwd_gen<double, 3>);
+  set_lds_limit(k_xfwd_gen<float, 3>);
   set_lds_limit(k_ffty_gen<double, false>);
   set_lds_limit(k_ffty_gen<double, true>);
   set_lds_limit(k_ffty_gen<float, false>);
@@ -238,6 +240,8 @@ void init_kernel_attributes() {
   set_lds_limit(k_xinv_gen<float, 0>);
   set_lds_limit(k_xinv_gen<float, 1>);
   set_lds_limit(k_xinv_gen<float, 2>);
+  set_lds_limit(k_xinv_gen<double, 3>);
+  set_lds_limit(k_xinv_gen<float, 3>);
 }
 
 void launch_xfwd(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int mode, int ct_n, void* stream) {
@@ -249,10 +253,12 @@ void launch_xfwd(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64
     return;
   }
   if (fp64 && mode == 2) MONC_GO((k_xfwd_gen<double, 2>));
+  else if (fp64 && mode == 3) MONC_GO((k_xfwd_gen<double, 3>));
   else if (fp64) MONC_GO((k_xfwd_gen<double, 0>));
   else if (mode == 0) MONC_GO((k_xfwd_gen<float, 0>));
   else if (mode == 1) MONC_GO((k_xfwd_gen<float, 1>));
-  else MONC_GO((k_xfwd_gen<float, 2>));
+  else if (mode == 2) MONC_GO((k_xfwd_gen<float, 2>));
+  else MONC_GO((k_xfwd_gen<float, 3>));
 }
 
 void launch_ffty(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, bool inverse, int ct_n, int ept,
@@ -281,10 +287,12 @@ void launch_xinv(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64
 #undef MONC_GROUP_TRY
     return;
   }
-  if (fp64) MONC_GO((k_xinv_gen<double, 0>));
+  if (fp64 && mode == 3) MONC_GO((k_xinv_gen<double, 3>));
+  else if (fp64) MONC_GO((k_xinv_gen<double, 0>));
   else if (mode == 0) MONC_GO((k_xinv_gen<float, 0>));
   else if (mode == 1) MONC_GO((k_xinv_gen<float, 1>));
-  else MONC_GO((k_xinv_gen<float, 2>));
+  else if (mode == 2) MONC_GO((k_xinv_gen<float, 2>));
+  else MONC_GO((k_xinv_gen<float, 3>));
 }
 
 void launch_grad(const LaunchArgs& a, int grid, bool fp64, int vec, bool red, void* stream) {

@@ -22,14 +22,17 @@
 //   rx = (rho_i + rho_{i+1})/2, ry = (rho_j + rho_{j+1})/2 (periodic),
 //   rz_k = za_k rho_k + zb_k rho_{k+1}, za_k = dz_{k+1}/(dz_k + dz_{k+1}),
 //   zb_k = dz_k/(dz_k + dz_{k+1}) (0 on the lid).
-// A workgroup of kVarBlock threads takes a 2-D tile of kVarSpan points of a
-// level, min(nx, 256) wide (kVarPts per thread at stride kVarBlock in the
-// tile, coalesced along rows). The stencil
-// kernels (divergence, operator) walk them up a group of kVarLevels levels
+// A workgroup of kVarBlock threads takes a 2-D tile of a level, min(nx, 256)
+// wide, a few points per thread at stride kVarBlock in the tile, coalesced
+// along rows. The stencil kernels (divergence, operator; kVarStPts points a
+// thread) walk them up a group of kVarLevels levels
 // (blockIdx.y), keeping the column's values of the levels below and above in
 // registers, so only the x and y neighbours come through the caches; the
-// pointwise kernels take one level per workgroup (more, shorter workgroups
-// stream faster). For even nx the operator works on pairs of adjacent x
+// pointwise kernels (kVarPts points a thread) take one level per workgroup (more, shorter
+// workgroups stream faster). Two points and two levels a stencil thread leave
+// enough workgroups to even out the last wave of them: the operator 68 us with
+// four and four, 60 us with two and two at 256^2 x 128, 39.5 and 29.5 us at 288 x 216
+// x 48. For even nx the operator works on pairs of adjacent x
 // points with 16-byte loads (k_var_apply2).
 // Inner products are weighted by dz_k (the weight that makes D_rho G
 // self-adjoint); each workgroup writes its partial sum and a one-workgroup
@@ -65,12 +68,12 @@ __device__ __forceinline__ double block_sum(double x) {
   return s;
 }
 
-// One thread's points: kVarPts points of a level at stride kVarBlock
-// (horizontal offsets inside a level and their x and y neighbours, periodic),
+// One thread's points: NPTS points of a level at stride kVarBlock (horizontal offsets inside a level and their x and y neighbours, periodic),
 // revisited on each level of the workgroup's group of kVarLevels levels.
+template <int NPTS>
 struct Col {
-  int h[kVarPts], hw[kVarPts], he[kVarPts], hs[kVarPts], hn[kVarPts];
-  bool live[kVarPts];
+  int h[NPTS], hw[NPTS], he[NPTS], hs[NPTS], hn[NPTS];
+  bool live[NPTS];
 };
 
 // The workgroup's (point chunk, level group)
@@ -79,12 +82,13 @@ struct Blk {
 };
 __device__ __forceinline__ Blk var_block() { return Blk{(int)blockIdx.x, (int)blockIdx.y}; }
 
-__device__ __forceinline__ Col columns(const VarGrid& g, const Blk& bk) {
-  Col c;
-  const int tw = var_tile_w(g.nx), th = var_tile_h(g.nx), ntx = var_tiles_x(g.nx);
+template <int NPTS>
+__device__ __forceinline__ Col<NPTS> columns(const VarGrid& g, const Blk& bk) {
+  Col<NPTS> c;
+  const int tw = var_tile_w(g.nx), th = var_tile_h(g.nx, NPTS), ntx = var_tiles_x(g.nx);
   const int tile_y = bk.x / ntx, tile_x = bk.x - tile_y * ntx;
 #pragma unroll
-  for (int t = 0; t < kVarPts; ++t) {
+  for (int t = 0; t < NPTS; ++t) {
     const int sl = t * kVarBlock + threadIdx.x;          // slot in the tile
     const int rr = sl / tw, ic = tile_x * tw + (sl - rr * tw), jr = tile_y * th + rr;
     c.live[t] = rr < th && ic < g.nx && jr < g.ny;
@@ -140,14 +144,14 @@ __global__ void __launch_bounds__(kVarBlock) k_var_div(VarGrid g, const double* 
                                                      double* __restrict__ r, double* __restrict__ p,
                                                      double* __restrict__ part) {
   const Blk bk = var_block();
-  const Col c = columns(g, bk);
+  const Col<kVarStPts> c = columns<kVarStPts>(g, bk);
   const long long nh = (long long)g.nx * g.ny;
   const int k0 = level_begin<kVarLevels>(bk), k1 = level_end<kVarLevels>(g, bk);
-  double rdn[kVarPts], wdn[kVarPts], rc[kVarPts];
+  double rdn[kVarStPts], wdn[kVarStPts], rc[kVarStPts];
   {
     const long long b0 = (long long)k0 * nh, bd = k0 > 0 ? b0 - nh : b0;
 #pragma unroll
-    for (int t = 0; t < kVarPts; ++t) {
+    for (int t = 0; t < kVarStPts; ++t) {
       rdn[t] = g.rho[bd + c.h[t]];
       wdn[t] = w[bd + c.h[t]];
       rc[t] = g.rho[b0 + c.h[t]];
@@ -158,7 +162,7 @@ __global__ void __launch_bounds__(kVarBlock) k_var_div(VarGrid g, const double* 
     const Lev L = level(g, k);
     const long long b = (long long)k * nh, bu = L.top ? b + nh : b;
 #pragma unroll
-    for (int t = 0; t < kVarPts; ++t) {
+    for (int t = 0; t < kVarStPts; ++t) {
       const double ru = g.rho[bu + c.h[t]], wc = w[b + c.h[t]];
       const double rxe = 0.5 * (rc[t] + g.rho[b + c.he[t]]), rxw = 0.5 * (g.rho[b + c.hw[t]] + rc[t]);
       const double ryn = 0.5 * (rc[t] + g.rho[b + c.hn[t]]), rys = 0.5 * (g.rho[b + c.hs[t]] + rc[t]);
@@ -188,14 +192,14 @@ __global__ void __launch_bounds__(kVarBlock) k_var_apply(VarGrid g, const double
                                                        double* __restrict__ part) {
   if (var_done(scal)) return;
   const Blk bk = var_block();
-  const Col c = columns(g, bk);
+  const Col<kVarStPts> c = columns<kVarStPts>(g, bk);
   const long long nh = (long long)g.nx * g.ny;
   const int k0 = level_begin<kVarLevels>(bk), k1 = level_end<kVarLevels>(g, bk);
-  double ddn[kVarPts], rdn[kVarPts], dc[kVarPts], rc[kVarPts];
+  double ddn[kVarStPts], rdn[kVarStPts], dc[kVarStPts], rc[kVarStPts];
   {
     const long long b0 = (long long)k0 * nh, bd = k0 > 0 ? b0 - nh : b0;
 #pragma unroll
-    for (int t = 0; t < kVarPts; ++t) {
+    for (int t = 0; t < kVarStPts; ++t) {
       ddn[t] = d[bd + c.h[t]];
       rdn[t] = g.rho[bd + c.h[t]];
       dc[t] = d[b0 + c.h[t]];
@@ -207,7 +211,7 @@ __global__ void __launch_bounds__(kVarBlock) k_var_apply(VarGrid g, const double
     const Lev L = level(g, k);
     const long long b = (long long)k * nh, bu = L.top ? b + nh : b;
 #pragma unroll
-    for (int t = 0; t < kVarPts; ++t) {
+    for (int t = 0; t < kVarStPts; ++t) {
       const double du = d[bu + c.h[t]], ru = g.rho[bu + c.h[t]];
       const double rxe = 0.5 * (rc[t] + g.rho[b + c.he[t]]), rxw = 0.5 * (g.rho[b + c.hw[t]] + rc[t]);
       const double ryn = 0.5 * (rc[t] + g.rho[b + c.hn[t]]), rys = 0.5 * (g.rho[b + c.hs[t]] + rc[t]);
@@ -232,7 +236,7 @@ __global__ void __launch_bounds__(kVarBlock) k_var_apply(VarGrid g, const double
 
 // The operator for even nx on pairs of adjacent x points with 16-byte
 // loads: a workgroup's tile (var_tile_h rows of var_tile_w / 2 pairs) holds
-// kVarSpan/2 pairs, two per thread at stride kVarBlock; a pair's x
+// half as many pairs as points, two per thread at stride kVarBlock; a pair's x
 // neighbours outside it are two 8-byte loads. 10 load instructions per pair
 // instead of 16 for two points.
 typedef double d2v __attribute__((ext_vector_type(2)));
@@ -242,10 +246,10 @@ __global__ void __launch_bounds__(kVarBlock) k_var_apply2(VarGrid g, const doubl
                                                         const double* __restrict__ d, double* __restrict__ q,
                                                         double* __restrict__ part) {
   if (var_done(scal)) return;
-  constexpr int NP = kVarPts / 2;   // pairs per thread
+  constexpr int NP = kVarStPts / 2;   // pairs per thread
   const Blk bk = var_block();
   const int hx = g.nx / 2;
-  const int txp = var_tile_w(g.nx) / 2, tyr = var_tile_h(g.nx), ntx = var_tiles_x(g.nx);
+  const int txp = var_tile_w(g.nx) / 2, tyr = var_tile_h(g.nx, kVarStPts), ntx = var_tiles_x(g.nx);
   const int tile_y = bk.x / ntx, tile_x = bk.x - tile_y * ntx;
   int h[NP], hw[NP], he[NP], hs[NP], hn[NP];
   bool live[NP];
@@ -313,16 +317,60 @@ __global__ void __launch_bounds__(kVarBlock) k_var_apply2(VarGrid g, const doubl
   if (threadIdx.x == 0) part[part_index()] = sm;
 }
 
-// alpha = rz/dq; p += alpha d; r -= alpha q; partial sums of dz r^2
-__global__ void __launch_bounds__(kVarBlock) k_var_update(VarGrid g, const double* __restrict__ scal, int it,
-                                                        double* __restrict__ p, double* __restrict__ r,
-                                                        const double* __restrict__ d, const double* __restrict__ q,
-                                                        double* __restrict__ part) {
-  if (var_done(scal)) return;
+// alpha of iteration it
+__device__ __forceinline__ double var_alpha(const double* scal, int it) {
   const double rz = scal[var_slot(it, kVarRZ)], dq = scal[var_slot(it, kVarDQ)];
-  const double alpha = dq != 0.0 ? rz / dq : 0.0;
+  return dq != 0.0 ? rz / dq : 0.0;
+}
+
+// The solution takes the step the residual took (p += alpha_{it-1} d_{it-1}),
+// then d = z + beta d (d = z at it = 0, and p unchanged), in one pass over d;
+// flexible (Polak-Ribiere):
+// beta = <z_it, r_it - r_{it-1}> / rz_{it-1} = -alpha_{it-1} <z_it, q_{it-1}> / rz_{it-1};
+// otherwise (Fletcher-Reeves) beta = rz_it / rz_{it-1}
+template <typename ZT, bool FLEX>
+__global__ void __launch_bounds__(kVarBlock) k_var_dir(VarGrid g, const double* __restrict__ scal, int it,
+                                                     const ZT* __restrict__ z, double* __restrict__ d,
+                                                     double* __restrict__ p) {
+  if (var_done(scal)) return;
+  double beta = 0.0, alpha = 0.0;
+  if (it > 0) {
+    const double rzp = scal[var_slot(it - 1, kVarRZ)];
+    alpha = var_alpha(scal, it - 1);
+    if constexpr (FLEX) beta = rzp != 0.0 ? -alpha * scal[var_slot(it, kVarZQ)] / rzp : 0.0;
+    else beta = rzp != 0.0 ? scal[var_slot(it, kVarRZ)] / rzp : 0.0;
+  }
   const Blk bk = var_block();
-  const Col c = columns(g, bk);
+  const Col<kVarPts> c = columns<kVarPts>(g, bk);
+  const long long nh = (long long)g.nx * g.ny;
+  for (int k = level_begin<1>(bk), k1 = level_end<1>(g, bk); k < k1; ++k) {
+    const long long b = (long long)k * nh;
+#pragma unroll
+    for (int t = 0; t < kVarPts; ++t) {
+      const long long o = b + c.h[t];
+      const double zc = (double)z[o];
+      if (it > 0) {  // d is not yet defined at it = 0
+        const double dc = d[o], pn = p[o] + alpha * dc;
+        if (c.live[t]) {
+          p[o] = pn;
+          d[o] = zc + beta * dc;
+        }
+      } else if (c.live[t]) {
+        d[o] = zc;
+      }
+    }
+  }
+}
+
+// The last iteration's step of the solution (p += alpha_{it-1} d_{it-1}: the
+// direction update that would take it is not run once the solve is done), and
+// partial sums of dz p (the gauge)
+__global__ void __launch_bounds__(kVarBlock) k_var_wsum(VarGrid g, const double* __restrict__ scal, int it,
+                                                      const double* __restrict__ d, double* __restrict__ p,
+                                                      double* __restrict__ part) {
+  const double alpha = var_alpha(scal, it - 1);
+  const Blk bk = var_block();
+  const Col<kVarPts> c = columns<kVarPts>(g, bk);
   const long long nh = (long long)g.nx * g.ny;
   double acc = 0.0;
   for (int k = level_begin<1>(bk), k1 = level_end<1>(g, bk); k < k1; ++k) {
@@ -332,101 +380,10 @@ __global__ void __launch_bounds__(kVarBlock) k_var_update(VarGrid g, const doubl
     for (int t = 0; t < kVarPts; ++t) {
       const long long o = b + c.h[t];
       const double pn = p[o] + alpha * d[o];
-      const double rn = r[o] - alpha * q[o];
       if (c.live[t]) {
         p[o] = pn;
-        r[o] = rn;
-        acc += dz * rn * rn;
+        acc += dz * pn;
       }
-    }
-  }
-  const double s = block_sum<kVarBlock>(acc);
-  if (threadIdx.x == 0) part[part_index()] = s;
-}
-
-// partial sums of dz r z (<r, z>) and, for the flexible update (FLEX),
-// dz z q (<z, q>)
-template <typename ZT, bool FLEX>
-__global__ void __launch_bounds__(kVarBlock) k_var_dots(VarGrid g, const double* __restrict__ scal,
-                                                      const double* __restrict__ r, const ZT* __restrict__ z,
-                                                      const double* __restrict__ q, double* __restrict__ part0,
-                                                      double* __restrict__ part1) {
-  if (var_done(scal)) return;
-  const Blk bk = var_block();
-  const Col c = columns(g, bk);
-  const long long nh = (long long)g.nx * g.ny;
-  double a0 = 0.0, a1 = 0.0;
-  for (int k = level_begin<1>(bk), k1 = level_end<1>(g, bk); k < k1; ++k) {
-    const long long b = (long long)k * nh;
-    const double dz = g.dz[k];
-#pragma unroll
-    for (int t = 0; t < kVarPts; ++t) {
-      const long long o = b + c.h[t];
-      const double zc = (double)z[o], rc = r[o];
-      if (c.live[t]) a0 += dz * rc * zc;
-      if constexpr (FLEX) {
-        const double qc = q[o];
-        if (c.live[t]) a1 += dz * zc * qc;
-      }
-    }
-  }
-  const double s0 = block_sum<kVarBlock>(a0);
-  if (threadIdx.x == 0) part0[part_index()] = s0;
-  if constexpr (FLEX) {
-    __syncthreads();  // block_sum's LDS is reused
-    const double s1 = block_sum<kVarBlock>(a1);
-    if (threadIdx.x == 0) part1[part_index()] = s1;
-  }
-}
-
-// d = z + beta d (beta = 0 at it = 0); flexible (Polak-Ribiere):
-// beta = <z_it, r_it - r_{it-1}> / rz_{it-1} = -alpha_{it-1} <z_it, q_{it-1}> / rz_{it-1};
-// otherwise (Fletcher-Reeves) beta = rz_it / rz_{it-1}
-template <typename ZT, bool FLEX>
-__global__ void __launch_bounds__(kVarBlock) k_var_dir(VarGrid g, const double* __restrict__ scal, int it,
-                                                     const ZT* __restrict__ z, double* __restrict__ d) {
-  if (var_done(scal)) return;
-  double beta = 0.0;
-  if (it > 0) {
-    const double rzp = scal[var_slot(it - 1, kVarRZ)];
-    if constexpr (FLEX) {
-      const double dqp = scal[var_slot(it - 1, kVarDQ)];
-      const double alpha = dqp != 0.0 ? rzp / dqp : 0.0;
-      beta = rzp != 0.0 ? -alpha * scal[var_slot(it, kVarZQ)] / rzp : 0.0;
-    } else {
-      beta = rzp != 0.0 ? scal[var_slot(it, kVarRZ)] / rzp : 0.0;
-    }
-  }
-  const Blk bk = var_block();
-  const Col c = columns(g, bk);
-  const long long nh = (long long)g.nx * g.ny;
-  for (int k = level_begin<1>(bk), k1 = level_end<1>(g, bk); k < k1; ++k) {
-    const long long b = (long long)k * nh;
-#pragma unroll
-    for (int t = 0; t < kVarPts; ++t) {
-      const long long o = b + c.h[t];
-      const double zc = (double)z[o];
-      // d is not yet defined at it = 0
-      const double dn = it > 0 ? zc + beta * d[o] : zc;
-      if (c.live[t]) d[o] = dn;
-    }
-  }
-}
-
-// partial sums of dz p (the gauge)
-__global__ void __launch_bounds__(kVarBlock) k_var_wsum(VarGrid g, const double* __restrict__ p,
-                                                      double* __restrict__ part) {
-  const Blk bk = var_block();
-  const Col c = columns(g, bk);
-  const long long nh = (long long)g.nx * g.ny;
-  double acc = 0.0;
-  for (int k = level_begin<1>(bk), k1 = level_end<1>(g, bk); k < k1; ++k) {
-    const long long b = (long long)k * nh;
-    const double dz = g.dz[k];
-#pragma unroll
-    for (int t = 0; t < kVarPts; ++t) {
-      const double pc = p[b + c.h[t]];
-      if (c.live[t]) acc += dz * pc;
     }
   }
   const double s = block_sum<kVarBlock>(acc);
@@ -438,7 +395,7 @@ __global__ void __launch_bounds__(kVarBlock) k_var_shift(VarGrid g, const double
                                                        double rw, double* __restrict__ p) {
   const double m = scal[slot] * rw;
   const Blk bk = var_block();
-  const Col c = columns(g, bk);
+  const Col<kVarPts> c = columns<kVarPts>(g, bk);
   const long long nh = (long long)g.nx * g.ny;
   for (int k = level_begin<1>(bk), k1 = level_end<1>(g, bk); k < k1; ++k) {
     const long long b = (long long)k * nh;
@@ -503,9 +460,9 @@ __global__ void k_var_zero(double* __restrict__ x, int n) {
 // the stencil kernels' grid (level groups of kVarLevels) and the pointwise
 // kernels' grid (one level per workgroup)
 static dim3 var_grid_stencil(const VarGrid& g) {
-  return dim3((unsigned)var_blocks_per_level(g.nx, g.ny), (unsigned)var_level_groups(g.nz));
+  return dim3((unsigned)var_blocks_per_level(g.nx, g.ny, kVarStPts), (unsigned)var_level_groups(g.nz));
 }
-static dim3 var_grid(const VarGrid& g) { return dim3((unsigned)var_blocks_per_level(g.nx, g.ny), (unsigned)g.nz); }
+static dim3 var_grid(const VarGrid& g) { return dim3((unsigned)var_blocks_per_level(g.nx, g.ny, kVarPts), (unsigned)g.nz); }
 
 void launch_var_div(const VarGrid& g, const double* u, const double* v, const double* w, double* r, double* p,
                     double* part, void* stream) {
@@ -520,35 +477,21 @@ void launch_var_apply(const VarGrid& g, const double* scal, const double* d, dou
     hipLaunchKernelGGL(k_var_apply, var_grid_stencil(g), dim3(kVarBlock), 0, (hipStream_t)stream, g, scal, d, q, part);
 }
 
-void launch_var_update(const VarGrid& g, const double* scal, int it, double* p, double* r, const double* d,
-                       const double* q, double* part, void* stream) {
-  hipLaunchKernelGGL(k_var_update, var_grid(g), dim3(kVarBlock), 0, (hipStream_t)stream, g, scal, it, p, r, d, q,
-                     part);
-}
-
 // the FP64 preconditioner takes the Fletcher-Reeves update, the FP32 one the
 // flexible update
-void launch_var_dots(const VarGrid& g, const double* scal, const double* r, const void* z, bool z64, const double* q,
-                     double* part0, double* part1, void* stream) {
-  if (z64)
-    hipLaunchKernelGGL((k_var_dots<double, false>), var_grid(g), dim3(kVarBlock), 0, (hipStream_t)stream, g, scal, r,
-                       static_cast<const double*>(z), q, part0, part1);
-  else
-    hipLaunchKernelGGL((k_var_dots<float, true>), var_grid(g), dim3(kVarBlock), 0, (hipStream_t)stream, g, scal, r,
-                       static_cast<const float*>(z), q, part0, part1);
-}
-
-void launch_var_dir(const VarGrid& g, const double* scal, int it, const void* z, bool z64, double* d, void* stream) {
+void launch_var_dir(const VarGrid& g, const double* scal, int it, const void* z, bool z64, double* d, double* p,
+                    void* stream) {
   if (z64)
     hipLaunchKernelGGL((k_var_dir<double, false>), var_grid(g), dim3(kVarBlock), 0, (hipStream_t)stream, g, scal,
-                       it, static_cast<const double*>(z), d);
+                       it, static_cast<const double*>(z), d, p);
   else
     hipLaunchKernelGGL((k_var_dir<float, true>), var_grid(g), dim3(kVarBlock), 0, (hipStream_t)stream, g, scal, it,
-                       static_cast<const float*>(z), d);
+                       static_cast<const float*>(z), d, p);
 }
 
-void launch_var_wsum(const VarGrid& g, const double* p, double* part, void* stream) {
-  hipLaunchKernelGGL(k_var_wsum, var_grid(g), dim3(kVarBlock), 0, (hipStream_t)stream, g, p, part);
+void launch_var_wsum(const VarGrid& g, const double* scal, int it, const double* d, double* p, double* part,
+                     void* stream) {
+  hipLaunchKernelGGL(k_var_wsum, var_grid(g), dim3(kVarBlock), 0, (hipStream_t)stream, g, scal, it, d, p, part);
 }
 
 void launch_var_shift(const VarGrid& g, const double* scal, int slot, double rw, double* p, void* stream) {

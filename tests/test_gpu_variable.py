@@ -107,6 +107,23 @@ def test_variable_density_matches_direct_solve(shape, dtype):
     assert perr <= 1e-8 * max(np.abs(ref[3]).max(), 1e-300), perr / np.abs(ref[3]).max()
 
 
+@pytest.mark.parametrize("dtype", ["f64", "mixed"])
+@pytest.mark.parametrize("shape", [(54, 16, 6), (27, 9, 5), (12, 6, 4)])
+@pytest.mark.parametrize("maxit", [1, 2, 3])
+def test_stopped_solve_returns_the_iterate_of_its_residual(shape, dtype, maxit):
+    """A solve stopped by maxit: the velocities' own divergence has the relative
+    norm that it reports (p holds the last step), whatever the row chunk (2, 1
+    point; the runtime-length kernels at 12) and the last workgroup's rows. D of
+    the outputs carries their rounding, 2^-53 max|u| / min spacing per term
+    against |D(u*)| of the same size over the grid: 1e-12 with room."""
+    g, rho, u, v, w = _case(shape, 1700 + sum(shape))
+    outs, it, rel = _run(g, rho, u, v, w, dtype, maxit=maxit)
+    assert it == maxit
+    b = oracle.divergence_var(u, v, w, g.dx, g.dy, g.dz, rho)
+    res = oracle.divergence_var(*outs[:3], g.dx, g.dy, g.dz, rho)
+    assert abs(_wnorm(res, g.dz) / _wnorm(b, g.dz) - rel) <= 1e-12
+
+
 def test_separable_density_is_one_spectral_solve():
     """rho = rho0(z): the preconditioner is the exact inverse, CG stops after
     one iteration (two at most, from rounding) with monc_project's answer."""

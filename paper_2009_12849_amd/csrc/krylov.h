@@ -8,6 +8,7 @@ constexpr int kVarBlock = 256;                  // threads per workgroup
 constexpr int kVarPts = 4;                      // points per thread of the pointwise kernels
 constexpr int kVarStPts = 2;                    // points per thread of the stencil kernels (even)
 constexpr int kVarLevels = 2;                   // levels per stencil workgroup (walked upwards)
+constexpr int kVarBand = 64;                    // tiles a level of the stencil kernels' block order
 constexpr int kVarFinishBlock = 1024;           // threads of the partial-sum reduction
 
 // Scalars in scal[]: a status row, then per iteration it the dz-weighted

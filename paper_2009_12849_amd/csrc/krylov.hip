@@ -82,6 +82,23 @@ struct Blk {
 };
 __device__ __forceinline__ Blk var_block() { return Blk{(int)blockIdx.x, (int)blockIdx.y}; }
 
+// The operator's blocks (a 1-D grid) in an order that lets the rows and levels a
+// stencil reads again meet in the L2 that holds them: of every 64 blocks an XCD
+// (block mod 8) takes 8 neighbouring ones, and the blocks walk the level groups
+// of a band of kVarBand tiles (about 32 K points a level) before the next band.
+// Against launch order: 535 -> 475 us at 1024^2 x 64, 29 -> 26 at 288 x 216 x 48,
+// equal at 256^2 x 128 (64; an eighth of the grid per XCD 75). The divergence,
+// run once, is 0-10 % slower that way and keeps launch order.
+__device__ __forceinline__ Blk var_operator_block(const VarGrid& g) {
+  const int tiles = (int)var_blocks_per_level(g.nx, g.ny, kVarStPts), groups = var_level_groups(g.nz);
+  const int b = blockIdx.x;
+  const int id = b < (tiles * groups & ~63) ? (b & ~63) | (b & 7) << 3 | (b >> 3 & 7) : b;
+  const int band = id / (kVarBand * groups), rem = id - band * kVarBand * groups;
+  const int nb = min(kVarBand, tiles - band * kVarBand);
+  const int grp = rem / nb;
+  return Blk{band * kVarBand + rem - grp * nb, grp};
+}
+
 template <int NPTS>
 __device__ __forceinline__ Col<NPTS> columns(const VarGrid& g, const Blk& bk) {
   Col<NPTS> c;
@@ -191,7 +208,7 @@ __global__ void __launch_bounds__(kVarBlock) k_var_apply(VarGrid g, const double
                                                        const double* __restrict__ d, double* __restrict__ q,
                                                        double* __restrict__ part) {
   if (var_done(scal)) return;
-  const Blk bk = var_block();
+  const Blk bk = var_operator_block(g);
   const Col<kVarStPts> c = columns<kVarStPts>(g, bk);
   const long long nh = (long long)g.nx * g.ny;
   const int k0 = level_begin<kVarLevels>(bk), k1 = level_end<kVarLevels>(g, bk);
@@ -236,9 +253,18 @@ __global__ void __launch_bounds__(kVarBlock) k_var_apply(VarGrid g, const double
 
 // The operator for even nx on pairs of adjacent x points with 16-byte
 // loads: a workgroup's tile (var_tile_h rows of var_tile_w / 2 pairs) holds
-// half as many pairs as points, two per thread at stride kVarBlock; a pair's x
-// neighbours outside it are two 8-byte loads. 10 load instructions per pair
-// instead of 16 for two points.
+// half as many pairs as points, at stride kVarBlock per thread; six 16-byte
+// loads a pair and level instead of 16 8-byte ones for two points.
+// The x neighbours come from the neighbouring lanes (a DPP shift by one lane of
+// the wave) wherever those hold the pair beside, else (the ends of a wave and of
+// a row of the tile) from memory: 64.7 -> 61.9 us at 256^2 x 128, 26.2 -> 24.7 at
+// 288 x 216 x 48, where the 8-byte loads for them were two in eight.
+template <int CTRL>
+__device__ __forceinline__ double wave_shift(double v) {  // 0x138: from the lane below, 0x130: above
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
+  return __hiloint2double(hi, lo);
+}
 typedef double d2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ d2v ld2(const double* p) { return *reinterpret_cast<const d2v*>(p); }
 
@@ -247,16 +273,19 @@ __global__ void __launch_bounds__(kVarBlock) k_var_apply2(VarGrid g, const doubl
                                                         double* __restrict__ part) {
   if (var_done(scal)) return;
   constexpr int NP = kVarStPts / 2;   // pairs per thread
-  const Blk bk = var_block();
+  const Blk bk = var_operator_block(g);
   const int hx = g.nx / 2;
   const int txp = var_tile_w(g.nx) / 2, tyr = var_tile_h(g.nx, kVarStPts), ntx = var_tiles_x(g.nx);
   const int tile_y = bk.x / ntx, tile_x = bk.x - tile_y * ntx;
   int h[NP], hw[NP], he[NP], hs[NP], hn[NP];
-  bool live[NP];
+  bool live[NP], loadw[NP], loade[NP];
+  const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int t = 0; t < NP; ++t) {
     const int sl = t * kVarBlock + threadIdx.x;          // slot in the tile
-    const int rr = sl / txp, pc = tile_x * txp + (sl - rr * txp), jr = tile_y * tyr + rr;
+    const int rr = sl / txp, pt = sl - rr * txp, pc = tile_x * txp + pt, jr = tile_y * tyr + rr;
+    loadw[t] = lane == 0 || pt == 0;
+    loade[t] = lane == 63 || pt == txp - 1 || pc == hx - 1;
     live[t] = rr < tyr && pc < hx && jr < g.ny;
     const int j = live[t] ? jr : 0, i0 = live[t] ? 2 * pc : 0;   // outside the grid: pair 0, nothing stored
     const int row = j * g.nx;
@@ -288,8 +317,16 @@ __global__ void __launch_bounds__(kVarBlock) k_var_apply2(VarGrid g, const doubl
       const d2v du = ld2(d + bu + h[t]), ru = ld2(g.rho + bu + h[t]);
       const d2v dn = ld2(d + b + hn[t]), ds = ld2(d + b + hs[t]);
       const d2v rn = ld2(g.rho + b + hn[t]), rs = ld2(g.rho + b + hs[t]);
-      const double dw = d[b + hw[t]], de = d[b + he[t]];
-      const double rw = g.rho[b + hw[t]], re = g.rho[b + he[t]];
+      double dw = wave_shift<0x138>(dc[t][1]), rw = wave_shift<0x138>(rc[t][1]);
+      double de = wave_shift<0x130>(dc[t][0]), re = wave_shift<0x130>(rc[t][0]);
+      if (loadw[t]) {
+        dw = d[b + hw[t]];
+        rw = g.rho[b + hw[t]];
+      }
+      if (loade[t]) {
+        de = d[b + he[t]];
+        re = g.rho[b + he[t]];
+      }
       d2v a;
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
@@ -462,6 +499,7 @@ __global__ void k_var_zero(double* __restrict__ x, int n) {
 static dim3 var_grid_stencil(const VarGrid& g) {
   return dim3((unsigned)var_blocks_per_level(g.nx, g.ny, kVarStPts), (unsigned)var_level_groups(g.nz));
 }
+static dim3 var_grid_operator(const VarGrid& g) { return dim3((unsigned)var_stencil_parts(g.nx, g.ny, g.nz)); }
 static dim3 var_grid(const VarGrid& g) { return dim3((unsigned)var_blocks_per_level(g.nx, g.ny, kVarPts), (unsigned)g.nz); }
 
 void launch_var_div(const VarGrid& g, const double* u, const double* v, const double* w, double* r, double* p,
@@ -471,10 +509,10 @@ void launch_var_div(const VarGrid& g, const double* u, const double* v, const do
 
 void launch_var_apply(const VarGrid& g, const double* scal, const double* d, double* q, double* part, void* stream) {
   if (g.nx % 2 == 0)
-    hipLaunchKernelGGL(k_var_apply2, var_grid_stencil(g), dim3(kVarBlock), 0, (hipStream_t)stream, g, scal, d, q,
+    hipLaunchKernelGGL(k_var_apply2, var_grid_operator(g), dim3(kVarBlock), 0, (hipStream_t)stream, g, scal, d, q,
                        part);
   else
-    hipLaunchKernelGGL(k_var_apply, var_grid_stencil(g), dim3(kVarBlock), 0, (hipStream_t)stream, g, scal, d, q, part);
+    hipLaunchKernelGGL(k_var_apply, var_grid_operator(g), dim3(kVarBlock), 0, (hipStream_t)stream, g, scal, d, q, part);
 }
 
 // the FP64 preconditioner takes the Fletcher-Reeves update, the FP32 one the

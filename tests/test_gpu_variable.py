@@ -124,6 +124,20 @@ def test_stopped_solve_returns_the_iterate_of_its_residual(shape, dtype, maxit):
     assert abs(_wnorm(res, g.dz) / _wnorm(b, g.dz) - rel) <= 1e-12
 
 
+@pytest.mark.parametrize("shape", [(288, 144, 5), (216, 24, 10), (162, 4, 3), (81, 432, 5), (2, 288, 3)])
+def test_operator_block_order_and_row_ends(shape):
+    """Two iterations over several bands of tiles (a ragged last one, a block count
+    that 64 does not divide), rows that end inside a wave, partial x tiles and
+    one-pair rows: the residual that the operator's recurrence reports is that of
+    the outputs, to their rounding (see the test above)."""
+    g, rho, u, v, w = _case(shape, 1800 + sum(shape))
+    outs, it, rel = _run(g, rho, u, v, w, "f64", maxit=2)
+    assert it == 2
+    b = oracle.divergence_var(u, v, w, g.dx, g.dy, g.dz, rho)
+    res = oracle.divergence_var(*outs[:3], g.dx, g.dy, g.dz, rho)
+    assert abs(_wnorm(res, g.dz) / _wnorm(b, g.dz) - rel) <= 1e-12
+
+
 def test_separable_density_is_one_spectral_solve():
     """rho = rho0(z): the preconditioner is the exact inverse, CG stops after
     one iteration (two at most, from rounding) with monc_project's answer."""

@@ -122,36 +122,63 @@ static int tri_rows(int nz, int P) {
   return 0;
 }
 
-// Waves and rows per wave of the wave-per-chunk tridiagonal kernel, or 0 where
-// the lanes-per-column kernel is the better one. Measured (default tiles, us,
-// lanes-per-column / wave-per-chunk):
-//   above 96 levels the former's default tiles are 8 or 4 columns wide, 64 or
-//   32 bytes of an FP32 level: 128^2 x 128 16.8 / 14.5, 256^2 x 128 31.2 / 23.3,
-//   512^2 x 128 92 / 55, 1024^2 x 256 1161 / 464; but 64^2 x 128 (40 tiles of 64
-//   columns) 10.1 / 12.8: the longer chain of few workgroups. In FP64 (twice
-//   the bytes) only spectra beyond the 256 MB Infinity Cache gain: 512^2 x 128
-//   126 / 118, 512^2 x 256 320 / 245, 256^2 x 128 33.8 / 36.5.
-//   up to 32 levels and over 512 tiles: 256^2 x 16 10.8 / 10.0 (FP32) and 13.3 /
-//   12.0 (FP64), 512^2 x 32 27.4 / 19.3 and 29.2 / 27.9; 192^2 x 32 equal.
-//   between: 256^2 x 64 17.3 / 18.1 and 18.1 / 20.7, 512^2 x 96 41.9 / 43.2; FP32
-//   beyond the Infinity Cache 131 / 109 (1024^2 x 64), FP64 no gain.
-// Rows per wave: the fewest waves (2, 4, 8 or 16) whose rows stay within a
-// limit. More rows mean fewer interface rows and more, smaller workgroups on a
-// CU, whose loads overlap each other's elimination (512^2 x 128 FP32 8 waves of
-// 16 rows 55 us, 16 of 8 75; 1024^2 x 64 4 of 16 109, 8 of 8 116, 16 of 4 196).
-// FP64 storage stops at 14 rows, where its registers spill (1024^2 x 64 FP64 8
-// of 8 196 us, 4 of 16 234; 256^2 x 110 8 of 14 28.8, 16 of 7 34.2).
-static void tricol_shape(int nz, long long tiles, bool fp64, int* waves, int* rows) {
+// Waves and rows per wave of the wave-per-chunk tridiagonal kernel (FP32 storage),
+// or 0 where the lanes-per-column kernel is the better one. Measured (default
+// tiles, us, lanes-per-column / wave-per-chunk):
+//   above 96 levels from about 512^2 columns on: 128^2 x 128 13.3 / 14.0, 256^2 x 128
+//   21.4 / 21.1, 512^2 x 128 54.7 / 53.1, 1024^2 x 100 211 / 160, 1024 x 512 x 128 128 /
+//   104, 512^2 x 256 189 / 126, 1024^2 x 256 686 / 461; but not from 129 to 160, where
+//   sixteen lanes still do and this kernel's sixteen waves have at most 10 rows
+//   each: 512^2 x 160 59.6 / 84.8, 1024^2 x 160 284 / 325, 2048^2 x 160 1240 / 1292.
+//   up to 32 levels over 512 tiles of 64 columns: 256^2 x 16 9.9 / 9.6, 512^2 x 32
+//   21.4 / 17.9, 432^2 x 32 18.7 / 16.3, 1024 x 512 x 16 20.4 / 18.3.
+//   between: 256^2 x 64 17.3 / 18.1, 512^2 x 96 41.9 / 43.2; beyond the 256 MB
+//   Infinity Cache 129 / 110 (1024^2 x 64).
+// Rows per wave: the fewest waves (2, 4, 8 or 16) with at most 16 rows. More rows
+// mean fewer interface rows and more, smaller workgroups on a CU, whose loads
+// overlap each other's elimination (512^2 x 128 8 waves of 16 rows 55 us, 16 of 8
+// 75; 1024^2 x 64 4 of 16 109, 8 of 8 116, 16 of 4 196).
+static void tricol_shape(int nz, long long tiles, int* waves, int* rows) {
   *waves = *rows = 0;
   if (nz > kTriColMax) return;
-  const bool beyond_cache = (double)tiles * 64 * nz * (fp64 ? 16 : 8) > 256.0 * (1 << 20);
-  const bool use = nz > 96 ? (fp64 ? beyond_cache : tiles > 128) : tiles > 512 && (nz <= 32 || (!fp64 && beyond_cache));
+  const bool beyond_cache = (double)tiles * 64 * nz * 8 > 256.0 * (1 << 20);
+  const bool use = nz > 96 ? tiles > 1024 && (nz <= 128 || nz > 160) : nz <= 32 ? tiles > 512 : beyond_cache;
   if (!use) return;
-  const int most = fp64 ? 14 : 16;
   int P = 2;
-  while (P < 16 && (nz + P - 1) / P > most) P *= 2;
+  while (P < 16 && (nz + P - 1) / P > 16) P *= 2;
   *waves = P;
   *rows = std::max(2, (nz + P - 1) / P);
+}
+
+// Default y-FFT columns per workgroup: 128 bytes of a row below length 256. From
+// there on the tile's LDS (columns * ny * cb) sets how many workgroups a CU holds,
+// and four columns pay (whole projection, us, against 128 bytes: FP64 1024^2 x 96
+// 3180 -> 3010, 432^2 x 32 185 -> 173, 256^2 x 128 237 -> 230, 128 x 768 x 32 112 ->
+// 101, equal at 243^2 x 48 and 128^2 x 64, 32^3 25.5 -> 26.8; FP32 256^2 x 128 242 ->
+// 232, 384 x 256 x 96 284 -> 277, 512^2 x 96 676 -> 668, 64^2 x 32 55.3 -> 56.7) until
+// the shorter runs cost the x kernels and the column solve as much: FP32 from
+// length 1024 on keeps eight (1024^2 x 96 -0.5 %, 2048^2 x 160 +0.5 % with four)
+// where these fill the CUs twice (96 x 2048 x 16 does not: 171 -> 157 with four).
+static int y_columns(int nx, int ny, int nz, int cb) {
+  if (ny < 256) return 128 / cb;
+  if (cb == 16 || ny < 1024) return 4;
+  return (long long)nz * ((nx / 2 + 8) / 8) >= 512 ? 8 : 4;
+}
+
+// Default transforms (of nt threads) per workgroup of the x kernels: 256 threads'
+// worth; where that leaves fewer than eight workgroups a CU, the fewest that fill
+// nine tenths of their waves (x kernels' sum, us, 256 threads -> these: 32^3 FP64
+// 15.7 -> 14.6 and mixed 25.5 -> 22.9, 64^2 x 32 mixed 32.8 -> 28.9, 96^2 x 48 FP64
+// 23.9 -> 20.6, 256^2 x 16 mixed 33.8 -> 32.1; equal at 256^2 x 128). A mixed plan
+// whose residual walks whole rows per wave takes whole-wave counts (its workgroups
+// would be rounded up to one: 384 x 256 x 96 63 -> 50 us).
+static int x_transforms(int nx, long long pairs, int nt, bool fp64) {
+  int m = std::max(1, 256 / nt);
+  if (pairs < 2048LL * m)
+    for (int k = 1; k < m; ++k)
+      if (k * nt * 10 >= (k * nt + 63) / 64 * 64 * 9) m = k;
+  const int w = wave_transforms(nt);
+  return !fp64 && xres_wave_rows(nx) && m > w ? m / w * w : m;
 }
 
 // Derive FFT plans and tile parameters from (ex, ey, ymt, triP, tricw, xpw,
@@ -177,25 +204,29 @@ static int configure_tiles(monc_plan* pl, int ex, int ey, int ymt, int triP, int
   if (yept == 32 && (pl->dtype == MONC_FP64 || !pp_supported(pl->ny)))
     return fail(MONC_EINVAL, "32 y-FFT elements per thread (the persistent kernel) need a mixed plan and ny of "
                              "1024, 1536, 2048 or 4096 (got ny=%d)", pl->ny);
-  const int yeff = yept > 0 ? yept : ct_yept_default(pl->ny);
+  const int yeff = yept > 0 ? yept : ct_yept_default(pl->ny, (int)cb / 2);
   // y-FFT columns per workgroup (also the width of the spectral column
-  // blocks, up to 8): 128 bytes of a row by default, bounded by the
-  // workgroup size (1024) and 128 KB of LDS
+  // blocks, up to 8): y_columns by default, bounded by the workgroup size
+  // (1024) and 128 KB of LDS
   const int nty = ct_supported(pl->ny) ? ct_threads_y_host(pl->ny, yeff) : fy.nt;
   if (nty > 1024)
     return fail(MONC_EUNSUPPORTED, "a %d-point y-FFT with %d elements per thread needs more than 1024 threads", pl->ny,
                 yeff);
   const int mt_cap = std::max(1, std::min(1024 / nty, (int)(131072 / (pl->ny * cb))));
-  if (ymt <= 0) ymt = pl->ymt > 0 ? pl->ymt : (int)(128 / cb);
+  if (ymt <= 0) ymt = pl->ymt > 0 ? pl->ymt : y_columns(pl->nx, pl->ny, pl->nz, (int)cb);
   if (ymt > 64) return fail(MONC_EINVAL, "y-FFT columns per workgroup must be <= 64 (got %d)", ymt);
   ymt = std::max(1, std::min(ymt, mt_cap));
   const int nxh = pl->nx / 2 + 1;
   ymt = std::min(ymt, pow2_floor(nxh) * 2);
-  // tridiagonal lanes per column: default = fewest lanes with <= 6 rows each
+  // tridiagonal lanes per column: sixteen (one DPP row, the cheapest exchange)
+  // where that leaves 2 to 10 rows a lane, four up to 16 levels, more lanes above
+  // 160. Against the fewest lanes of at most 6 rows, us (FP64): 32^3 7.7 -> 6.6 and
+  // 128^2 x 40 10.8 -> 9.5 (8 -> 16 lanes), 256^2 x 128 36.5 -> 28.7 (32 -> 16), 128 x
+  // 128 x 256 23.6 -> 20.4 (64 -> 32); but 1024 x 512 x 16 26 with four, 34 with 16.
   if (triP <= 0) triP = pl->triP;
   if (triP <= 0) {
-    triP = 1;
-    while ((pl->nz + triP - 1) / triP > 6 && triP < kTriPmax) triP *= 2;
+    triP = pl->nz <= 4 ? 1 : pl->nz <= 16 ? 4 : 16;
+    while ((pl->nz + triP - 1) / triP > 10 && triP < kTriPmax) triP *= 2;
   }
   if (triP & (triP - 1) || triP > kTriPmax)
     return fail(MONC_EINVAL, "tridiagonal lanes per column must be a power of 2 <= %d (got %d)", kTriPmax, triP);
@@ -203,24 +234,30 @@ static int configure_tiles(monc_plan* pl, int ex, int ey, int ymt, int triP, int
   if (s == 0)
     return fail(MONC_EINVAL, "%d lanes leave %d rows per lane (max %d)", triP, (pl->nz + triP - 1) / triP, kTriSmax);
   // tridiagonal tile: columns per workgroup (0 = automatic: 256 threads, four
-  // waves, so that five workgroups fit a CU at ~100 registers per lane)
+  // waves, so that five workgroups fit a CU at ~100 registers per lane; half
+  // that where it leaves fewer than four workgroups a CU: 128^2 x 128 FP64 16.0
+  // -> 15.4 us, but 1024^2 x 64 FP32 129 -> 185)
   if (tricw <= 0) tricw = pl->tricw;
-  const int cw = tricw > 0 ? tricw : std::max(1, 256 / triP);
+  const int tri_threads = (long long)pl->ny * nxh * triP < 1024 * 256 ? 128 : 256;
+  const int cw = tricw > 0 ? tricw : std::max(1, tri_threads / triP);
   if (cw & (cw - 1) || cw * triP > 512)
     return fail(MONC_EINVAL, "tridiagonal columns per workgroup must be a power of 2 with %d lanes <= 512 threads (got %d)",
                 triP, cw);
-  // x transforms per workgroup of the compile-time x kernels (default: 256
-  // threads); at most 512 threads and 160 KB of LDS
+  // x transforms per workgroup of the compile-time x kernels (default:
+  // x_transforms); at most 512 threads and 160 KB of LDS
   if (xpw <= 0) xpw = pl->xpw;
   int xeff = 1;
   if (ct_supported(pl->nx)) {
-    const int nt = ct_threads_host(pl->nx);
+    const int nt = ct_threads_host(pl->nx, (int)cb / 2), ntr = ct_threads_x_request(pl->nx);
     const size_t per = (size_t)xlds_len(pl->nx, (int)cb) * cb;
-    xeff = xpw > 0 ? xpw : std::max(1, 256 / nt);
+    xeff = xpw > 0 ? xpw : x_transforms(pl->nx, ((long long)pl->ny * pl->nz + 1) / 2, nt, pl->dtype == MONC_FP64);
     // lengths with a radix plan of their own take any request, clamped
     if (ct_plan_index(pl->nx) >= 0)
       xeff = (int)std::min<size_t>(xeff, std::max<size_t>(1, std::min<size_t>(512 / nt, (160 * 1024) / per)));
-    if (xeff * nt > 512 || xeff * per > 160 * 1024)
+    // the others as many as 512 threads of ct_threads_x_request hold, of which a
+    // launch takes what its own 512 threads hold (512 threads of at most sixteen
+    // elements are within the LDS)
+    if (xeff * ntr > 512)
       return fail(MONC_EINVAL, "%d x transforms of %d points per workgroup exceed 512 threads or 160 KB of LDS", xeff,
                   pl->nx);
   }
@@ -246,7 +283,9 @@ static int configure_tiles(monc_plan* pl, int ex, int ey, int ymt, int triP, int
   h.triP = triP;
   h.tris = s;
   h.tricw = cw;
-  tricol_shape(pl->nz, ((long long)pl->ny * h.nxp + 63) / 64, pl->dtype == MONC_FP64, &h.tcwaves, &h.tcrows);
+  h.tcwaves = h.tcrows = 0;
+  if (pl->dtype != MONC_FP64)
+    tricol_shape(pl->nz, ((long long)pl->ny * h.nxp + 63) / 64, &h.tcwaves, &h.tcrows);
   return MONC_OK;
 }
 
@@ -663,8 +702,8 @@ static Shape member_shape(const MemberDesc& d, Phase ph, bool fp64) {
   if (is_xphase(ph)) {
     const long long pairs = (d.nrow + 1) / 2;
     if (ct_supported(d.nx)) {
-      const int nt = ct_threads_host(d.nx);
-      int ipw = d.xpw > 0 ? d.xpw : std::max(1, 256 / nt);
+      const int nt = ct_threads_host(d.nx, (int)cb / 2);
+      int ipw = d.xpw > 0 ? std::min(d.xpw, std::max(1, 512 / nt)) : std::max(1, 256 / nt);
       // the residual kernel at these lengths walks whole rows per wave: its
       // workgroups hold whole waves, the nearest multiple of m transforms
       // (up, unless that passes 512 threads; m nt <= 512, and at most 16
@@ -775,7 +814,7 @@ static int launch_one(const Group& g, const std::vector<int>& idx, Phase ph, con
     case PH_YFWD: launch_ffty(a, grid, block, lds, g.fp64, false, v, g.mem[idx[0]].h->yept, stream); break;
     case PH_YINV: launch_ffty(a, grid, block, lds, g.fp64, true, v, g.mem[idx[0]].h->yept, stream); break;
     case PH_TRI:
-      if (sh.sub == 2) launch_tricol(a, grid, block, lds, g.fp64, v, stream);
+      if (sh.sub == 2) launch_tricol(a, grid, block, lds, v, stream);
       else launch_tridiag(a, grid, block, lds, g.fp64, v, sh.sub != 0, stream); break;
     case PH_XINV: launch_xinv(a, grid, block, lds, g.fp64, 0, v, stream); break;
     case PH_XINV_P1: launch_xinv(a, grid, block, lds, false, 2, v, stream); break;

@@ -540,9 +540,9 @@ __device__ __forceinline__ long long tiled_pair(const MemberDesc& d, long long p
 // loses 6 %.
 template <typename T, int MODE, int N>
 __global__ void __launch_bounds__(512)
-    __attribute__((amdgpu_waves_per_eu(MODE == 1 && ct_threads(N) % 64 != 0 && !xres_wave_rows(N) ? 3 : 1, 8)))
+    __attribute__((amdgpu_waves_per_eu(MODE == 1 && ct_threads(N, sizeof(T)) % 64 != 0 && !xres_wave_rows(N) ? 3 : 1, 8)))
     k_xfwd_ct(LaunchArgs a) {
-  constexpr int NT = ct_threads(N);
+  constexpr int NT = ct_threads(N, sizeof(T));
   using F = CtFft<T, N, NT, false>;
   extern __shared__ unsigned char smem_raw[];
   const Member mb = launch_member(a, blockIdx.x);
@@ -1077,7 +1077,7 @@ __device__ __forceinline__ void store_rows(const MemberDesc& d, const IoPtrs& io
 
 template <typename T, int MODE, int N>
 __global__ void __launch_bounds__(512) k_xinv_ct(LaunchArgs a) {
-  constexpr int NT = ct_threads(N);
+  constexpr int NT = ct_threads(N, sizeof(T));
   using F = CtFft<T, N, NT, true>;
   extern __shared__ unsigned char smem_raw[];
   const Member mb = launch_member(a, blockIdx.x);

@@ -40,7 +40,7 @@ bool ct_supported(int n);
 MONC_FFT_GROUPS(MONC_GROUP_DECL)
 // lengths with the persistent FP32 y-FFT kernel (32 elements per thread)
 bool pp_supported(int n);
-inline int ct_threads_host(int n) { return ct_threads_x_n(n); }
+inline int ct_threads_host(int n, int eb) { return ct_threads_x_n(n, eb); }
 inline int ct_threads_y_host(int n, int ept) { return ct_threads_y_n(n, ept); }
 
 // ct_n: the compile-time length, or 0 for the runtime-length kernel.
@@ -58,7 +58,7 @@ void launch_ffty(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64
 void launch_tridiag(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int rows, bool pairs, void* stream);
 // the wave-per-chunk kernel (up to kTriColMax levels): rows per wave (the
 // member's tcrows), block = 64 times the member's tcwaves
-void launch_tricol(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int rows, void* stream);
+void launch_tricol(const LaunchArgs& a, int grid, int block, size_t lds, int rows, void* stream);
 // the result goes to io.p (mode 0), io.s1 (mode 1, float only: the
 // correction delta) or io.s2 (mode 2, float only: the first-pass pressure);
 // mode 3 (one member): io.p, with one partial sum per workgroup of dz io.u io.p

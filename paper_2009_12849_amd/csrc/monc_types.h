@@ -97,7 +97,22 @@ constexpr int ct_plan_index(int n) {  // its place in kCtPlans, or -1
     if (kCtPlans[i].n == n) return i;
   return -1;
 }
-constexpr int ct_threads_x_n(int n) {
+//
+// Along x, in storage type of eb bytes: eight elements a thread (radix-8 passes),
+// sixteen (radix-16 passes, one exchange through LDS fewer) from length 768 on in
+// FP32 and from 2049 on in FP64, whose transforms (16 bytes a value, 160 KB a CU)
+// leave room for ten waves of sixteen-element threads but twenty of eight-element
+// ones. The x kernels of a pass, sixteen -> eight elements a thread, us:
+// FP64 512^2 x 96 291 -> 259, 768^2 x 64 452 -> 386, 1024^2 x 96 1033 -> 1005,
+// 1536 x 768 x 64 839 -> 772, 2048^2 x 40 1832 -> 1782, but 4096 x 1024 x 32 1443 ->
+// 1469; FP32 512^2 x 96 292 -> 285, 768^2 x 64 488 -> 442, but 1024^2 x 96 1124 ->
+// 1208, 1536 x 768 x 64 921 -> 939.
+constexpr int ct_threads_x_n(int n, int eb) {
+  const int i = ct_plan_index(n);
+  return i >= 0 ? kCtPlans[i].nt : n > (eb == 8 ? 2048 : 768) ? n / 16 : (n >= 8 ? n / 8 : 1);
+}
+// threads a transform that the acceptance of a requested x tile counts
+constexpr int ct_threads_x_request(int n) {
   const int i = ct_plan_index(n);
   return i >= 0 ? kCtPlans[i].nt : n >= 512 ? n / 16 : (n >= 8 ? n / 8 : 1);
 }
@@ -109,20 +124,24 @@ constexpr int wave_transforms(int nt) {
 }
 // The residual's stencil phase at lengths whose transforms do not fill whole
 // waves, are a multiple of 64 points and fit whole waves in 512 threads (64,
-// 128, 192, 256, 384, 512, 768, 1536) walks whole rows per wave (64 lanes x
+// 128, 192, 256, 384, 768, 1536) walks whole rows per wave (64 lanes x
 // xres_chunk points: 4 where the length allows, else 2, else 1), so that each
 // wave handles one transform's rows at a time and its row contexts are
 // wave-uniform; its workgroups then hold whole waves.
 constexpr bool xres_wave_rows(int n) {
-  return ct_threads_x_n(n) % 64 != 0 && n % 64 == 0 && wave_transforms(ct_threads_x_n(n)) * ct_threads_x_n(n) <= 512;
+  const int nt = ct_threads_x_n(n, 4);
+  return nt % 64 != 0 && n % 64 == 0 && wave_transforms(nt) * nt <= 512;
 }
 constexpr int xres_chunk(int n) { return n % 256 == 0 ? 4 : (n % 128 == 0 ? 2 : 1); }
 // Points a lane takes at once of a row of n points in storage type of eb
 // bytes: 16 bytes' worth where the row divides by it, else fewer.
 constexpr int x_chunk(int n, int eb) { return n % (16 / eb) == 0 ? 16 / eb : n % 2 == 0 && eb == 4 ? 2 : 1; }
 // Along y the elements per thread (8: radix-8 passes, 16: radix-16 passes)
-// are a tile parameter: default sixteen from length 2048 on, eight below.
-constexpr int ct_yept_default(int n) { return n >= 2048 ? 16 : 8; }
+// are a tile parameter: default sixteen from length 2048 on in FP64, from 256 on
+// in FP32 (eight -> sixteen, four columns a tile, whole projection: 256^2 x 128 233.7
+// -> 231.8 us, 512^2 x 96 673 -> 668, 1024^2 x 96 2845 -> 2781; FP64 512^2 x 96 684 ->
+// 703, 2048^2 x 160 20845 -> 20454), eight below.
+constexpr int ct_yept_default(int n, int eb) { return n >= (eb == 8 ? 2048 : 256) ? 16 : 8; }
 constexpr int ct_threads_y_n(int n, int ept) {
   const int i = ct_plan_index(n);
   return i >= 0 ? kCtPlans[i].nt : n >= ept ? n / ept : 1;
@@ -144,7 +163,7 @@ constexpr int kXswBits64 = 4;    // FP64 complex (16 B): 16 values per bank row
 constexpr int kXpadShift32 = 4;
 constexpr int kXpadShift64 = 3;
 constexpr int xsw_bits(int cb) { return cb == 16 ? kXswBits64 : kXswBits32; }
-constexpr bool xsw_on(int n, int cb) { return ct_threads_x_n(n) * 16 == n && n % (1 << xsw_bits(cb)) == 0; }
+constexpr bool xsw_on(int n, int cb) { return ct_threads_x_n(n, cb / 2) * 16 == n && n % (1 << xsw_bits(cb)) == 0; }
 // LDS slots of one x transform of length n (complex values of cb bytes)
 constexpr int xlds_len(int n, int cb) {
   return xsw_on(n, cb) ? n : n + (n >> (cb == 16 ? kXpadShift64 : kXpadShift32)) + 1;

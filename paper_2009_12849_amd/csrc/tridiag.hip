@@ -506,12 +506,12 @@ k_tridiag(LaunchArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// FP64 tridiagonal solve, a wave per row chunk (the grids tricol_shape picks,
-// at most kTriColMax levels). The same partition method as above, mapped the other way round: a
-// workgroup takes 64 consecutive entries of the level plane, lane c of every
-// wave holds column c, and wave q eliminates rows q S .. q S + S-1. Every load
-// and store is then a run of 64 columns of one level (512 bytes FP32, 1 KB
-// FP64) straight between memory and registers, the rows' coefficients are
+// FP64 tridiagonal solve over FP32 storage, a wave per row chunk (the grids
+// tricol_shape picks, at most kTriColMax levels). The same partition method as
+// above, mapped the other way round: a workgroup takes 64 consecutive entries of
+// the level plane, lane c of every wave holds column c, and wave q eliminates rows
+// q S .. q S + S-1. Every load and store is then a run of 64 columns of one level
+// (512 bytes) straight between memory and registers, the rows' coefficients are
 // wave-uniform (scalar loads and operands), and only the interface system
 // crosses waves, through LDS. Registers: a row keeps 1/pivot and its
 // right-hand side (6 registers) between the elimination and the back
@@ -519,31 +519,17 @@ k_tridiag(LaunchArgs a) {
 // them.
 //
 // Bound by the access pattern: with the elimination left out (a copy of the
-// kernel that loads and stores its tiles) it takes 1.15 of 1.32 ms (FP32
-// storage) and 2.26 of 2.27 ms (FP64) at 2048^2 x 160, 4.7-4.8 TB/s over nz
-// runs a level apart against 6.5 TB/s of one contiguous copy. Before, with the
-// lanes-per-column kernel at its default lanes and tiles: 1.95 and 2.41 ms;
-// 1024^2 x 256 FP32 1.16 -> 0.46 ms. The interface rows are eliminated by two waves from both ends: parallel cyclic
+// kernel that loads and stores its tiles) it takes 1.15 of 1.32 ms at 2048^2 x
+// 160, 4.7 TB/s over nz runs a level apart against 6.5 TB/s of one contiguous
+// copy. Against the lanes-per-column kernel, us: 1024^2 x 256 1161 -> 461 (32
+// lanes 686), 1024^2 x 100 211 -> 160, 512^2 x 256 189 -> 126. FP64 storage, whose
+// runs are twice as long in either kernel, was no faster this way (2048^2 x 160
+// 2166 against 2274 us, 1024^2 x 256 907 / 924, 512^2 x 128 108 / 118).
+// The interface rows are eliminated by two waves from both ends: parallel cyclic
 // reduction on all waves took as long as the chunk elimination itself (1.42 ms
 // at 2048^2 x 160), and loading the next tile during the solve (a persistent
 // workgroup) gained 1 % there and lost up to 25 % at 384 x 256 x 96.
 // ---------------------------------------------------------------------------
-// sum over the waves of a workgroup of each lane's value (red: one row of 64
-// per wave); every thread must call it
-__device__ __forceinline__ double2 wave_rows_sum(double2 v, double2* red, int P) {
-  __syncthreads();
-  red[threadIdx.x] = v;
-  __syncthreads();
-  double2 s = make_double2(0.0, 0.0);
-  for (int w = 0; w < P; ++w) {
-    const double2 x = red[w * 64 + (threadIdx.x & 63)];
-    s.x += x.x;
-    s.y += x.y;
-  }
-  __syncthreads();
-  return s;
-}
-
 // The (0,0) column, one wave: with no horizontal part the rows telescope.
 // c_k dz_k (P_{k+1} - P_k) = sum_{j <= k} dz_j (B_j - mean) is the flux through
 // the top of level k (a_{k+1} dz_{k+1} = c_k dz_k), so P is a running sum of
@@ -563,10 +549,9 @@ __device__ __forceinline__ double2 wave_scan(double2 v) {  // inclusive
   return v;
 }
 
-template <typename TS>
-__device__ __forceinline__ void tri_mean_column(cx<TS>* S, int nz, long long plane, const double* dz, const double* trc,
+__device__ __forceinline__ void tri_mean_column(cx<float>* S, int nz, long long plane, const double* dz, const double* trc,
                                                 double rH, double sc) {
-  using CS = cx<TS>;
+  using CS = cx<float>;
   const int k0 = 4 * (threadIdx.x & 63);
   double2 v[4];
   double w[4];
@@ -615,7 +600,7 @@ __device__ __forceinline__ void tri_mean_column(cx<TS>* S, int nz, long long pla
   const double gx = __shfl(s.x, 63) * rH, gy = __shfl(s.y, 63) * rH;
 #pragma unroll
   for (int r = 0; r < 4; ++r)
-    if (k0 + r < nz) S[(long long)(k0 + r) * plane] = CS{(TS)((v[r].x - gx) * sc), (TS)((v[r].y - gy) * sc)};
+    if (k0 + r < nz) S[(long long)(k0 + r) * plane] = CS{(float)((v[r].x - gx) * sc), (float)((v[r].y - gy) * sc)};
 }
 
 // A wave-uniform index whose value the compiler cannot trace: coefficients
@@ -691,12 +676,11 @@ __device__ __forceinline__ void tri_interface_back(const double* Ib, double* Fb,
   }
 }
 
-template <typename TS, int S>
+template <int S>
 __global__ void __launch_bounds__(1024) k_tricol(LaunchArgs a) {
   extern __shared__ double smem[];
-  constexpr bool F32 = sizeof(TS) == 4;
-  using CS = cx<TS>;
-  typedef TS cv __attribute__((ext_vector_type(2)));
+  using CS = cx<float>;
+  typedef float cv __attribute__((ext_vector_type(2)));
   const int P = blockDim.x >> 6;                 // waves = row chunks
   const int q = wuni((int)(threadIdx.x >> 6)), c = threadIdx.x & 63;
   const Member mb = launch_member(a, blockIdx.x);
@@ -716,7 +700,7 @@ __global__ void __launch_bounds__(1024) k_tricol(LaunchArgs a) {
   // (m >= nxh) solve a dummy system with a zero right-hand side here and are
   // not stored
   const bool valid = col > 0 && col < ncolp && m < d.nxh;
-  if (lb == 0 && q == 0) tri_mean_column<TS>(S0, nz, plane, d.dz, d.trc, d.rH, d.inv_nxny);  // no barrier inside
+  if (lb == 0 && q == 0) tri_mean_column(S0, nz, plane, d.dz, d.trc, d.rH, d.inv_nxny);  // no barrier inside
 
   // rows q S .. q S + S-1 of the lane's column: entries past the plane read
   // the tile's first, rows past nz the last level
@@ -741,31 +725,6 @@ __global__ void __launch_bounds__(1024) k_tricol(LaunchArgs a) {
   double* Ib = smem;                               // [5][P][64] interface rows
   double* Lb = smem + 5 * VS;                      // [4][P][64] last rows of the chunks
   double* Fb = smem + 9 * VS;                      // [2][P][64] interface solution
-  // deflation of the near-null direction (FP64 storage), as in tri_tile: the
-  // columns are the same in every wave, so the branch is uniform over the
-  // workgroup
-  double2 cdef = make_double2(0.0, 0.0);
-  if constexpr (!F32) {
-    if (__any(lam < d.lamdef)) {
-      double2 sb = make_double2(0.0, 0.0);
-#pragma unroll
-      for (int r = 0; r < S; ++r) {
-        const double dzr = k0 + r < nz ? ldc(d.dz + min(k0 + r, nz - 1)) : 0.0;
-        sb.x += dzr * D[r].x;
-        sb.y += dzr * D[r].y;
-      }
-      sb = wave_rows_sum(sb, reinterpret_cast<double2*>(smem), P);
-      const double gx = sb.x * d.rSr, gy = sb.y * d.rSr;
-#pragma unroll
-      for (int r = 0; r < S; ++r) {
-        const double r0 = ldc(tr + k0 + r);
-        D[r].x -= r0 * gx;
-        D[r].y -= r0 * gy;
-      }
-      const double il = 1.0 / lam;
-      cdef = make_double2(-gx * il, -gy * il);
-    }
-  }
 
   // 1. chunk elimination, x_r + al_r x_0 + ga_r x_{r+1} = de_r (de in D), and
   //    the same sums run forward for x_1 = e1 - f1 x_0 + g1 x_{S-1}
@@ -850,8 +809,8 @@ __global__ void __launch_bounds__(1024) k_tricol(LaunchArgs a) {
     for (int r = 0; r < S; ++r)
       if (k0 + r < nz) {
         cv v;
-        v.x = (TS)((D[r].x + cdef.x) * sc);  // cdef: the deflated constant (0 with FP32 storage)
-        v.y = (TS)((D[r].y + cdef.y) * sc);
+        v.x = (float)(D[r].x * sc);
+        v.y = (float)(D[r].y * sc);
         ((__attribute__((address_space(1))) cv*)(S0 + (long long)(k0 + r) * plane))[c] = v;
       }
   }
@@ -877,9 +836,7 @@ void init_tridiag_attributes() {
   }
   MONC_TRI_ROWS(MONC_TRI_ATTR)
 #undef MONC_TRI_ATTR
-#define MONC_TRICOL_ATTR(S)            \
-  set_lds_limit(k_tricol<double, S>);  \
-  set_lds_limit(k_tricol<float, S>);
+#define MONC_TRICOL_ATTR(S) set_lds_limit(k_tricol<S>);
   MONC_TRICOL_ROWS(MONC_TRICOL_ATTR)
 #undef MONC_TRICOL_ATTR
 }
@@ -914,12 +871,11 @@ void launch_tridiag(const LaunchArgs& a, int grid, int block, size_t lds, bool f
   }
 }
 
-void launch_tricol(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int rows, void* stream) {
+void launch_tricol(const LaunchArgs& a, int grid, int block, size_t lds, int rows, void* stream) {
   switch (rows) {
-#define MONC_CASE(S)                               \
-  case S:                                          \
-    if (fp64) MONC_GO((k_tricol<double, S>));      \
-    else MONC_GO((k_tricol<float, S>));            \
+#define MONC_CASE(S)         \
+  case S:                    \
+    MONC_GO((k_tricol<S>));  \
     return;
     MONC_TRICOL_ROWS(MONC_CASE)
 #undef MONC_CASE

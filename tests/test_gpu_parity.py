@@ -194,6 +194,40 @@ def test_planned_lengths(n):
         assert max(errs) <= TOL_MIXED, (shape, errs)
 
 
+@pytest.mark.parametrize("n", [256, 512, 768, 1024, 1536, 2048, 4096])
+def test_elements_per_thread(n):
+    # lengths on both sides of the lines between eight and sixteen elements a
+    # thread (x: FP64 2048, FP32 768; y by default: FP64 2048, FP32 256) and of the
+    # default y tile's width; the x tile takes every request up to 512 threads of
+    # sixteen elements (eight below length 512) and refuses the next one
+    rng = np.random.default_rng(n + 1)
+    most = 512 * (16 if n >= 512 else 8) // n
+    for shape in ((n, 3, 3), (n, 12, 2), (6, n, 3), (48, n, 2)):
+        g = synth.Grid(*shape, 50.0, 40.0, 1000.0 * rng.uniform(0.8, 1.2, shape[2]), rng.uniform(0.5, 1.5, shape[2]))
+        u, v, w = synth.random_fields(rng, g)
+        check_fp64(g, u, v, w)
+        errs, out, ref = mixed_case(g, u, v, w)
+        assert max(errs) <= TOL_MIXED, (shape, errs)
+        if shape[0] != n:
+            continue
+        for dtype in ("f64", "mixed"):
+            plan = monc.Plan.from_grid(g, dtype)
+            outs = []
+            for xpw in {1, max(1, most // 2), most}:
+                plan.params = [0, 0, 0, 0, 0, xpw, 0]
+                assert plan.params[5] == xpw
+                f = [to_dev(x, plan.torch_dtype) for x in (u, v, w)]
+                f.append(torch.empty_like(f[0]))
+                plan.project(*f)
+                torch.cuda.synchronize()
+                outs.append([x.cpu().numpy() for x in f])
+            for o in outs[1:]:  # a transform's arithmetic does not depend on the grouping
+                assert all(np.array_equal(a, b) for a, b in zip(outs[0], o))
+            with pytest.raises(monc.MoncError):
+                plan.params = [0, 0, 0, 0, 0, most + 1, 0]
+            plan.close()
+
+
 @pytest.mark.parametrize("shape", [(8192, 2, 3), (2, 8192, 2), (6561, 3, 2), (4, 6561, 3)])
 @pytest.mark.parametrize("dtype", ["f64", "mixed"])
 def test_size_limits(shape, dtype):
@@ -629,8 +663,10 @@ def test_mixed_tridiagonal_tiles_give_identical_bits(nz, lanes):
 # at 183 tiles of 64 columns (128 x 162: 11664 entries, the last tile ragged),
 # 122 tiles (128 x 108) and 517 (256 x 243: 33048 entries); rows per wave from 2
 # to 16 on 2 to 16 waves
+# (1280 and 1536 tiles, 32 x 4096, for the levels above 96)
 @pytest.mark.parametrize("shape", [(128, 162, n) for n in (96, 97, 112, 113, 129, 160, 161, 241, 256, 257)]
-                         + [(128, 108, 97)] + [(256, 243, n) for n in (1, 2, 3, 5, 28, 29, 31, 32, 33)])
+                         + [(128, 108, 97)] + [(256, 243, n) for n in (1, 2, 3, 5, 28, 29, 31, 32, 33)]
+                         + [(32, 4096, n) for n in (97, 128, 161)])
 @pytest.mark.parametrize("dtype", ["f64", "mixed"])
 def test_column_solve_row_chunks(shape, dtype):
     g, u, v, w = _case(shape, 37)

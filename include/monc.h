@@ -269,7 +269,9 @@ const char* monc_kernel_name(int kernel_id);
 /* Per-kernel timing with HIP events recorded on the launch stream around
  * every launch of the kernels in `mask` (bit i = kernel id i); 0 disables.
  * Applies to monc_project/monc_project_batched calls on this plan (for a
- * batch, the first member's plan controls it). */
+ * batch, the first member's plan controls it). While enabled, a small plan's
+ * x and y transforms, otherwise one launch per direction, are launched by
+ * themselves (the results are the same to the bit). */
 int monc_profile_enable(monc_plan* plan, unsigned mask);
 /* Wait for the recorded events, add their durations per kernel into
  * ms[MONC_K_COUNT] and launches[MONC_K_COUNT], and clear the record. */

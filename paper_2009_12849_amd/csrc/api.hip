@@ -647,17 +647,19 @@ struct Group {
 
 enum Phase {
   PH_XFWD, PH_XPRE, PH_XPRE_UPDATE, PH_RESID, PH_YFWD, PH_TRI, PH_YINV, PH_XINV, PH_XINV_P1, PH_XINV_CORR,
-  PH_XINV_DOTS, PH_GRAD, PH_GRAD_MIXED
+  PH_XINV_DOTS, PH_GRAD, PH_GRAD_MIXED,
+  PH_LEVEL_FWD, PH_LEVEL_RESID, PH_LEVEL_INV, PH_LEVEL_INV_P1, PH_LEVEL_INV_CORR
 };
 
 static int phase_kernel_id(Phase ph) {
   switch (ph) {
-    case PH_XFWD: case PH_XPRE: case PH_XPRE_UPDATE: return MONC_K_DIV_FFTX;
-    case PH_RESID: return MONC_K_RESID_FFTX;
+    case PH_XFWD: case PH_XPRE: case PH_XPRE_UPDATE: case PH_LEVEL_FWD: return MONC_K_DIV_FFTX;
+    case PH_RESID: case PH_LEVEL_RESID: return MONC_K_RESID_FFTX;
     case PH_YFWD: return MONC_K_FFTY_FWD;
     case PH_TRI: return MONC_K_TRIDIAG;
     case PH_YINV: return MONC_K_FFTY_INV;
     case PH_XINV: case PH_XINV_P1: case PH_XINV_CORR: case PH_XINV_DOTS: return MONC_K_IFFTX;
+    case PH_LEVEL_INV: case PH_LEVEL_INV_P1: case PH_LEVEL_INV_CORR: return MONC_K_IFFTX;
     case PH_GRAD: return MONC_K_GRAD;
     case PH_GRAD_MIXED: return MONC_K_GRAD_FINAL;
   }
@@ -669,6 +671,7 @@ static bool is_xphase(Phase ph) {
          ph == PH_XINV_P1 || ph == PH_XINV_CORR || ph == PH_XINV_DOTS;
 }
 static bool is_yphase(Phase ph) { return ph == PH_YFWD || ph == PH_YINV; }
+static bool is_level_phase(Phase ph) { return ph >= PH_LEVEL_FWD; }
 
 // Launch shape of one member in one phase. Members whose shapes agree share
 // a launch; `variant` identifies the kernel instance (compile-time length or
@@ -699,7 +702,17 @@ static int cu_count() {
 static Shape member_shape(const MemberDesc& d, Phase ph, bool fp64) {
   const size_t cb = fp64 ? 16 : 8;
   Shape s;
-  if (is_xphase(ph)) {
+  if (is_level_phase(ph)) {
+    const int ntx = ct_threads_host(d.nx, (int)cb / 2), nty = ct_threads_y_host(d.ny, 8);
+    s.variant = 1;
+    const int threads = std::max(d.ny / 2 * ntx, d.nxh * nty), rounds = (threads + 511) / 512;
+    s.block = ((threads + rounds - 1) / rounds + 63) / 64 * 64;
+    // whole transforms and a partial one that fills the workgroup
+    const size_t x = (size_t)((s.block + ntx - 1) / ntx) * xlds_len(d.nx, (int)cb);
+    const size_t y = (size_t)((s.block + nty - 1) / nty) * d.ny;
+    s.lds = std::max(x, y) * cb;
+    s.blocks = d.nz;
+  } else if (is_xphase(ph)) {
     const long long pairs = (d.nrow + 1) / 2;
     if (ct_supported(d.nx)) {
       const int nt = ct_threads_host(d.nx, (int)cb / 2);
@@ -817,6 +830,11 @@ static int launch_one(const Group& g, const std::vector<int>& idx, Phase ph, con
       if (sh.sub == 2) launch_tricol(a, grid, block, lds, v, stream);
       else launch_tridiag(a, grid, block, lds, g.fp64, v, sh.sub != 0, stream); break;
     case PH_XINV: launch_xinv(a, grid, block, lds, g.fp64, 0, v, stream); break;
+    case PH_LEVEL_FWD: launch_level_fwd(a, grid, block, lds, g.fp64, 0, stream); break;
+    case PH_LEVEL_RESID: launch_level_fwd(a, grid, block, lds, false, 1, stream); break;
+    case PH_LEVEL_INV: launch_level_inv(a, grid, block, lds, g.fp64, 0, stream); break;
+    case PH_LEVEL_INV_P1: launch_level_inv(a, grid, block, lds, false, 2, stream); break;
+    case PH_LEVEL_INV_CORR: launch_level_inv(a, grid, block, lds, false, 1, stream); break;
     case PH_XINV_P1: launch_xinv(a, grid, block, lds, false, 2, v, stream); break;
     case PH_XINV_DOTS: launch_xinv(a, grid, block, lds, g.fp64, 3, v, stream); break;
     case PH_XINV_CORR: launch_xinv(a, grid, block, lds, false, 1, v, stream); break;
@@ -890,6 +908,30 @@ static const std::vector<Phase>& full_sequence(bool fp64) {
   return fp64 ? f64 : mixed;
 }
 
+// Whether one workgroup a level does both transforms of a plan (k_level_fwd,
+// k_level_inv): FP32 up to 64 x 64 points, FP64 up to 1536 points a level, where
+// the launches that it saves outweigh the CUs that it leaves idle. GPU time of a
+// projection, us, separate / level kernels: mixed 16^3 36.5 / 32.0, 32^3 36.5 / 32.8,
+// 48^3 44.6 / 41.5, 64^2 x 32 46.4 / 39.8, 64^2 x 256 82.8 / 65.7, but 72^2 x 32 47.5 /
+// 50.8, 96^2 x 48 57 / 87; FP64 16^3 22.0 / 19.2, 32^3 22.0 / 20.7, 24 x 48 x 32 26.4 /
+// 25.8, 32^2 x 512 40.6 / 37.6, but 54 x 36 x 20 24.6 / 29.1, 48^3 28.5 / 30.3, 64^2 x
+// 32 23.8 / 27.2.
+static bool level_fused(const MemberDesc& d, bool fp64) {
+  return d.ny % 2 == 0 && level_length(d.nx, false) && level_length(d.ny, true) &&
+         (!fp64 || d.nx * d.ny <= 1536) && (ct_plan_index(d.ny) >= 0 || d.yept == 8);
+}
+
+// The launches of one plan's projection: with the level kernels where these are
+// the better ones, but each kernel by itself while its times are recorded (the
+// results' bits are the same).
+static const std::vector<Phase>& plan_sequence(const MemberDesc& d, bool fp64, const Profiler* prof) {
+  static const std::vector<Phase> f64 = {PH_LEVEL_FWD, PH_TRI, PH_LEVEL_INV, PH_GRAD};
+  static const std::vector<Phase> mixed = {PH_LEVEL_FWD, PH_TRI,            PH_LEVEL_INV_P1, PH_LEVEL_RESID,
+                                           PH_TRI,       PH_LEVEL_INV_CORR, PH_GRAD_MIXED};
+  if (prof || !level_fused(d, fp64)) return full_sequence(fp64);
+  return fp64 ? f64 : mixed;
+}
+
 // The launch pointers of one member: caller fields, the plan's spectral
 // workspace and (mixed plans) its two scratch fields.
 static IoPtrs plan_io(const monc_plan* pl, void* u, void* v, void* w, void* p) {
@@ -944,7 +986,8 @@ extern "C" int monc_project(monc_plan* pl, void* u, void* v, void* w, void* p, v
   g.fp64 = pl->dtype == MONC_FP64;
   g.mem.push_back({&pl->h, pl->d_desc, plan_io(pl, u, v, w, p)});
   std::vector<Group> groups{g};
-  return run_phases(groups, full_sequence(g.fp64), stream, pl->prof.mask ? &pl->prof : nullptr);
+  Profiler* const prof = pl->prof.mask ? &pl->prof : nullptr;
+  return run_phases(groups, plan_sequence(pl->h, g.fp64, prof), stream, prof);
 }
 
 extern "C" int monc_project_reduce(monc_plan* pl, void* u, void* v, void* w, void* p, double* stats,
@@ -970,7 +1013,8 @@ extern "C" int monc_project_reduce(monc_plan* pl, void* u, void* v, void* w, voi
   io.stats = stats;
   g.mem.push_back({&pl->h, pl->d_desc, io});
   std::vector<Group> groups{g};
-  return run_phases(groups, full_sequence(g.fp64), stream, pl->prof.mask ? &pl->prof : nullptr);
+  Profiler* const prof = pl->prof.mask ? &pl->prof : nullptr;
+  return run_phases(groups, plan_sequence(pl->h, g.fp64, prof), stream, prof);
 }
 
 // ---------------------------------------------------------------------------
@@ -1007,7 +1051,7 @@ extern "C" int monc_project_noalloc(monc_plan* pl, void* u, void* v, void* w, vo
   g.fp64 = fp64;
   g.mem.push_back({&pl->h, pl->d_desc, io});
   std::vector<Group> groups{g};
-  return run_phases(groups, full_sequence(fp64), stream, nullptr);  // no profiling events
+  return run_phases(groups, plan_sequence(pl->h, fp64, nullptr), stream, nullptr);  // no profiling events
 }
 
 // ---------------------------------------------------------------------------

@@ -530,45 +530,27 @@ __device__ __forceinline__ long long tiled_pair(const MemberDesc& d, long long p
 // threads per transform; blockDim =
 // transforms per workgroup * NT)
 // ---------------------------------------------------------------------------
-// The residual variant at lengths whose transforms share a wave and whose
-// stencil does not walk whole rows per wave (lengths that are not a multiple
-// of 64, such as 16-48, 96, 144, 288, or whose whole-wave workgroups would
-// pass 512 threads: 576, 1152, 2304) keeps its row contexts in vector
-// registers: about 172 registers, 2 waves per SIMD. A budget for 3 spills 2-6
-// registers and measured about 1 % faster where it applied before the
-// whole-row stencil; a budget for 5 waves at the longer lengths spills 16 and
-// loses 6 %.
-template <typename T, int MODE, int N>
-__global__ void __launch_bounds__(512)
-    __attribute__((amdgpu_waves_per_eu(MODE == 1 && ct_threads(N, sizeof(T)) % 64 != 0 && !xres_wave_rows(N) ? 3 : 1, 8)))
-    k_xfwd_ct(LaunchArgs a) {
+// The transform of the row pair `pair` by the NT threads q of instance inst
+// (ipw in the workgroup lb): stencil, FFT, half spectrum into the spectral
+// buffer. Returns the thread's part of MODE 3's sum. LEVEL: a pair of the
+// workgroup's level (k_level_fwd); in = false only takes part in the barriers.
+// (The descriptor by value, here and below: by reference the compiler orders the
+// loads otherwise and the FP64 kernels measure 3-6 % slower.)
+template <typename T, int MODE, int N, bool LEVEL>
+__device__ __forceinline__ double xfwd_pair(MemberDesc d, IoPtrs io, int lb, int ipw, int inst, int q,
+                                            long long pair, bool in) {
+  extern __shared__ unsigned char smem_raw[];
   constexpr int NT = ct_threads(N, sizeof(T));
   using F = CtFft<T, N, NT, false>;
-  extern __shared__ unsigned char smem_raw[];
-  const Member mb = launch_member(a, blockIdx.x);
-  const MemberDesc d = load_desc(mb.desc);
-  keep_x(d);
-  if (skipped(d)) return;
-  const IoPtrs& io = mb.io;
-  // workgroups in launch order for the residual (1-7 % faster than grouped
-  // by XCD: 2048^2 x 160, 1024^2 x 256, 4096^2 x 64 and the ensemble), by XCD
-  // for the divergence (FP32 2 % faster that way at 2048^2 x 160; FP64 4 %
-  // slower there but 7 % faster at 4096^2 x 64) and the given-field mode
-  constexpr bool PLAIN = MODE == 1;
-  const int lb = PLAIN ? (int)blockIdx.x - mb.start : xcd_local_block(mb);
-  const int ipw = blockDim.x / NT;
   // scalar row contexts for the residual only, and only where a transform
   // spans whole waves (NT a multiple of 64: then no wave holds lanes of two
   // transforms): its registers fall from 174 to 126 and its occupancy rises
   // from 2 to 4 waves per SIMD, and it gains; the divergence variants measure
   // slower with scalar contexts
   constexpr bool UNI = NT % 64 == 0 && MODE == 1;
-  const int inst = UNI ? wuni((int)(threadIdx.x / NT)) : (int)(threadIdx.x / NT);
-  const int q = threadIdx.x - inst * NT;
   cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw) + inst * xlds_len(N, 2 * sizeof(T));
-  const long long pair = tiled_pair(d, (long long)lb * ipw + inst);
   const long long r0 = 2 * pair, r1 = 2 * pair + 1;
-  const bool v0 = r0 < d.nrow, v1 = r1 < d.nrow;
+  const bool v0 = in && r0 < d.nrow, v1 = in && r1 < d.nrow;
   RowCtx c0 = make_row(d, r0, v0), c1 = make_row(d, r1, v1);
   if constexpr (UNI) {
     c0 = wuni(c0);
@@ -624,7 +606,7 @@ __global__ void __launch_bounds__(512)
 #pragma unroll
     for (int e = 0; e < V; ++e) L[xpad<T, N>(i0 + e)] = cx<T>{s0[e], s1[e]};
   };
-  if constexpr (MODE == 1 && xres_wave_rows(N)) {
+  if constexpr (MODE == 1 && !LEVEL && xres_wave_rows(N)) {
     // residual with transforms narrower than a wave: each wave takes one
     // transform's run of 64 chunks of W points at a time (the host launches
     // whole waves), so the row contexts are wave-uniform, in scalar
@@ -721,6 +703,40 @@ __global__ void __launch_bounds__(512)
       }
     }
   }
+  return rr;
+}
+
+// The residual variant at lengths whose transforms share a wave and whose
+// stencil does not walk whole rows per wave (lengths that are not a multiple
+// of 64, such as 16-48, 96, 144, 288, or whose whole-wave workgroups would
+// pass 512 threads: 576, 1152, 2304) keeps its row contexts in vector
+// registers: about 172 registers, 2 waves per SIMD. A budget for 3 spills 2-6
+// registers and measured about 1 % faster where it applied before the
+// whole-row stencil; a budget for 5 waves at the longer lengths spills 16 and
+// loses 6 %.
+template <typename T, int MODE, int N>
+__global__ void __launch_bounds__(512)
+    __attribute__((amdgpu_waves_per_eu(MODE == 1 && ct_threads(N, sizeof(T)) % 64 != 0 && !xres_wave_rows(N) ? 3 : 1, 8)))
+    k_xfwd_ct(LaunchArgs a) {
+  constexpr int NT = ct_threads(N, sizeof(T));
+  extern __shared__ unsigned char smem_raw[];
+  const Member mb = launch_member(a, blockIdx.x);
+  const MemberDesc d = load_desc(mb.desc);
+  keep_x(d);
+  if (skipped(d)) return;
+  const IoPtrs& io = mb.io;
+  // workgroups in launch order for the residual (1-7 % faster than grouped
+  // by XCD: 2048^2 x 160, 1024^2 x 256, 4096^2 x 64 and the ensemble), by XCD
+  // for the divergence (FP32 2 % faster that way at 2048^2 x 160; FP64 4 %
+  // slower there but 7 % faster at 4096^2 x 64) and the given-field mode
+  constexpr bool PLAIN = MODE == 1;
+  const int lb = PLAIN ? (int)blockIdx.x - mb.start : xcd_local_block(mb);
+  const int ipw = blockDim.x / NT;
+  constexpr bool UNI = NT % 64 == 0 && MODE == 1;
+  const int inst = UNI ? wuni((int)(threadIdx.x / NT)) : (int)(threadIdx.x / NT);
+  const int q = threadIdx.x - inst * NT;
+  const long long pair = tiled_pair(d, (long long)lb * ipw + inst);
+  const double rr = xfwd_pair<T, MODE, N, false>(d, io, lb, ipw, inst, q, pair, true);
   if constexpr (MODE == 3) {
     const double s = group_sum(rr, reinterpret_cast<double*>(smem_raw));
     if (threadIdx.x == 0) io.stats[blockIdx.x] = s;
@@ -808,39 +824,8 @@ __global__ void __launch_bounds__(1024) k_ffty_ct(LaunchArgs a) {
   const int c = threadIdx.x % mt;
   const int q = threadIdx.x / mt;
   const int m = (lb - k * tiles) * mt + c;
-  const bool valid = m < d.nxh;
-  cx<T>* S = reinterpret_cast<cx<T>*>(io.spec) + (long long)k * d.plane + spec_col(d, valid ? m : 0);
-  const int rs = d.sbw;  // row stride inside a column block
-  cx<T> v[F::VMAX];
-  // FP32: unconditional loads (an invalid column reads column 0), zeroed
-  // after; FP64 keeps the guarded loads, which measure faster there
-#pragma unroll
-  for (int t = 0; t < F::BT0; ++t) {
-    const int b = q + t * NT;
-    if (F::valid_first(b)) {
-#pragma unroll
-      for (int r = 0; r < F::R0; ++r) {
-        if constexpr (sizeof(T) == 4) {
-          const cx<T> x = S[(b + r * F::NB0) * rs];
-          v[t * F::R0 + r] = valid ? x : cx<T>{0, 0};
-        } else {
-          v[t * F::R0 + r] = valid ? S[(b + r * F::NB0) * rs] : cx<T>{0, 0};
-        }
-      }
-    }
-  }
-  auto li = [mt, c](int i) { return i * mt + c; };
-  F::run(v, lds, li, q, reinterpret_cast<const cx<T>*>(d.twy));
-  if (valid) {
-#pragma unroll
-    for (int t = 0; t < F::BTL; ++t) {
-      const int b = q + t * NT;
-      if (F::valid_last(b)) {
-#pragma unroll
-        for (int r = 0; r < F::RL; ++r) S[F::out_index(q, t, r) * rs] = v[t * F::RL + r];
-      }
-    }
-  }
+  constexpr bool part = true;
+#include "ffty_column.h"
 }
 
 // y-direction complex FFT, persistent form (FP32, 32 elements per thread, so
@@ -1091,109 +1076,8 @@ __global__ void __launch_bounds__(512) k_xinv_ct(LaunchArgs a) {
   const int q = threadIdx.x - inst * NT;
   cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw) + inst * xlds_len(N, 2 * sizeof(T));
   const long long pair = (long long)lb * ipw + inst;
-  const long long r0 = 2 * pair, r1 = 2 * pair + 1;
-  const bool v0 = r0 < d.nrow, v1 = r1 < d.nrow;
-  const cx<T>* S = reinterpret_cast<const cx<T>*>(io.spec);
-  auto li = [](int i) { return xpad<T, N>(i); };
-  if (sizeof(T) == 4 && d.sbw >= 2) {
-    // FP32 with column blocks at least 2 wide: bins m, m+1 (m even) of a row
-    // are adjacent and 16-byte aligned in memory, so a lane loads both with
-    // one access (half the load instructions). Pairs m = 0, 2, .. up to nx/2
-    // over NT threads; the slot after bin nx/2 (a padding slot of the row's
-    // last block: nx/2 + 1 is odd, the padded row length a multiple of 8) is
-    // read and dropped. Loads first and unconditional, as below.
-    typedef T t4 __attribute__((ext_vector_type(4)));
-    constexpr int NP = N / 4 + 1;  // pairs (m even, m <= N/2)
-    constexpr int RND2 = (NP + NT - 1) / NT;
-    const long long so0 = spec_row(d, v0 ? r0 : 0), so1 = spec_row(d, v1 ? r1 : 0);
-    t4 ya[RND2], yb[RND2];
-#pragma unroll
-    for (int t = 0; t < RND2; ++t) {
-      const int m = 2 * (q + t * NT);
-      const bool in = m <= N / 2;
-      const long long cm = spec_col(d, in ? m : 0);
-      const t4 a = *reinterpret_cast<const t4*>(S + so0 + cm), b = *reinterpret_cast<const t4*>(S + so1 + cm);
-      ya[t] = (in && v0) ? a : (t4)(T)0;
-      yb[t] = (in && v1) ? b : (t4)(T)0;
-    }
-#pragma unroll
-    for (int t = 0; t < RND2; ++t) {
-      const int m = 2 * (q + t * NT);
-      if (m <= N / 2) {
-        pack_bins<T>(lds, li, cx<T>{ya[t][0], ya[t][1]}, cx<T>{yb[t][0], yb[t][1]}, N, m);
-        if (m + 1 <= N / 2) pack_bins<T>(lds, li, cx<T>{ya[t][2], ya[t][3]}, cx<T>{yb[t][2], yb[t][3]}, N, m + 1);
-      }
-    }
-  } else {
-    // nx/2 + 1 bins over NT threads: N/(2 NT) + 1 rounds, loads issued first
-    // and unconditional (clamped bin; a missing row reads row 0), selected after
-    constexpr int RND = N / (2 * NT) + 1;
-    const long long so0 = spec_row(d, v0 ? r0 : 0), so1 = spec_row(d, v1 ? r1 : 0);
-    cx<T> xa[RND], xb[RND];
-#pragma unroll
-    for (int t = 0; t < RND; ++t) {
-      const int m = q + t * NT;
-      const bool in = m <= N / 2;
-      const long long cm = spec_col(d, in ? m : N / 2);
-      const cx<T> a = S[so0 + cm], b = S[so1 + cm];
-      xa[t] = (in && v0) ? a : cx<T>{0, 0};
-      xb[t] = (in && v1) ? b : cx<T>{0, 0};
-    }
-#pragma unroll
-    for (int t = 0; t < RND; ++t) {
-      const int m = q + t * NT;
-      if (m <= N / 2) pack_bins<T>(lds, li, xa[t], xb[t], N, m);
-    }
-  }
-  __syncthreads();
-  cx<T> v[F::VMAX];
-#pragma unroll
-  for (int t = 0; t < F::BT0; ++t) {
-    const int b = q + t * NT;
-    if (F::valid_first(b)) {
-#pragma unroll
-      for (int r = 0; r < F::R0; ++r) v[t * F::R0 + r] = lds[xpad<T, N>(b + r * F::NB0)];
-    }
-  }
-  __syncthreads();
-  F::run(v, lds, li, q, reinterpret_cast<const cx<T>*>(d.twx));
-#pragma unroll
-  for (int t = 0; t < F::BTL; ++t) {
-    const int b = q + t * NT;
-    if (F::valid_last(b)) {
-#pragma unroll
-      for (int r = 0; r < F::RL; ++r) lds[xpad<T, N>(F::out_index(q, t, r))] = v[t * F::RL + r];
-    }
-  }
-  __syncthreads();
-  // vector phase: chunks of V points of both rows
-  constexpr int V = x_chunk(N, sizeof(T)), NCH = N / V;
-  using vt = typename Vec<T, V>::type;
-  auto p = reinterpret_cast<__attribute__((address_space(1))) vt*>(xinv_dest<T, MODE>(io));
-  double dz0 = 0.0, dz1 = 0.0, rz = 0.0, zq = 0.0;  // MODE 3
-  if constexpr (MODE == 3) {
-    dz0 = ldg(d.dz + row_level(d, v0 ? (int)r0 : 0));
-    dz1 = ldg(d.dz + row_level(d, v1 ? (int)r1 : 0));
-  }
-#pragma unroll
-  for (int t = 0; t < (NCH + NT - 1) / NT; ++t) {
-    const int ch = q + t * NT;
-    if (NCH % NT == 0 || ch < NCH) {
-      vt a0, a1;
-#pragma unroll
-      for (int e = 0; e < V; ++e) {
-        const cx<T> z = lds[xpad<T, N>(ch * V + e)];
-        a0[e] = z.x;
-        a1[e] = z.y;
-      }
-      if (v0) p[r0 * NCH + ch] = a0;
-      if (v1) p[r1 * NCH + ch] = a1;
-      if constexpr (MODE == 3) {
-        if (v0) dots_vec<T, V>(io, r0 * N + ch * V, reinterpret_cast<const T*>(&a0), dz0, rz, zq);
-        if (v1) dots_vec<T, V>(io, r1 * N + ch * V, reinterpret_cast<const T*>(&a1), dz1, rz, zq);
-      }
-    }
-  }
+  constexpr bool part = true;
+#include "xinv_pair.h"
   if constexpr (MODE == 3) dots_commit<T>(io, rz, zq, smem_raw);
 }
 

@@ -9,6 +9,7 @@ namespace monc {
 // Raise the dynamic-LDS limit of every kernel to the CU's 160 KB.
 void init_kernel_attributes();
 void init_tridiag_attributes();  // the tridiagonal kernels' part of it
+void init_level_attributes();    // the level kernels'
 
 // Transform lengths with compile-time FFT kernels: every 2^a 3^b from 16 to
 // 4096 (others take the runtime-length kernels). The kernels need blockDim =
@@ -64,6 +65,12 @@ void launch_tricol(const LaunchArgs& a, int grid, int block, size_t lds, int row
 // mode 3 (one member): io.p, with one partial sum per workgroup of dz io.u io.p
 // into io.stats and (float, io.v given) of dz io.p io.v into io.w
 void launch_xinv(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int mode, int ct_n, void* stream);
+// both transforms of each level by one workgroup of `block` threads, for even ny
+// and lengths of level_length along x and y (those below ept 16): modes as
+// launch_xfwd's 0 and 1 and launch_xinv's 0, 1 and 2
+bool level_length(int n, bool y);
+void launch_level_fwd(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int mode, void* stream);
+void launch_level_inv(const LaunchArgs& a, int grid, int block, size_t lds, bool fp64, int mode, void* stream);
 // fp64: pressure from io.p (FP64); else (mixed path) p1 + delta summed in
 // FP64 from io.s2 + io.s1, and written rounded to io.p. vec: points per
 // thread (2 needs an even nx, 4 a multiple of 4; else 1)

@@ -222,6 +222,7 @@ bool pp_supported(int n) { return pp_length(n); }
 
 void init_kernel_attributes() {
   init_tridiag_attributes();
+  init_level_attributes();
 #define MONC_GROUP_INIT(K) init_fft_group_##K();
   MONC_FFT_GROUPS(MONC_GROUP_INIT)
 #undef MONC_GROUP_INIT

@@ -228,6 +228,33 @@ def test_elements_per_thread(n):
             plan.close()
 
 
+# every length of the level kernels along x and y, one level and many, transforms
+# whose threads do not divide the workgroup (18, 27, 36, 48, 54), one column past
+# the last whole tile (64 x 64), FP64 below and above its 1536 points; odd ny and
+# the lengths around take the separate kernels
+@pytest.mark.parametrize("shape", [(16, 16, 1), (18, 54, 3), (24, 48, 5), (27, 36, 4), (32, 32, 33), (36, 18, 7),
+                                   (48, 32, 6), (54, 24, 3), (64, 64, 5), (64, 16, 2), (16, 64, 9), (32, 27, 4),
+                                   (72, 16, 3), (16, 72, 3)])
+def test_level_kernels(shape):
+    g, u, v, w = _case(shape, 41)
+    check_fp64(g, u, v, w)
+    errs, out, ref = mixed_case(g, u, v, w)
+    assert max(errs) <= TOL_MIXED, errs
+    for dtype in ("f64", "mixed"):
+        plan = monc.Plan.from_grid(g, dtype)
+        outs = []
+        for mask in (0, (1 << len(monc.KERNELS)) - 1):  # timed: each kernel by itself
+            plan.profile_enable(mask)
+            f = [to_dev(x, plan.torch_dtype) for x in (u, v, w)]
+            f.append(torch.empty_like(f[0]))
+            plan.project(*f)
+            torch.cuda.synchronize()
+            outs.append([x.cpu().numpy() for x in f])
+        plan.profile_enable(0)
+        plan.close()
+        assert all(np.array_equal(a, b) for a, b in zip(*outs))
+
+
 @pytest.mark.parametrize("shape", [(8192, 2, 3), (2, 8192, 2), (6561, 3, 2), (4, 6561, 3)])
 @pytest.mark.parametrize("dtype", ["f64", "mixed"])
 def test_size_limits(shape, dtype):

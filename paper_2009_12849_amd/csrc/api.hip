@@ -155,9 +155,9 @@ static void tricol_shape(int nz, long long tiles, int* waves, int* rows) {
 // and four columns pay (whole projection, us, against 128 bytes: FP64 1024^2 x 96
 // 3180 -> 3010, 432^2 x 32 185 -> 173, 256^2 x 128 237 -> 230, 128 x 768 x 32 112 ->
 // 101, equal at 243^2 x 48 and 128^2 x 64, 32^3 25.5 -> 26.8; FP32 256^2 x 128 242 ->
-// 232, 384 x 256 x 96 284 -> 277, 512^2 x 96 676 -> 668, 64^2 x 32 55.3 -> 56.7) until
+// 234, 384 x 256 x 96 284 -> 280, 512^2 x 96 676 -> 673, 64^2 x 32 55.3 -> 56.7) until
 // the shorter runs cost the x kernels and the column solve as much: FP32 from
-// length 1024 on keeps eight (1024^2 x 96 -0.5 %, 2048^2 x 160 +0.5 % with four)
+// length 1024 on keeps eight (with four 1024^2 x 96 1.6 % slower, 2048^2 x 160 0.5 % faster)
 // where these fill the CUs twice (96 x 2048 x 16 does not: 171 -> 157 with four).
 static int y_columns(int nx, int ny, int nz, int cb) {
   if (ny < 256) return 128 / cb;
@@ -204,7 +204,7 @@ static int configure_tiles(monc_plan* pl, int ex, int ey, int ymt, int triP, int
   if (yept == 32 && (pl->dtype == MONC_FP64 || !pp_supported(pl->ny)))
     return fail(MONC_EINVAL, "32 y-FFT elements per thread (the persistent kernel) need a mixed plan and ny of "
                              "1024, 1536, 2048 or 4096 (got ny=%d)", pl->ny);
-  const int yeff = yept > 0 ? yept : ct_yept_default(pl->ny, (int)cb / 2);
+  const int yeff = yept > 0 ? yept : ct_yept_default(pl->ny);
   // y-FFT columns per workgroup (also the width of the spectral column
   // blocks, up to 8): y_columns by default, bounded by the workgroup size
   // (1024) and 128 KB of LDS
@@ -783,17 +783,17 @@ static Shape member_shape(const MemberDesc& d, Phase ph, bool fp64) {
   return s;
 }
 
-static int launch_one(const Group& g, const std::vector<int>& idx, Phase ph, const Shape& sh, void* stream,
+// The n members idx of the group in one launch (sh: the first one's shape).
+static int launch_one(const Group& g, const int* idx, int n, Phase ph, const Shape& sh, void* stream,
                       Profiler* prof) {
-  LaunchArgs a;
-  std::memset(&a, 0, sizeof a);
-  a.nmem = (int)idx.size();
+  LaunchArgs a;  // entries past the members are not read
+  a.nmem = n;
   long long blocks = 0;
   size_t lds = 0;
   int block = sh.block;
-  for (size_t t = 0; t < idx.size(); ++t) {
+  for (int t = 0; t < n; ++t) {
     const GroupMember& m = g.mem[idx[t]];
-    const Shape s = member_shape(*m.h, ph, g.fp64);
+    const Shape s = t == 0 ? sh : member_shape(*m.h, ph, g.fp64);
     a.mem[t] = m.d;
     a.io[t] = m.io;
     a.block_start[t] = (int)blocks;
@@ -802,7 +802,7 @@ static int launch_one(const Group& g, const std::vector<int>& idx, Phase ph, con
     block = std::max(block, s.block);
     if (blocks > (1LL << 31) - 1) return fail(MONC_EUNSUPPORTED, "grid too large");
   }
-  a.block_start[idx.size()] = (int)blocks;
+  a.block_start[n] = (int)blocks;
   if (block > 1024) return fail(MONC_EUNSUPPORTED, "launch needs %d threads per workgroup", block);
   if (lds > 160 * 1024) return fail(MONC_EUNSUPPORTED, "phase needs %zu bytes of LDS", lds);
   if (blocks == 0) return MONC_OK;
@@ -842,7 +842,7 @@ static int launch_one(const Group& g, const std::vector<int>& idx, Phase ph, con
     case PH_GRAD_MIXED: {
       // per-level reductions of the outputs when the caller asked for them
       bool red = false;
-      for (size_t t = 0; t < idx.size(); ++t)
+      for (int t = 0; t < n; ++t)
         if (a.io[t].stats) {
           launch_stats_init(a.io[t].stats, g.mem[idx[t]].h->nz, stream);
           red = true;
@@ -865,6 +865,10 @@ static int launch_one(const Group& g, const std::vector<int>& idx, Phase ph, con
 // instance and workgroup size, and each partition (up to kMaxLaunchMembers
 // members) is one launch.
 static int launch_phase(const Group& g, Phase ph, void* stream, Profiler* prof) {
+  if (g.mem.size() == 1) {
+    const int only = 0;
+    return launch_one(g, &only, 1, ph, member_shape(*g.mem[0].h, ph, g.fp64), stream, prof);
+  }
   std::vector<std::pair<std::array<int, 3>, std::vector<int>>> parts;
   std::vector<Shape> shapes;
   for (int i = 0; i < (int)g.mem.size(); ++i) {
@@ -882,7 +886,7 @@ static int launch_phase(const Group& g, Phase ph, void* stream, Profiler* prof) 
     parts[pi].second.push_back(i);
   }
   for (size_t pi = 0; pi < parts.size(); ++pi) {
-    const int rc = launch_one(g, parts[pi].second, ph, shapes[pi], stream, prof);
+    const int rc = launch_one(g, parts[pi].second.data(), (int)parts[pi].second.size(), ph, shapes[pi], stream, prof);
     if (rc != MONC_OK) return rc;
   }
   return MONC_OK;
@@ -982,10 +986,10 @@ extern "C" int monc_project(monc_plan* pl, void* u, void* v, void* w, void* p, v
   if (rc != MONC_OK) return rc;
   rc = check_device(pl);
   if (rc != MONC_OK) return rc;
-  Group g;
+  std::vector<Group> groups(1);
+  Group& g = groups[0];
   g.fp64 = pl->dtype == MONC_FP64;
   g.mem.push_back({&pl->h, pl->d_desc, plan_io(pl, u, v, w, p)});
-  std::vector<Group> groups{g};
   Profiler* const prof = pl->prof.mask ? &pl->prof : nullptr;
   return run_phases(groups, plan_sequence(pl->h, g.fp64, prof), stream, prof);
 }
@@ -1007,12 +1011,12 @@ extern "C" int monc_project_reduce(monc_plan* pl, void* u, void* v, void* w, voi
   }
   rc = check_device(pl);
   if (rc != MONC_OK) return rc;
-  Group g;
+  std::vector<Group> groups(1);
+  Group& g = groups[0];
   g.fp64 = pl->dtype == MONC_FP64;
   IoPtrs io = plan_io(pl, u, v, w, p);
   io.stats = stats;
   g.mem.push_back({&pl->h, pl->d_desc, io});
-  std::vector<Group> groups{g};
   Profiler* const prof = pl->prof.mask ? &pl->prof : nullptr;
   return run_phases(groups, plan_sequence(pl->h, g.fp64, prof), stream, prof);
 }
@@ -1047,10 +1051,9 @@ extern "C" int monc_project_noalloc(monc_plan* pl, void* u, void* v, void* w, vo
   io.spec = b;
   io.s1 = fp64 ? nullptr : reinterpret_cast<float*>(b + spec);
   io.s2 = fp64 ? nullptr : reinterpret_cast<float*>(b + spec + field);
-  Group g;
-  g.fp64 = fp64;
-  g.mem.push_back({&pl->h, pl->d_desc, io});
-  std::vector<Group> groups{g};
+  std::vector<Group> groups(1);
+  groups[0].fp64 = fp64;
+  groups[0].mem.push_back({&pl->h, pl->d_desc, io});
   return run_phases(groups, plan_sequence(pl->h, fp64, nullptr), stream, nullptr);  // no profiling events
 }
 

@@ -137,11 +137,10 @@ constexpr int xres_chunk(int n) { return n % 256 == 0 ? 4 : (n % 128 == 0 ? 2 : 
 // bytes: 16 bytes' worth where the row divides by it, else fewer.
 constexpr int x_chunk(int n, int eb) { return n % (16 / eb) == 0 ? 16 / eb : n % 2 == 0 && eb == 4 ? 2 : 1; }
 // Along y the elements per thread (8: radix-8 passes, 16: radix-16 passes)
-// are a tile parameter: default sixteen from length 2048 on in FP64, from 256 on
-// in FP32 (eight -> sixteen, four columns a tile, whole projection: 256^2 x 128 233.7
-// -> 231.8 us, 512^2 x 96 673 -> 668, 1024^2 x 96 2845 -> 2781; FP64 512^2 x 96 684 ->
-// 703, 2048^2 x 160 20845 -> 20454), eight below.
-constexpr int ct_yept_default(int n, int eb) { return n >= (eb == 8 ? 2048 : 256) ? 16 : 8; }
+// are a tile parameter: default sixteen from length 2048 on, eight below (FP64
+// 512^2 x 96 684 us of the projection against 703, 2048^2 x 160 20845 against 20454;
+// FP32 below 2048 within 1 %, with other roundings).
+constexpr int ct_yept_default(int n) { return n >= 2048 ? 16 : 8; }
 constexpr int ct_threads_y_n(int n, int ept) {
   const int i = ct_plan_index(n);
   return i >= 0 ? kCtPlans[i].nt : n >= ept ? n / ept : 1;

@@ -197,7 +197,7 @@ def test_planned_lengths(n):
 @pytest.mark.parametrize("n", [256, 512, 768, 1024, 1536, 2048, 4096])
 def test_elements_per_thread(n):
     # lengths on both sides of the lines between eight and sixteen elements a
-    # thread (x: FP64 2048, FP32 768; y by default: FP64 2048, FP32 256) and of the
+    # thread (x: FP64 2048, FP32 768; y by default: 2048) and of the
     # default y tile's width; the x tile takes every request up to 512 threads of
     # sixteen elements (eight below length 512) and refuses the next one
     rng = np.random.default_rng(n + 1)

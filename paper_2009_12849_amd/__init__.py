@@ -127,6 +127,8 @@ class Plan:
         L = lib()
         self.nx, self.ny, self.nz = int(nx), int(ny), int(nz)
         self.dtype = _dtype_code(dtype)
+        self._tdtype = None
+        self._shape = (self.nz, self.ny, self.nx)
         dzv = np.ascontiguousarray(dz, dtype=np.float64)
         rv = np.ascontiguousarray(rho0, dtype=np.float64)
         if dzv.shape != (self.nz,) or rv.shape != (self.nz,):
@@ -148,8 +150,10 @@ class Plan:
 
     @property
     def torch_dtype(self):
-        import torch
-        return torch.float64 if self.dtype == FP64 else torch.float32
+        if self._tdtype is None:
+            import torch
+            self._tdtype = torch.float64 if self.dtype == FP64 else torch.float32
+        return self._tdtype
 
     def close(self):
         if getattr(self, "_h", None):
@@ -163,19 +167,20 @@ class Plan:
             pass
 
     def _field(self, t, name):
-        if t.dtype != self.torch_dtype or not t.is_cuda or not t.is_contiguous():
+        if t.dtype != (self._tdtype or self.torch_dtype) or not t.is_cuda or not t.is_contiguous():
             raise ValueError(f"{name} must be a contiguous CUDA tensor of {self.torch_dtype}")
-        if tuple(t.shape) != (self.nz, self.ny, self.nx):
-            raise ValueError(f"{name} must have shape (nz, ny, nx) = {(self.nz, self.ny, self.nx)}")
-        return ctypes.c_void_p(t.data_ptr())
+        if t.shape != self._shape:
+            raise ValueError(f"{name} must have shape (nz, ny, nx) = {self._shape}")
+        return t.data_ptr()
 
     def project(self, u, v, w, p, stream=None, stats=None):
         """In-place projection of u, v, w; p receives the pressure. With
         `stats` (a float64 device tensor of 8*nz values), also the per-level
         horizontal mean and max of u, v, w, p: stats.view(4, 2, nz)[f, s, k]
         (see monc_project_reduce)."""
-        args = [self._field(t, n) for t, n in ((u, "u"), (v, "v"), (w, "w"), (p, "p"))]
-        st = ctypes.c_void_p(_stream_handle(stream))
+        field = self._field
+        args = field(u, "u"), field(v, "v"), field(w, "w"), field(p, "p")
+        st = _stream_handle(stream)
         if stats is None:
             _check(lib().monc_project(self._h, *args, st))
             return
@@ -188,8 +193,9 @@ class Plan:
     def project_noalloc(self, u, v, w, p, stream=None):
         """project() with its workspace in the library's static device array
         (see monc_project_noalloc): no device allocation."""
-        args = [self._field(t, n) for t, n in ((u, "u"), (v, "v"), (w, "w"), (p, "p"))]
-        _check(lib().monc_project_noalloc(self._h, *args, ctypes.c_void_p(_stream_handle(stream))))
+        field = self._field
+        args = field(u, "u"), field(v, "v"), field(w, "w"), field(p, "p")
+        _check(lib().monc_project_noalloc(self._h, *args, _stream_handle(stream)))
 
     def project_var(self, rho, u, v, w, p, tol=1e-12, maxit=200, stream=None):
         """Projection with the density field rho(x, y, z) (see

@@ -411,15 +411,15 @@ def max_errors(out, ref, members_in):
 def var_iteration_bytes_per_point(nx, mixed):
     """Algorithmic HBM bytes per grid point of one conjugate-gradient
     iteration of the variable-density projection: the operator (read d and
-    rho, write q), the update (read p, d, r, q; write p, r), the spectral
-    preconditioner (read r, the spectrum's four round trips, write z in the
-    plan's storage type), the inner products (read r and z; with the FP32
-    preconditioner's flexible update also q) and the direction update (read
-    z, d; write d). FP64 128 + 64f, mixed 124 + 32f."""
+    rho, write q), the spectral preconditioner (its first kernel updates the
+    residual: read r, q, write r; the spectrum's four round trips; its last
+    writes z in the plan's storage type and sums the inner products: read r;
+    with the FP32 preconditioner's flexible update also q), p and the direction
+    update (read z, d, p; write d, p). FP64 104 + 64f, mixed 104 + 32f."""
     f = spectral_words(nx)
     wb = 4.0 if mixed else 8.0
-    dots = (8 + wb + 8) if mixed else (8 + wb)
-    return 24 + 48 + (8 + 8 * f * wb + wb) + dots + (16 + wb)
+    dots = (8 + 8) if mixed else 8
+    return 24 + (24 + 8 * f * wb + wb + dots) + (32 + wb)
 
 
 def variable_density(monc, torch, member, reps=3, tol=1e-10, amp=0.2, strong=0.5):
@@ -575,7 +575,9 @@ def classify_kernel(name):
     import re
     if "k_probe_" in name:
         return ("probe", name.split("k_probe_", 1)[1].split("(", 1)[0].split("<", 1)[0])
-    m = re.search(r"k_(xfwd|ffty|xinv|tridiag|grad)(?:_ct|_gen|_pp)?<([^>]*)>", name)
+    if "k_tricol<" in name:  # the wave-per-chunk column solve (FP32 storage)
+        return ("mixed", "tridiag")
+    m = re.search(r"k_(xfwd|ffty|xinv|tridiag|grad|level_fwd|level_inv)(?:_ct|_gen|_pp)?<([^>]*)>", name)
     if not m:
         return None
     kind, args = m.group(1), [x.strip() for x in m.group(2).split(",")]
@@ -588,8 +590,8 @@ def classify_kernel(name):
         return (path, "ffty_inv" if args[1] == "true" else "ffty_fwd")
     if kind == "xinv":
         return (path, "ifftx_corr" if args[1] == "1" else "ifftx")
-    if kind == "tridiag":
-        return (path, "tridiag")
+    if kind in ("tridiag", "level_fwd", "level_inv"):
+        return (path, kind)
     return (path, "grad" if path == "fp64" else "grad_final")
 
 

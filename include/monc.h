@@ -334,17 +334,21 @@ int monc_stream_probe(int kind, void* a, void* b, void* c, void* d, size_t bytes
  *   out[0] = x-FFT elements per thread (runtime-length FFTs only),
  *   out[1] = y-FFT elements per thread (runtime-length FFTs only),
  *   out[2] = y-FFT columns per workgroup,
- *   out[3] = tridiagonal lanes per column (power of 2, <= 64; on grids whose
- *            columns are solved by the kernel with a wave per chunk of rows,
- *            mostly those of many columns and more than 96 levels, out[3] and
- *            out[4] have no effect),
+ *   out[3] = tridiagonal lanes per column (power of 2, <= 64; on the mixed
+ *            plans whose columns are solved by the kernel with a wave per
+ *            chunk of rows, those of many columns and at most 32, 97 to 128 or
+ *            161 to 256 levels or beyond 256 MB, out[3] and out[4] have no
+ *            effect),
  *   out[4] = tridiagonal columns per workgroup (power of 2, times out[3]
  *            at most 1024 threads),
  *   out[5] = x-direction transforms (row pairs) per workgroup of the
  *            compile-time x-FFT kernels (at most 512 threads and 160 KB of
- *            LDS per workgroup; default 256 threads' worth; the mixed
- *            path's residual kernel, at lengths whose transforms are
- *            narrower than a wave, rounds it to whole waves),
+ *            LDS per workgroup, counted with 16 elements a thread from 512
+ *            points on; a kernel with 8 takes as many as its own 512 threads
+ *            hold; default 256 threads' worth, about a wave's on small grids;
+ *            the mixed path's residual kernel, at lengths whose transforms
+ *            are narrower than a wave, rounds it to whole waves; no effect
+ *            where one workgroup transforms a whole level),
  *   out[6] = elements per thread of the compile-time y-FFT kernels, i.e.
  *            their radix plan: 8 (radix-8 passes) or 16 (radix-16 passes);
  *            default 16 from ny = 2048 on, else 8. On MONC_MIXED plans with

@@ -690,7 +690,7 @@ def test_mixed_tridiagonal_tiles_give_identical_bits(nz, lanes):
 # at 183 tiles of 64 columns (128 x 162: 11664 entries, the last tile ragged),
 # 122 tiles (128 x 108) and 517 (256 x 243: 33048 entries); rows per wave from 2
 # to 16 on 2 to 16 waves
-# (1280 and 1536 tiles, 32 x 4096, for the levels above 96)
+# (and 1536, 32 x 4096, for the levels above 96)
 @pytest.mark.parametrize("shape", [(128, 162, n) for n in (96, 97, 112, 113, 129, 160, 161, 241, 256, 257)]
                          + [(128, 108, 97)] + [(256, 243, n) for n in (1, 2, 3, 5, 28, 29, 31, 32, 33)]
                          + [(32, 4096, n) for n in (97, 128, 161)])

@@ -16,7 +16,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmonc.so")
-SOURCES = ["kernels.hip", "tridiag.hip", "level.hip", "krylov.hip", "api.hip", "probe.hip", "plan_math.cpp"]
+SOURCES = ["kernels.hip", "tridiag.hip", "level.hip", "krylov.hip", "api.hip", "probe.hip", "launch_shape.cpp",
+           "plan_math.cpp"]
 # the FFT kernels' compile-time lengths, one object per group (kernels.h)
 FFT_GROUPS = 8
 # (source, object, extra flags)

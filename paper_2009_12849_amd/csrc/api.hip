@@ -19,6 +19,7 @@
 #include "../../include/monc.h"
 #include "kernels.h"
 #include "krylov.h"
+#include "launch_shape.h"
 #include "monc_types.h"
 #include "plan_math.h"
 
@@ -120,34 +121,6 @@ static int tri_rows(int nz, int P) {
   if (s <= 12) return 12;
   if (s <= kTriSmax) return kTriSmax;
   return 0;
-}
-
-// Waves and rows per wave of the wave-per-chunk tridiagonal kernel (FP32 storage),
-// or 0 where the lanes-per-column kernel is the better one. Measured (default
-// tiles, us, lanes-per-column / wave-per-chunk):
-//   above 96 levels from about 512^2 columns on: 128^2 x 128 13.3 / 14.0, 256^2 x 128
-//   21.4 / 21.1, 512^2 x 128 54.7 / 53.1, 1024^2 x 100 211 / 160, 1024 x 512 x 128 128 /
-//   104, 512^2 x 256 189 / 126, 1024^2 x 256 686 / 461; but not from 129 to 160, where
-//   sixteen lanes still do and this kernel's sixteen waves have at most 10 rows
-//   each: 512^2 x 160 59.6 / 84.8, 1024^2 x 160 284 / 325, 2048^2 x 160 1240 / 1292.
-//   up to 32 levels over 512 tiles of 64 columns: 256^2 x 16 9.9 / 9.6, 512^2 x 32
-//   21.4 / 17.9, 432^2 x 32 18.7 / 16.3, 1024 x 512 x 16 20.4 / 18.3.
-//   between: 256^2 x 64 17.3 / 18.1, 512^2 x 96 41.9 / 43.2; beyond the 256 MB
-//   Infinity Cache 129 / 110 (1024^2 x 64).
-// Rows per wave: the fewest waves (2, 4, 8 or 16) with at most 16 rows. More rows
-// mean fewer interface rows and more, smaller workgroups on a CU, whose loads
-// overlap each other's elimination (512^2 x 128 8 waves of 16 rows 55 us, 16 of 8
-// 75; 1024^2 x 64 4 of 16 109, 8 of 8 116, 16 of 4 196).
-static void tricol_shape(int nz, long long tiles, int* waves, int* rows) {
-  *waves = *rows = 0;
-  if (nz > kTriColMax) return;
-  const bool beyond_cache = (double)tiles * 64 * nz * 8 > 256.0 * (1 << 20);
-  const bool use = nz > 96 ? tiles > 1024 && (nz <= 128 || nz > 160) : nz <= 32 ? tiles > 512 : beyond_cache;
-  if (!use) return;
-  int P = 2;
-  while (P < 16 && (nz + P - 1) / P > 16) P *= 2;
-  *waves = P;
-  *rows = std::max(2, (nz + P - 1) / P);
 }
 
 // Default y-FFT columns per workgroup: 128 bytes of a row below length 256. From
@@ -645,12 +618,6 @@ struct Group {
   bool fp64 = true;
 };
 
-enum Phase {
-  PH_XFWD, PH_XPRE, PH_XPRE_UPDATE, PH_RESID, PH_YFWD, PH_TRI, PH_YINV, PH_XINV, PH_XINV_P1, PH_XINV_CORR,
-  PH_XINV_DOTS, PH_GRAD, PH_GRAD_MIXED,
-  PH_LEVEL_FWD, PH_LEVEL_RESID, PH_LEVEL_INV, PH_LEVEL_INV_P1, PH_LEVEL_INV_CORR
-};
-
 static int phase_kernel_id(Phase ph) {
   switch (ph) {
     case PH_XFWD: case PH_XPRE: case PH_XPRE_UPDATE: case PH_LEVEL_FWD: return MONC_K_DIV_FFTX;
@@ -666,25 +633,6 @@ static int phase_kernel_id(Phase ph) {
   return 0;
 }
 
-static bool is_xphase(Phase ph) {
-  return ph == PH_XFWD || ph == PH_XPRE || ph == PH_XPRE_UPDATE || ph == PH_RESID || ph == PH_XINV ||
-         ph == PH_XINV_P1 || ph == PH_XINV_CORR || ph == PH_XINV_DOTS;
-}
-static bool is_yphase(Phase ph) { return ph == PH_YFWD || ph == PH_YINV; }
-static bool is_level_phase(Phase ph) { return ph >= PH_LEVEL_FWD; }
-
-// Launch shape of one member in one phase. Members whose shapes agree share
-// a launch; `variant` identifies the kernel instance (compile-time length or
-// the runtime-length kernel) and `block` its workgroup size.
-struct Shape {
-  int variant = 0;   // compile-time length, or 0 for the runtime-length kernel
-  int sub = 0;       // kernel instance within the variant (tridiagonal: 1 column pairs, 2 wave per chunk)
-  int block = 256;
-  size_t lds = 0;
-  long long blocks = 0;       // tiles of the phase
-  bool persistent = false;    // the grid covers the CUs once and walks the tiles
-};
-
 
 // compute units of the current device (queried once per device)
 static int cu_count() {
@@ -697,90 +645,6 @@ static int cu_count() {
     cache[dev].store(n);
   }
   return n;
-}
-
-static Shape member_shape(const MemberDesc& d, Phase ph, bool fp64) {
-  const size_t cb = fp64 ? 16 : 8;
-  Shape s;
-  if (is_level_phase(ph)) {
-    const int ntx = ct_threads_host(d.nx, (int)cb / 2), nty = ct_threads_y_host(d.ny, 8);
-    s.variant = 1;
-    const int threads = std::max(d.ny / 2 * ntx, d.nxh * nty), rounds = (threads + 511) / 512;
-    s.block = ((threads + rounds - 1) / rounds + 63) / 64 * 64;
-    // whole transforms and a partial one that fills the workgroup
-    const size_t x = (size_t)((s.block + ntx - 1) / ntx) * xlds_len(d.nx, (int)cb);
-    const size_t y = (size_t)((s.block + nty - 1) / nty) * d.ny;
-    s.lds = std::max(x, y) * cb;
-    s.blocks = d.nz;
-  } else if (is_xphase(ph)) {
-    const long long pairs = (d.nrow + 1) / 2;
-    if (ct_supported(d.nx)) {
-      const int nt = ct_threads_host(d.nx, (int)cb / 2);
-      int ipw = d.xpw > 0 ? std::min(d.xpw, std::max(1, 512 / nt)) : std::max(1, 256 / nt);
-      // the residual kernel at these lengths walks whole rows per wave: its
-      // workgroups hold whole waves, the nearest multiple of m transforms
-      // (up, unless that passes 512 threads; m nt <= 512, and at most 16
-      // transforms of 256 to 1536 points stay within the LDS limit)
-      if (ph == PH_RESID && xres_wave_rows(d.nx)) {
-        const int m = wave_transforms(nt);
-        ipw = (ipw + m - 1) / m * m;
-        if (ipw * nt > 512) ipw -= m;
-      }
-      s.variant = d.nx;
-      s.block = ipw * nt;
-      s.lds = (size_t)ipw * xlds_len(d.nx, (int)cb) * cb;
-      s.blocks = (pairs + ipw - 1) / ipw;
-    } else {
-      s.block = std::max(256, (d.fx.nt + 63) / 64 * 64);
-      const int ipw = s.block / d.fx.nt;
-      s.lds = (size_t)ipw * d.nx * cb;
-      s.blocks = (pairs + ipw - 1) / ipw;
-    }
-  } else if (is_yphase(ph)) {
-    if (ct_supported(d.ny) && d.yept == 32) {
-      // the persistent kernel: a fixed number of columns per tile (ymt then
-      // only sets the spectral column blocks)
-      const int nt = ct_threads_y_host(d.ny, 32);
-      const int mt = pp_columns(d.ny);
-      s.variant = d.ny;
-      s.block = mt * nt;
-      s.lds = (size_t)d.ny * (mt + 1) * cb;  // the tile and the twiddle table
-      s.blocks = (long long)d.nz * ((d.nxh + mt - 1) / mt);
-      s.persistent = true;
-    } else if (ct_supported(d.ny)) {
-      const int nt = ct_threads_y_host(d.ny, d.yept);
-      const int mt = std::max(1, std::min(d.ymt, 1024 / nt));
-      s.variant = d.ny;
-      s.block = mt * nt;
-      s.lds = (size_t)d.ny * mt * cb;
-      s.blocks = (long long)d.nz * ((d.nxh + mt - 1) / mt);
-    } else {
-      s.block = std::max(64, (d.ymt * d.fy.nt + 63) / 64 * 64);
-      s.lds = (size_t)d.ny * d.ymt * cb;
-      s.blocks = (long long)d.nz * ((d.nxh + d.ymt - 1) / d.ymt);
-    }
-  } else if (ph == PH_TRI && d.tcwaves) {
-    s.variant = d.tcrows;
-    s.sub = 2;
-    s.block = 64 * d.tcwaves;
-    s.lds = (size_t)tricol_lds(d.tcwaves) * sizeof(double);
-    s.blocks = ((long long)d.ny * d.nxp + 63) / 64;
-  } else if (ph == PH_TRI) {
-    s.variant = d.tris;
-    s.sub = tri_pairs(d.tris, d.tricw, !fp64) ? 1 : 0;
-    s.block = d.tricw * d.triP;
-    s.lds = (size_t)d.tricw * (d.triP * tri_lane_slots(d.tris, !fp64) + 1) * 16;  // matches the kernel's column stride
-    s.blocks = ((long long)d.ny * d.nxp + d.tricw - 1) / d.tricw;  // over the padded plane
-  } else {
-    // points per thread: 16-byte field accesses on the mixed path (4 floats),
-    // 2 doubles on the FP64 path; fewer when nx does not divide
-    const int want = (ph == PH_GRAD_MIXED) ? 4 : 2;
-    const int vec = (d.nx % want == 0) ? want : (d.nx % 2 == 0) ? 2 : 1;
-    const long long nvec = (long long)d.nx * d.ny * d.nz / vec;
-    s.variant = vec;
-    s.blocks = (nvec + 255) / 256;
-  }
-  return s;
 }
 
 // The n members idx of the group in one launch (sh: the first one's shape).

@@ -205,21 +205,6 @@ __global__ void __launch_bounds__(256) k_grad(LaunchArgs a) {
 // ---------------------------------------------------------------------------
 // host-side launchers
 // ---------------------------------------------------------------------------
-bool ct_supported(int n) {
-  switch (n) {
-#define MONC_CASE(N) case N:
-#define MONC_GROUP_CASES(K) MONC_CT_GROUP_##K(MONC_CASE)
-    MONC_FFT_GROUPS(MONC_GROUP_CASES)
-#undef MONC_GROUP_CASES
-#undef MONC_CASE
-    return true;
-    default:
-      return false;
-  }
-}
-
-bool pp_supported(int n) { return pp_length(n); }
-
 void init_kernel_attributes() {
   init_tridiag_attributes();
   init_level_attributes();

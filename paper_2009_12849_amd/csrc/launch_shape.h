@@ -1,0 +1,40 @@
+// Launch shapes of the projection's phases, and the rule that picks the column
+// kernel. Pure C++ (no HIP calls), so that what the host gives a kernel can be
+// checked without a device.
+#pragma once
+#include <stddef.h>
+
+#include "monc_types.h"
+
+namespace monc {
+
+enum Phase {
+  PH_XFWD, PH_XPRE, PH_XPRE_UPDATE, PH_RESID, PH_YFWD, PH_TRI, PH_YINV, PH_XINV, PH_XINV_P1, PH_XINV_CORR,
+  PH_XINV_DOTS, PH_GRAD, PH_GRAD_MIXED,
+  PH_LEVEL_FWD, PH_LEVEL_RESID, PH_LEVEL_INV, PH_LEVEL_INV_P1, PH_LEVEL_INV_CORR
+};
+
+bool is_xphase(Phase ph);
+bool is_yphase(Phase ph);
+bool is_level_phase(Phase ph);
+
+// Launch shape of one member in one phase. Members whose shapes agree share
+// a launch; `variant` identifies the kernel instance (compile-time length or
+// the runtime-length kernel) and `block` its workgroup size.
+struct Shape {
+  int variant = 0;   // compile-time length, or 0 for the runtime-length kernel
+  int sub = 0;       // kernel instance within the variant (tridiagonal: 1 column pairs, 2 wave per chunk)
+  int block = 256;
+  size_t lds = 0;
+  long long blocks = 0;       // tiles of the phase
+  bool persistent = false;    // the grid covers the CUs once and walks the tiles
+};
+
+Shape member_shape(const MemberDesc& d, Phase ph, bool fp64);
+
+// Waves and rows per wave of the wave-per-chunk tridiagonal kernel for a plan of
+// FP32 storage with nz levels and `tiles` tiles of 64 columns, or 0 where the
+// lanes-per-column kernel is the better one.
+void tricol_shape(int nz, long long tiles, int* waves, int* rows);
+
+}  // namespace monc

@@ -66,6 +66,9 @@ Shape member_shape(const MemberDesc& d, Phase ph, bool fp64) {
       s.lds = (size_t)ipw * d.nx * cb;
       s.blocks = (pairs + ipw - 1) / ipw;
     }
+    // group_sum: a double per thread, idle ones too (a runtime-length FP32 kernel
+    // of one element a thread has fewer LDS values than threads)
+    if (ph == PH_XPRE_UPDATE || ph == PH_XINV_DOTS) s.lds = std::max(s.lds, (size_t)s.block * sizeof(double));
   } else if (is_yphase(ph)) {
     if (ct_supported(d.ny) && d.yept == 32) {
       // the persistent kernel: a fixed number of columns per tile (ymt then

@@ -405,3 +405,28 @@ def test_long_domain_converges_like_a_square_one(dtype):
     cond = _cond_estimate(g.nx, g.ny, g.dx, g.dy, g.dz, contrast=1.3 / 0.7)
     pmax = np.abs(ref[3]).max()
     assert np.abs(outs[3] - ref[3]).max() <= 10 * cond * TOL * pmax, (np.abs(outs[3] - ref[3]).max() / pmax, cond)
+
+
+@pytest.mark.parametrize("nx", [3, 6, 9, 12])
+def test_one_element_a_thread(nx):
+    """The runtime-length x kernels with one element a thread on FP32 storage,
+    where whole transforms leave idle threads in a workgroup (255 or 252 of 256
+    at work): the workgroup sums of the residual and the inner products need a
+    double of LDS for those as well. Outputs against the direct solve, bounds as
+    in test_variable_density_matches_direct_solve."""
+    g, rho, u, v, w = _case((nx, 24, 9), 1900 + nx)
+    plan = _plan(g, rho, "mixed")
+    plan.params = [1, 1, 0, 0, 0, 0, 0]
+    assert plan.params[0] == 1
+    print(f"case one element a thread nx={nx}", flush=True)
+    t = [_t(a) for a in (u, v, w)]
+    p = torch.empty_like(t[0])
+    it, rel = plan.project_var(_t(rho), *t, p, tol=TOL)
+    torch.cuda.synchronize()
+    plan.close()
+    assert rel <= TOL and it < 200
+    ref = oracle.project_var(u, v, w, g.dx, g.dy, g.dz, rho)
+    scale = max(np.abs(a).max() for a in (u, v, w))
+    for f in range(3):
+        assert np.abs(t[f].cpu().numpy() - ref[f]).max() <= 1e-9 * scale, f
+    assert np.abs(p.cpu().numpy() - ref[3]).max() <= 1e-8 * np.abs(ref[3]).max()

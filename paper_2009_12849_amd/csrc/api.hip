@@ -3,7 +3,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <array>
 #include <atomic>
 #include <cmath>
 #include <cstdarg>
@@ -725,32 +724,16 @@ static int launch_one(const Group& g, const int* idx, int n, Phase ph, const Sha
   return MONC_OK;
 }
 
-// One phase for every member of the group: members are partitioned by kernel
-// instance and workgroup size, and each partition (up to kMaxLaunchMembers
-// members) is one launch.
+// One phase for every member of the group, a launch per part.
 static int launch_phase(const Group& g, Phase ph, void* stream, Profiler* prof) {
   if (g.mem.size() == 1) {
     const int only = 0;
     return launch_one(g, &only, 1, ph, member_shape(*g.mem[0].h, ph, g.fp64), stream, prof);
   }
-  std::vector<std::pair<std::array<int, 3>, std::vector<int>>> parts;
-  std::vector<Shape> shapes;
-  for (int i = 0; i < (int)g.mem.size(); ++i) {
-    const Shape s = member_shape(*g.mem[i].h, ph, g.fp64);
-    // the compile-time kernels need blockDim to match each member exactly,
-    // and the y kernels the member's elements per thread
-    const std::array<int, 3> key{s.variant, s.variant ? s.block : 0,
-                                 !s.variant ? 0 : is_yphase(ph) ? g.mem[i].h->yept : s.sub};
-    size_t pi = 0;
-    while (pi < parts.size() && (parts[pi].first != key || parts[pi].second.size() >= (size_t)kMaxLaunchMembers)) ++pi;
-    if (pi == parts.size()) {
-      parts.push_back({key, {}});
-      shapes.push_back(s);
-    }
-    parts[pi].second.push_back(i);
-  }
-  for (size_t pi = 0; pi < parts.size(); ++pi) {
-    const int rc = launch_one(g, parts[pi].second.data(), (int)parts[pi].second.size(), ph, shapes[pi], stream, prof);
+  std::vector<const MemberDesc*> mem;
+  for (const GroupMember& m : g.mem) mem.push_back(m.h);
+  for (const LaunchPart& part : launch_parts(mem, ph, g.fp64)) {
+    const int rc = launch_one(g, part.mem.data(), (int)part.mem.size(), ph, part.shape, stream, prof);
     if (rc != MONC_OK) return rc;
   }
   return MONC_OK;

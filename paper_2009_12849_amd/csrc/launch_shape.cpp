@@ -2,6 +2,7 @@
 #include "launch_shape.h"
 
 #include <algorithm>
+#include <array>
 
 #include "kernels.h"
 
@@ -114,6 +115,29 @@ Shape member_shape(const MemberDesc& d, Phase ph, bool fp64) {
     s.blocks = (nvec + 255) / 256;
   }
   return s;
+}
+
+std::vector<LaunchPart> launch_parts(const std::vector<const MemberDesc*>& mem, Phase ph, bool fp64) {
+  std::vector<LaunchPart> parts;
+  std::vector<std::array<int, 3>> keys;
+  for (int i = 0; i < (int)mem.size(); ++i) {
+    const Shape s = member_shape(*mem[i], ph, fp64);
+    // the compile-time kernels need blockDim to match each member exactly,
+    // and the y kernels the member's elements per thread; the runtime-length x
+    // kernels fill blockDim with transforms, of which the LDS holds those of the
+    // member's own workgroup (8 beside 4374 points: 576 transforms of 8 where
+    // the LDS of 4374 values holds 546)
+    const std::array<int, 3> key{s.variant, s.variant || is_xphase(ph) ? s.block : 0,
+                                 !s.variant ? 0 : is_yphase(ph) ? mem[i]->yept : s.sub};
+    size_t pi = 0;
+    while (pi < parts.size() && (keys[pi] != key || parts[pi].mem.size() >= (size_t)kMaxLaunchMembers)) ++pi;
+    if (pi == parts.size()) {
+      parts.push_back({s, {}});
+      keys.push_back(key);
+    }
+    parts[pi].mem.push_back(i);
+  }
+  return parts;
 }
 
 // Measured (default tiles, us, lanes-per-column / wave-per-chunk):

@@ -4,6 +4,8 @@
 #pragma once
 #include <stddef.h>
 
+#include <vector>
+
 #include "monc_types.h"
 
 namespace monc {
@@ -31,6 +33,14 @@ struct Shape {
 };
 
 Shape member_shape(const MemberDesc& d, Phase ph, bool fp64);
+
+// The launches of one phase over several members: members of one kernel
+// instance and workgroup size, up to kMaxLaunchMembers in each.
+struct LaunchPart {
+  Shape shape;           // of its first member
+  std::vector<int> mem;  // indices of its members
+};
+std::vector<LaunchPart> launch_parts(const std::vector<const MemberDesc*>& mem, Phase ph, bool fp64);
 
 // Waves and rows per wave of the wave-per-chunk tridiagonal kernel for a plan of
 // FP32 storage with nz levels and `tiles` tiles of 64 columns, or 0 where the

@@ -494,6 +494,35 @@ def test_batch_with_whole_row_residual_equals_member_projections():
         pl.close()
 
 
+@pytest.mark.parametrize("dtype", ["f64", "mixed"])
+def test_batch_of_shortest_and_longest_rows_equals_member_projections(dtype):
+    # the runtime-length x kernels of short rows (8 points: as many transforms in
+    # a workgroup as it has threads, 576 row pairs for several of them) beside
+    # those of rows above 4096 points, whose workgroups are larger: each member's
+    # single projection bit for bit, launched directly, captured and replayed
+    mem = [m for i, shape in enumerate([(8, 36, 32), (4374, 2, 2), (3, 54, 24)])
+           for m in _ensemble(1, [shape], 70 + i)]
+    plans = [monc.Plan.from_grid(g, dtype) for g, *_ in mem]
+    tdt = plans[0].torch_dtype
+    cast = np.float64 if dtype == "f64" else np.float32
+    base = [[to_dev(a.astype(cast), tdt) for a in (u, v, w)] for _, u, v, w in mem]
+    singles = [run_gpu(g, u.astype(cast), v.astype(cast), w.astype(cast), dtype, plan=pl)
+               for (g, u, v, w), pl in zip(mem, plans)]
+    fields = [[t.clone() for t in b] + [torch.empty_like(b[0])] for b in base]
+    print(f"case batch of shortest and longest rows {dtype}", flush=True)
+    for call in range(3):
+        for f, b in zip(fields, base):
+            for t, a in zip(f, b):
+                t.copy_(a)
+        monc.project_batched(plans, *[[f[t] for f in fields] for t in range(4)])
+        torch.cuda.synchronize()
+        for i, f in enumerate(fields):
+            for t, ref in zip(f, singles[i]):
+                assert np.array_equal(t.cpu().numpy().astype(np.float64), ref), (call, i)
+    for pl in plans:
+        pl.close()
+
+
 def test_batch_autotune_picks_a_schedule_and_caches_it(tmp_path, monkeypatch):
     import json
     cache = tmp_path / "tune.json"

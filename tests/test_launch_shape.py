@@ -13,6 +13,7 @@ CSRC = os.path.join(ROOT, "paper_2009_12849_amd", "csrc")
 DRIVER = r"""
 #include <cstdio>
 #include <cstring>
+#include <vector>
 #include "kernels.h"
 #include "launch_shape.h"
 #include "plan_math.h"
@@ -42,10 +43,42 @@ static void x_shapes() {
   std::printf("\n");
 }
 
+// b fp64 n, then nx ny nz ex of each member: per launch of the forward x phase its
+// workgroup and LDS bytes (as the launch takes them, the largest of its members)
+// and each member's index and threads a transform
+static void batch_shapes() {
+  int fp64, n;
+  if (std::scanf("%d %d", &fp64, &n) != 2) return;
+  std::vector<MemberDesc> d(n);
+  std::vector<const MemberDesc*> mem;
+  for (MemberDesc& m : d) {
+    int ex;
+    if (std::scanf("%d %d %d %d", &m.nx, &m.ny, &m.nz, &ex) != 4) return;
+    m.nxh = m.nx / 2 + 1;
+    m.nrow = (long long)m.ny * m.nz;
+    if (!radix_plan(m.nx, m.fx) || !fft_threads(m.fx, ex)) return;
+    mem.push_back(&m);
+  }
+  for (const LaunchPart& p : launch_parts(mem, PH_XFWD, fp64 != 0)) {
+    int block = 0;
+    size_t lds = 0;
+    for (int i : p.mem) {
+      const Shape s = member_shape(d[i], PH_XFWD, fp64 != 0);
+      block = s.block > block ? s.block : block;
+      lds = s.lds > lds ? s.lds : lds;
+    }
+    std::printf("part %d %zu", block, lds);
+    for (int i : p.mem) std::printf(" %d %d", i, ct_supported(d[i].nx) ? ct_threads_host(d[i].nx, fp64 ? 8 : 4) : d[i].fx.nt);
+    std::printf("\n");
+  }
+  std::printf("end\n");
+}
+
 int main() {
   char what[32];
   while (std::scanf("%31s", what) == 1) {
     if (!std::strcmp(what, "x")) x_shapes();
+    if (!std::strcmp(what, "b")) batch_shapes();
   }
   return 0;
 }
@@ -110,3 +143,27 @@ def test_x_kernels_fit_the_lds_they_are_given(ask):
             assert ipw * n * cb <= lds, case
             if name in ("xpre_update", "xinv_dots"):
                 assert block * 8 <= lds, case
+
+
+@pytest.mark.parametrize("f64", [0, 1])
+def test_members_that_share_an_x_launch_fit_its_lds(ask, f64):
+    """A launch's workgroup is the largest of its members' and a kernel fills it
+    with as many transforms of its member as it holds: their LDS is within what
+    the launch has, for every pair of lengths (of the runtime-length kernels,
+    whose workgroups differ from 256 threads above 4096 points) and for one batch
+    of them all."""
+    lengths = smooth(1, 15) + smooth(4097, 8192) + [16, 27, 96]
+    batches = [[a, b] for a in lengths for b in lengths if a < b] + [lengths]
+    rows = ask([f"b {f64} {len(b)} " + " ".join(f"{n} 36 32 8" for n in b) for b in batches])
+    cb = 16 if f64 else 8
+    it = iter(rows)
+    for b in batches:
+        seen = []
+        for r in it:
+            if r[0] == "end":
+                break
+            block, lds, members = int(r[1]), int(r[2]), list(map(int, r[3:]))
+            for i, nt in zip(members[::2], members[1::2]):
+                seen.append(i)
+                assert block // nt * b[i] * cb <= lds, (b, b[i], block, lds)
+        assert sorted(seen) == list(range(len(b)))

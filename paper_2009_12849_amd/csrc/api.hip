@@ -111,17 +111,6 @@ static int pow2_floor(int x) {
   return p;
 }
 
-// Rows per lane of the tridiagonal kernel for nz rows on P lanes: the
-// smallest compiled row count (2..8, 10, 12, 16) that covers them, 0 if none.
-static int tri_rows(int nz, int P) {
-  const int s = std::max(2, (nz + P - 1) / P);
-  if (s <= 8) return s;
-  if (s <= 10) return 10;
-  if (s <= 12) return 12;
-  if (s <= kTriSmax) return kTriSmax;
-  return 0;
-}
-
 // Default y-FFT columns per workgroup: 128 bytes of a row below length 256. From
 // there on the tile's LDS (columns * ny * cb) sets how many workgroups a CU holds,
 // and four columns pay (whole projection, us, against 128 bytes: FP64 1024^2 x 96
@@ -205,13 +194,9 @@ static int configure_tiles(monc_plan* pl, int ex, int ey, int ymt, int triP, int
   const int s = tri_rows(pl->nz, triP);
   if (s == 0)
     return fail(MONC_EINVAL, "%d lanes leave %d rows per lane (max %d)", triP, (pl->nz + triP - 1) / triP, kTriSmax);
-  // tridiagonal tile: columns per workgroup (0 = automatic: 256 threads, four
-  // waves, so that five workgroups fit a CU at ~100 registers per lane; half
-  // that where it leaves fewer than four workgroups a CU: 128^2 x 128 FP64 16.0
-  // -> 15.4 us, but 1024^2 x 64 FP32 129 -> 185)
+  // tridiagonal tile: columns per workgroup (0 = automatic)
   if (tricw <= 0) tricw = pl->tricw;
-  const int tri_threads = (long long)pl->ny * nxh * triP < 1024 * 256 ? 128 : 256;
-  const int cw = tricw > 0 ? tricw : std::max(1, tri_threads / triP);
+  const int cw = tricw > 0 ? tricw : tri_columns(pl->ny, nxh, triP);
   if (cw & (cw - 1) || cw * triP > 512)
     return fail(MONC_EINVAL, "tridiagonal columns per workgroup must be a power of 2 with %d lanes <= 512 threads (got %d)",
                 triP, cw);
@@ -1742,9 +1727,6 @@ static int tune_plan(monc_plan* pl, void* stream) {
     std::vector<int> vals;
     unsigned mask;
   };
-  std::vector<int> pvals;
-  for (int P = 1; P <= kTriPmax; P *= 2)
-    if (tri_rows(pl->nz, P) != 0 && (P == 1 || (pl->nz + P - 1) / P >= 2)) pvals.push_back(P);
   // elements per thread only shape the runtime-length FFT kernels
   std::vector<Axis> axes;
   if (!ct_supported(pl->nx)) axes.push_back({0, {2, 4, 8}, xmask});
@@ -1759,18 +1741,28 @@ static int tune_plan(monc_plan* pl, void* stream) {
     else axes.push_back({6, {8, 16}, ymask | xmask});
   }
   axes.push_back({2, {1, 2, 4, 8, 16, 32}, ymask | xmask});
+  std::vector<int> lanes;
+  std::map<int, int> lane_columns;
   if (!pl->h.tcwaves) {  // the lanes-per-column tridiagonal kernel
-    axes.push_back({3, pvals, tmask});
-    axes.push_back({4, {4, 8, 16, 32}, tmask});
+    // each lane count with the columns of its automatic tile: a fixed column
+    // count would time the others with more or fewer threads a workgroup, or
+    // refuse them
+    for (const TriTile& t : tri_lane_tiles(pl->nz, pl->ny, pl->h.nxh)) {
+      lanes.push_back(t.lanes);
+      lane_columns[t.lanes] = t.columns;
+    }
+    axes.push_back({3, lanes, tmask});
+    axes.push_back({4, {}, tmask});  // its values follow from the lanes chosen
   }
   if (ct_supported(pl->nx)) axes.push_back({5, {1, 2, 4}, xmask});
   for (const auto& ax : axes) {
     double best_cost = 1e300;
     int best_val = best[ax.idx];
-    for (int val : ax.vals) {
+    for (int val : ax.idx == 4 ? tri_column_values(pl->ny, pl->h.nxh, best[3]) : ax.vals) {
       int prm[MONC_NPARAMS];
       std::copy(best, best + MONC_NPARAMS, prm);
       prm[ax.idx] = val;
+      if (ax.idx == 3) prm[4] = lane_columns[val];
       double cost = 0.0;
       if (measure(prm, ax.mask, cost) != MONC_OK) continue;
       int eff[MONC_NPARAMS];
@@ -1782,6 +1774,7 @@ static int tune_plan(monc_plan* pl, void* stream) {
       }
     }
     best[ax.idx] = best_val;
+    if (ax.idx == 3 && lane_columns.count(best_val)) best[4] = lane_columns[best_val];
   }
   pl->prof.mask = saved_mask;
   for (auto& b : buf) (void)hipFree(b);

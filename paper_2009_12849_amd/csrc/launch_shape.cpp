@@ -140,6 +140,37 @@ std::vector<LaunchPart> launch_parts(const std::vector<const MemberDesc*>& mem, 
   return parts;
 }
 
+int tri_rows(int nz, int P) {
+  const int s = std::max(2, (nz + P - 1) / P);
+  if (s <= 8) return s;
+  if (s <= 10) return 10;
+  if (s <= 12) return 12;
+  if (s <= kTriSmax) return kTriSmax;
+  return 0;
+}
+
+// 256 threads, four waves, so that five workgroups fit a CU at ~100 registers per
+// lane; half that where it leaves fewer than four workgroups a CU: 128^2 x 128 FP64
+// 16.0 -> 15.4 us, but 1024^2 x 64 FP32 129 -> 185
+int tri_columns(int ny, int nxh, int P) {
+  const int threads = (long long)ny * nxh * P < 1024 * 256 ? 128 : 256;
+  return std::max(1, threads / P);
+}
+
+std::vector<TriTile> tri_lane_tiles(int nz, int ny, int nxh) {
+  std::vector<TriTile> out;
+  for (int P = 1; P <= kTriPmax; P *= 2)
+    if (tri_rows(nz, P) != 0 && (P == 1 || (nz + P - 1) / P >= 2)) out.push_back({P, tri_columns(ny, nxh, P)});
+  return out;
+}
+
+std::vector<int> tri_column_values(int ny, int nxh, int P) {
+  std::vector<int> out = {4, 8, 16, 32};
+  const int automatic = tri_columns(ny, nxh, P);
+  if (std::find(out.begin(), out.end(), automatic) == out.end()) out.push_back(automatic);
+  return out;
+}
+
 // Measured (default tiles, us, lanes-per-column / wave-per-chunk):
 //   above 96 levels from about 512^2 columns on: 128^2 x 128 13.3 / 14.0, 256^2 x 128
 //   21.4 / 21.1, 512^2 x 128 54.7 / 53.1, 1024^2 x 100 211 / 160, 1024 x 512 x 128 128 /

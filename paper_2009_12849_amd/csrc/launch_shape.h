@@ -1,5 +1,5 @@
-// Launch shapes of the projection's phases, and the rule that picks the column
-// kernel. Pure C++ (no HIP calls), so that what the host gives a kernel can be
+// Launch shapes of the projection's phases, and the rules of the column
+// kernels' tiles. Pure C++ (no HIP calls), so that what the host gives a kernel can be
 // checked without a device.
 #pragma once
 #include <stddef.h>
@@ -41,6 +41,19 @@ struct LaunchPart {
   std::vector<int> mem;  // indices of its members
 };
 std::vector<LaunchPart> launch_parts(const std::vector<const MemberDesc*>& mem, Phase ph, bool fp64);
+
+// Rows per lane of the lanes-per-column tridiagonal kernel for nz rows on P lanes:
+// the smallest compiled row count (2..8, 10, 12, 16) that covers them, 0 if none.
+int tri_rows(int nz, int P);
+// Its automatic columns per workgroup with P lanes a column.
+int tri_columns(int ny, int nxh, int P);
+// Its tiles that the autotuner times: every lane count of at least two rows a lane
+// with its automatic columns, then for the lanes chosen the column counts.
+struct TriTile {
+  int lanes, columns;
+};
+std::vector<TriTile> tri_lane_tiles(int nz, int ny, int nxh);
+std::vector<int> tri_column_values(int ny, int nxh, int P);
 
 // Waves and rows per wave of the wave-per-chunk tridiagonal kernel for a plan of
 // FP32 storage with nz levels and `tiles` tiles of 64 columns, or 0 where the

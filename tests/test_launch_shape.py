@@ -74,11 +74,26 @@ static void batch_shapes() {
   std::printf("end\n");
 }
 
+// t nz ny nxh: the column solve's tiles that the autotuner times, lanes and columns
+// of each; after a bar the column counts of each
+static void tri_tiles() {
+  int nz, ny, nxh;
+  if (std::scanf("%d %d %d", &nz, &ny, &nxh) != 3) return;
+  std::printf("t");
+  for (const TriTile& t : tri_lane_tiles(nz, ny, nxh)) std::printf(" %d %d", t.lanes, t.columns);
+  for (const TriTile& t : tri_lane_tiles(nz, ny, nxh)) {
+    std::printf(" |");
+    for (int c : tri_column_values(ny, nxh, t.lanes)) std::printf(" %d", c);
+  }
+  std::printf("\n");
+}
+
 int main() {
   char what[32];
   while (std::scanf("%31s", what) == 1) {
     if (!std::strcmp(what, "x")) x_shapes();
     if (!std::strcmp(what, "b")) batch_shapes();
+    if (!std::strcmp(what, "t")) tri_tiles();
   }
   return 0;
 }
@@ -167,3 +182,21 @@ def test_members_that_share_an_x_launch_fit_its_lds(ask, f64):
                 seen.append(i)
                 assert block // nt * b[i] * cb <= lds, (b, b[i], block, lds)
         assert sorted(seen) == list(range(len(b)))
+
+
+@pytest.mark.parametrize("ny,nx", [(4, 4), (32, 32), (256, 256), (1024, 1024)])
+def test_autotuned_lane_counts_keep_the_threads_of_a_workgroup(ask, ny, nx):
+    """The autotuner times every lane count that the kernel takes (2 rows a lane or
+    more, at most 16), each with 128 or 256 threads a workgroup and so none refused
+    (512 threads at most); the column counts timed for the lanes chosen include
+    the automatic one."""
+    nxh = nx // 2 + 1
+    for nz, r in zip(range(1, 1025), ask([f"t {nz} {ny} {nxh}" for nz in range(1, 1025)])):
+        head, *cols = " ".join(r[1:]).split("|")
+        v = list(map(int, head.split()))
+        tiles = list(zip(v[::2], v[1::2]))
+        lanes = [1 << i for i in range(7)]
+        assert [t[0] for t in tiles] == [P for P in lanes if -(-nz // P) <= 16 and (P == 1 or -(-nz // P) >= 2)], nz
+        for (P, c), vals in zip(tiles, cols):
+            assert P * c in (128, 256), (nz, P, c)
+            assert c in map(int, vals.split()), (nz, P, c, vals)

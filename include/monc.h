@@ -68,7 +68,7 @@ enum {
 #define MONC_MAX_N 8192
 #define MONC_MAX_NZ 1024
 #define MONC_MAX_BATCH 256
-/* Most independent graph branches a batch schedule deals its groups to. */
+/* Most independent graph branches of a batch schedule. */
 #define MONC_MAX_BRANCHES 4
 
 /*
@@ -133,9 +133,10 @@ int monc_project_noalloc(monc_plan* plan, void* u, void* v, void* w, void* p, vo
  * plans and pointers launches the phases directly (grouped per-phase launches
  * covering every member, in the member order and grouping that monc_autotune
  * chose for this set of grids, else largest first in one group); the second
- * captures them in a HIP graph, members of different lengths on up to
- * MONC_MAX_BRANCHES concurrent branches, and it and later calls with the same
- * plans and pointers replay the graph. A call on a stream that the caller is
+ * captures them in a HIP graph, members of different lengths on concurrent
+ * branches (as many as the schedule asks for, by default up to
+ * MONC_MAX_BRANCHES), and it and later calls with the same plans and pointers
+ * replay the graph. A call on a stream that the caller is
  * capturing always launches directly. The batch is the ensemble workload of the
  * paper's self-tuning proposal (Sec. 5): many independent solves scheduled
  * together on one device.
@@ -289,7 +290,8 @@ int monc_profile_read(monc_plan* plan, double* ms, int* launches);
  * member order (largest or smallest first), grouping (all members per
  * phase, or groups of at most 1024, 512, 256, 128 or 64 MB of working set,
  * each running its whole phase sequence) and number of graph branches the
- * groups are dealt to (1, 2 or 4) is captured and its graph replayed on
+ * groups are dealt to (1, 2 or 4; the members of one group are dealt to the
+ * branches of the default schedule) is captured and its graph replayed on
  * scratch fields.
  * Results are stored in the plans / the schedule table and in the JSON cache
  * named by the MONC_TUNE_CACHE environment variable (if set), which plans and
@@ -302,13 +304,18 @@ int monc_autotune(monc_plan* const* plans, int count, void* stream);
  * from the cache, or the default): out[0] = member order (0 largest first,
  * 1 smallest first), out[1] = working-set budget per group in MB (0 = one
  * group, every phase over all members), out[2] = number of groups, out[3] =
- * graph branches (1..MONC_MAX_BRANCHES): with a budget, group g runs on
- * branch g mod branches, and the branches are independent chains of the
- * captured graph that the device runs concurrently. out holds 4 ints. */
+ * branches of the captured graph (1..MONC_MAX_BRANCHES): independent chains
+ * that the device runs concurrently. With a budget, group g runs on branch g
+ * mod branches; without, members of one nx and ny stay together and these
+ * classes are dealt to the branches by their points, to no more than there are
+ * classes. A schedule set by hand reads back as it was set; the default one
+ * group has the smaller of its classes and MONC_MAX_BRANCHES. Direct launches
+ * (see monc_project_batched) take one chain. out holds 4 ints. */
 int monc_batch_schedule(monc_plan* const* plans, int count, int* out);
 /* Set that schedule by hand (order 0 or 1, budget_mb >= 0, branches in
- * [1, MONC_MAX_BRANCHES]; branches only matter with budget_mb > 0); the next
- * monc_project_batched call over these plans captures it. */
+ * [1, MONC_MAX_BRANCHES], the most that the graph has; 1: a single chain). As
+ * over new pointers, the first monc_project_batched call after it launches
+ * directly and the second captures. */
 int monc_batch_set_schedule(monc_plan* const* plans, int count, int order, int budget_mb, int branches);
 
 /* Streaming-bandwidth probes: one launch of the plainest kernel that moves

@@ -295,7 +295,8 @@ def autotune_batched(plans: Sequence[Plan], stream=None):
 
 
 def batch_schedule(plans: Sequence[Plan]):
-    """(order, budget_mb, groups, branches) of the batch schedule of these plans."""
+    """(order, budget_mb, groups, branches) of the batch schedule of these plans
+    (monc_batch_schedule)."""
     arr = (ctypes.c_void_p * len(plans))(*[pl.handle for pl in plans])
     out = (ctypes.c_int * 4)()
     _check(lib().monc_batch_schedule(arr, len(plans), out))

@@ -1237,7 +1237,9 @@ static void drop_batch_cache_for(unsigned long long plan_id) {
 struct BatchSchedule {
   int order = 0;
   int budget_mb = 0;
-  int branches = 1;  // independent graph branches the groups are dealt to
+  // most independent graph branches: of the groups with a budget, of the members
+  // without (deal_chains); 0 (the default): one with a budget, MONC_MAX_BRANCHES without
+  int branches = 0;
 };
 
 static std::mutex g_sched_mu;
@@ -1283,7 +1285,9 @@ static BatchSchedule lookup_schedule(monc_plan* const* plans, int count) {
         (it->second.size() == 2 || (it->second[2] >= 1 && it->second[2] <= MONC_MAX_BRANCHES))) {
       sc.order = it->second[0];
       sc.budget_mb = it->second[1];
-      sc.branches = it->second.size() == 3 ? it->second[2] : 1;
+      // a file names the branches that a schedule has: one group's chains, dealt
+      // automatically, are one where its members share their lengths
+      sc.branches = it->second.size() == 3 && (sc.budget_mb > 0 || it->second[2] > 1) ? it->second[2] : 0;
     }
   }
   std::lock_guard<std::mutex> lk(g_sched_mu);
@@ -1330,43 +1334,26 @@ static void build_groups(monc_plan* const* plans, int count, void* const* u, voi
   groups.push_back(std::move(g));
 }
 
-// Members dealt to at most MONC_MAX_BRANCHES independent chains of about equal
-// points, members of one (nx, ny) together (they share every launch), in the
-// members' order. A phase is one launch per kernel instance, and an ensemble
-// of uneven grids has one for most of its lengths: one after the other they
-// leave a tail each, which for small members is most of their time (six
-// members between 72 x 54 x 33 and 162 x 128 x 41 in FP64: 281 -> 204 us).
-static std::vector<Group> deal_chains(const Group& g) {
-  struct Class {
-    int nx, ny;
-    double points;
-    std::vector<int> mem;
-  };
-  std::vector<Class> cls;
-  for (int i = 0; i < (int)g.mem.size(); ++i) {
-    const MemberDesc& h = *g.mem[i].h;
-    size_t c = 0;
-    while (c < cls.size() && (cls[c].nx != h.nx || cls[c].ny != h.ny)) ++c;
-    if (c == cls.size()) cls.push_back({h.nx, h.ny, 0.0, {}});
-    cls[c].mem.push_back(i);
-    cls[c].points += (double)h.nx * h.ny * h.nz;
-  }
-  std::stable_sort(cls.begin(), cls.end(), [](const Class& a, const Class& b) { return a.points > b.points; });
-  const size_t nb = std::min<size_t>(cls.size(), MONC_MAX_BRANCHES);
-  std::vector<double> load(nb, 0.0);
-  std::vector<std::vector<int>> pick(nb);
-  for (const Class& c : cls) {
-    const size_t b = std::min_element(load.begin(), load.end()) - load.begin();
-    load[b] += c.points;
-    pick[b].insert(pick[b].end(), c.mem.begin(), c.mem.end());
-  }
-  std::vector<Group> out(nb);
-  for (size_t b = 0; b < nb; ++b) {
-    std::sort(pick[b].begin(), pick[b].end());
-    out[b].fp64 = g.fp64;
-    for (int i : pick[b]) out[b].mem.push_back(g.mem[i]);
+// The group's members as its chains.
+static std::vector<Group> chain_groups(const Group& g, int most) {
+  std::vector<const MemberDesc*> mem;
+  for (const GroupMember& m : g.mem) mem.push_back(m.h);
+  std::vector<Group> out;
+  for (const std::vector<int>& chain : deal_chains(mem, most)) {
+    out.emplace_back();
+    out.back().fp64 = g.fp64;
+    for (int i : chain) out.back().mem.push_back(g.mem[i]);
   }
   return out;
+}
+
+// The graph branches that the schedule asks for (of groups) or has (of chains).
+static int schedule_branches(monc_plan* const* plans, int count, const BatchSchedule& sc) {
+  if (sc.branches > 0) return sc.branches;
+  if (sc.budget_mb > 0) return 1;
+  std::vector<const MemberDesc*> mem;
+  for (int i = 0; i < count; ++i) mem.push_back(&plans[i]->h);
+  return (int)deal_chains(mem, MONC_MAX_BRANCHES).size();
 }
 
 // All phases of each group in turn. With side streams (a capture in progress
@@ -1533,9 +1520,9 @@ extern "C" int monc_project_batched(monc_plan* const* plans, int count, void* co
     return run_batch(groups, seq, stream, prof);
   }
   if (!ent->exec) {
-    int branches = sc.branches;
+    int branches = std::max(1, sc.branches);
     if (sc.budget_mb == 0) {  // one group: its chains
-      groups = deal_chains(groups[0]);
+      groups = chain_groups(groups[0], sc.branches > 0 ? sc.branches : MONC_MAX_BRANCHES);
       branches = (int)groups.size();
     }
     // side streams of the capture: forked from the first and joined back into
@@ -1585,7 +1572,7 @@ extern "C" int monc_batch_schedule(monc_plan* const* plans, int count, int* out)
   out[0] = sc.order;
   out[1] = sc.budget_mb;
   out[2] = ngroups;
-  out[3] = sc.branches;
+  out[3] = schedule_branches(plans, count, sc);
   return MONC_OK;
 }
 
@@ -1789,8 +1776,9 @@ static int tune_plan(monc_plan* pl, void* stream) {
   return MONC_OK;
 }
 
-// The batch schedule: every candidate (member order x grouping budget) is
-// captured and replayed on scratch fields; the fastest replay wins.
+// The batch schedule: every candidate (member order x grouping budget x
+// branches of the groups; one group is dealt to its chains automatically) is
+// captured and replayed on scratch fields; the fastest replays win.
 static int tune_schedule(monc_plan* const* plans, int count, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   const size_t eb = elem_bytes(plans[0]->dtype);
@@ -1823,6 +1811,10 @@ static int tune_schedule(monc_plan* const* plans, int count, void* stream) {
   for (int i = 0; i < count; ++i) total += member_bytes(plans[i]);
   const int budgets[] = {0, 1024, 512, 256, 128, 64};
   const int branch_counts[] = {1, 2, 4};
+  auto store = [&](const BatchSchedule& sc) {
+    std::lock_guard<std::mutex> lk(g_sched_mu);
+    g_sched[batch_key(plans, count)] = sc;
+  };
   BatchSchedule best;
   double best_ms = 1e300;
   int rc = MONC_OK;
@@ -1831,11 +1823,15 @@ static int tune_schedule(monc_plan* const* plans, int count, void* stream) {
       for (int branches : branch_counts) {
         if (rc != MONC_OK) break;
         if (budget && ((size_t)budget << 20) >= total) continue;  // one group anyway
-        if (branches > 1 && !budget) continue;                     // one group: one chain
+        if (branches > 1 && !budget) continue;                     // one group: its chains
         if (branches > 1 && ((size_t)budget << 20) * (size_t)(branches - 1) >= total)
           continue;  // fewer groups than branches
-        rc = monc_batch_set_schedule(plans, count, order, budget, branches);
-        for (int r = 0; r < 2 && rc == MONC_OK; ++r)  // capture, then one warm replay
+        BatchSchedule sc;
+        sc.order = order;
+        sc.budget_mb = budget;
+        sc.branches = budget ? branches : 0;
+        store(sc);
+        for (int r = 0; r < 3 && rc == MONC_OK; ++r)  // direct launches, capture and launch, one warm replay
           rc = monc_project_batched(plans, count, f[0].data(), f[1].data(), f[2].data(), f[3].data(), stream);
         if (rc != MONC_OK) break;
         const int reps = 5;
@@ -1848,9 +1844,7 @@ static int tune_schedule(monc_plan* const* plans, int count, void* stream) {
           rc = fail(MONC_EHIP, "autotune: event timing failed");
         if (rc == MONC_OK && ms < best_ms) {
           best_ms = ms;
-          best.order = order;
-          best.budget_mb = budget;
-          best.branches = branches;
+          best = sc;
         }
       }
   (void)hipEventDestroy(e0);
@@ -1860,12 +1854,11 @@ static int tune_schedule(monc_plan* const* plans, int count, void* stream) {
   for (int i = 0; i < count; ++i) drop_batch_cache_for(plans[i]->id);
   release();
   if (rc != MONC_OK) return rc;
-  rc = monc_batch_set_schedule(plans, count, best.order, best.budget_mb, best.branches);
-  if (rc != MONC_OK) return rc;
+  store(best);
   if (const char* path = std::getenv("MONC_TUNE_CACHE")) {
     std::lock_guard<std::mutex> lk(g_cache_mu);
     auto m = read_cache(path);
-    m[batch_key(plans, count)] = {best.order, best.budget_mb, best.branches};
+    m[batch_key(plans, count)] = {best.order, best.budget_mb, schedule_branches(plans, count, best)};
     write_cache(path, m);
   }
   return MONC_OK;

@@ -42,6 +42,10 @@ struct LaunchPart {
 };
 std::vector<LaunchPart> launch_parts(const std::vector<const MemberDesc*>& mem, Phase ph, bool fp64);
 
+// Members (their indices, in order) dealt to at most `most` independent chains of
+// about equal points, members of one (nx, ny) together.
+std::vector<std::vector<int>> deal_chains(const std::vector<const MemberDesc*>& mem, int most);
+
 // Rows per lane of the lanes-per-column tridiagonal kernel for nz rows on P lanes:
 // the smallest compiled row count (2..8, 10, 12, 16) that covers them, 0 if none.
 int tri_rows(int nz, int P);

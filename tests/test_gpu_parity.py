@@ -494,6 +494,39 @@ def test_batch_with_whole_row_residual_equals_member_projections():
         pl.close()
 
 
+def test_batch_schedule_reports_the_branches_it_has(tmp_path, monkeypatch):
+    # the default's chains (one per nx, ny, up to four), a schedule set by hand as
+    # set, and the three forms of a saved one: those of a single group without
+    # branches, or with one, are the default's
+    import json
+    cache = tmp_path / "tune.json"
+    monkeypatch.setenv("MONC_TUNE_CACHE", str(cache))
+    shapes = [(32, 32, 4), (48, 32, 4), (32, 32, 7), (32, 48, 4), (54, 32, 4), (64, 32, 4)]
+    rng = np.random.default_rng(80)
+    plans = [monc.Plan.from_grid(synth.random_grid(rng, *s, stretch=(1.0, 1.02)), "f64") for s in shapes]
+    for n, chains in ((1, 1), (2, 2), (3, 2), (4, 3), (5, 4), (6, 4)):
+        assert monc.batch_schedule(plans[:n]) == (0, 0, 1, chains), n
+    for order, budget, branches in ((0, 0, 1), (1, 0, 2), (0, 1, 1), (1, 1, 4)):
+        monc.set_batch_schedule(plans, order, budget, branches)
+        o, b, _, nb = monc.batch_schedule(plans)
+        assert (o, b, nb) == (order, budget, branches)
+    # (a schedule is looked up once per set of grids: other grids for each form)
+    for i, (saved, want) in enumerate((([1, 0], (1, 0, 2)), ([1, 0, 1], (1, 0, 2)), ([0, 0, 2], (0, 0, 2)),
+                                       ([1, 64, 1], (1, 64, 1)), ([0, 64], (0, 64, 1)))):
+        pair = [monc.Plan.from_grid(synth.random_grid(rng, nx, 8, 3 + i, stretch=(1.0, 1.02)), "f64") for nx in (16, 18)]
+        cache.write_text(json.dumps({f"gfx950:batch:2:{_grids_hash(pair):016x}:fp64": saved}))
+        o, b, _, nb = monc.batch_schedule(pair)
+        assert (o, b, nb) == want, (saved, (o, b, nb))
+
+
+def _grids_hash(plans):
+    # the name of a set of grids in the cache: FNV-1a over its sorted list
+    h = 1469598103934665603
+    for c in "".join(sorted(f"{p.nx},{p.ny},{p.nz};" for p in plans)):
+        h = (h ^ ord(c)) * 1099511628211 % 2 ** 64
+    return h
+
+
 @pytest.mark.parametrize("dtype", ["f64", "mixed"])
 def test_batch_of_shortest_and_longest_rows_equals_member_projections(dtype):
     # the runtime-length x kernels of short rows (8 points: as many transforms in

@@ -88,12 +88,31 @@ static void tri_tiles() {
   std::printf("\n");
 }
 
+// c most n, then nx ny nz of each member: the chains they are dealt to
+static void chains() {
+  int most, n;
+  if (std::scanf("%d %d", &most, &n) != 2) return;
+  std::vector<MemberDesc> d(n);
+  std::vector<const MemberDesc*> mem;
+  for (MemberDesc& m : d) {
+    if (std::scanf("%d %d %d", &m.nx, &m.ny, &m.nz) != 3) return;
+    mem.push_back(&m);
+  }
+  std::printf("c");
+  for (const std::vector<int>& c : deal_chains(mem, most)) {
+    std::printf(" |");
+    for (int i : c) std::printf(" %d", i);
+  }
+  std::printf("\n");
+}
+
 int main() {
   char what[32];
   while (std::scanf("%31s", what) == 1) {
     if (!std::strcmp(what, "x")) x_shapes();
     if (!std::strcmp(what, "b")) batch_shapes();
     if (!std::strcmp(what, "t")) tri_tiles();
+    if (!std::strcmp(what, "c")) chains();
   }
   return 0;
 }
@@ -200,3 +219,26 @@ def test_autotuned_lane_counts_keep_the_threads_of_a_workgroup(ask, ny, nx):
         for (P, c), vals in zip(tiles, cols):
             assert P * c in (128, 256), (nz, P, c)
             assert c in map(int, vals.split()), (nz, P, c, vals)
+
+
+@pytest.mark.parametrize("most", [1, 2, 3, 4])
+def test_chains_of_a_batch(ask, most):
+    """A batch's members are dealt to as many chains as asked for, to no more than
+    there are pairs of nx and ny: each member once, in the members' order, those
+    of one pair on one chain, and no chain more than a pair's points above the
+    lightest. One chain is the members as they stand."""
+    import random
+    rng = random.Random(7)
+    grids = [(64, 64, 64), (128, 128, 96), (192, 192, 128), (256, 256, 128), (64, 64, 20), (96, 64, 9), (64, 96, 9)]
+    batches = [[rng.choice(grids) for _ in range(n)] for n in (1, 2, 3, 5, 8, 48) for _ in range(4)]
+    rows = ask([f"c {most} {len(b)} " + " ".join(" ".join(map(str, g)) for g in b) for b in batches])
+    for b, r in zip(batches, rows):
+        chains = [list(map(int, c.split())) for c in " ".join(r[1:]).split("|")[1:]]
+        pairs = {g[:2] for g in b}
+        assert len(chains) == min(most, len(pairs)), (b, chains)
+        assert sorted(i for c in chains for i in c) == list(range(len(b)))
+        assert all(c == sorted(c) for c in chains)
+        assert sum(len({b[i][:2] for i in c}) for c in chains) == len(pairs)
+        points = [sum(b[i][0] * b[i][1] * b[i][2] for i in c) for c in chains]
+        largest = max(sum(g[0] * g[1] * g[2] for g in b if g[:2] == p) for p in pairs)
+        assert max(points) - min(points) <= largest

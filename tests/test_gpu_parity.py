@@ -527,6 +527,60 @@ def _grids_hash(plans):
     return h
 
 
+def _every_call_equals_singles(plans, base, calls, what):
+    """Call k of a batch over the same fields (0 direct launches, 1 captured and
+    launched, from 2 on replays), inputs restored eagerly in between: every
+    member's single projection bit for bit."""
+    singles = []
+    for pl, b in zip(plans, base):
+        f = [t.clone() for t in b] + [torch.empty_like(b[0])]
+        pl.project(*f)
+        singles.append(f)
+    fields = [[t.clone() for t in b] + [torch.empty_like(b[0])] for b in base]
+    for call in range(calls):
+        for f, b in zip(fields, base):
+            for t, a in zip(f, b):
+                t.copy_(a)
+            f[3].fill_(float("nan"))
+        monc.project_batched(plans, *[[f[t] for f in fields] for t in range(4)])
+        torch.cuda.synchronize()
+        for i, (f, ref) in enumerate(zip(fields, singles)):
+            for t, r in zip(f, ref):
+                assert torch.equal(t, r), (what, call, i)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "mixed"])
+def test_every_call_of_every_schedule_equals_member_projections(dtype):
+    # every order, grouping and number of branches, and the default (None): the
+    # graph's fork and join, several chains of groups or of lengths, as they replay
+    mem = _ensemble(7, [(32, 32, 16), (48, 48, 24), (64, 32, 20), (24, 36, 12), (96, 96, 9)], 41)
+    plans = [monc.Plan.from_grid(g, dtype) for g, *_ in mem]
+    base = [[to_dev(a, pl.torch_dtype) for a in (u, v, w)] for (_, u, v, w), pl in zip(mem, plans)]
+    for sched in [None, (0, 0, 1), (0, 0, 2), (1, 0, 3), (0, 0, 4), (0, 1, 1), (1, 1, 2), (1, 1, 4), (0, 8, 1), (0, 8, 2),
+                  (1, 8, 4)]:
+        print(f"case every call {dtype} {sched}", flush=True)
+        if sched is not None:
+            monc.set_batch_schedule(plans, *sched)
+            o, b, _, nb = monc.batch_schedule(plans)
+            assert (o, b, nb) == sched
+        _every_call_equals_singles(plans, base, 4, sched)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "mixed"])
+def test_every_call_of_the_ensemble_equals_member_projections(dtype):
+    # the 48-member ensemble with default tiles: four lengths on four branches
+    torch.manual_seed(90)
+    plans, base = [], []
+    for g, _ in synth.ensemble_members(48):
+        plans.append(monc.Plan.from_grid(g, dtype))
+        base.append([torch.randn((g.nz, g.ny, g.nx), dtype=plans[-1].torch_dtype, device=DEV) for _ in range(3)])
+    assert monc.batch_schedule(plans) == (0, 0, 1, 4)
+    print(f"case every call of the ensemble {dtype}", flush=True)
+    _every_call_equals_singles(plans, base, 4, "ensemble")
+    for pl in plans:
+        pl.close()
+
+
 @pytest.mark.parametrize("dtype", ["f64", "mixed"])
 def test_batch_of_shortest_and_longest_rows_equals_member_projections(dtype):
     # the runtime-length x kernels of short rows (8 points: as many transforms in

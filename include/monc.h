@@ -347,7 +347,7 @@ int monc_stream_probe(int kind, void* a, void* b, void* c, void* d, size_t bytes
  *            161 to 256 levels or beyond 256 MB, out[3] and out[4] have no
  *            effect),
  *   out[4] = tridiagonal columns per workgroup (power of 2, times out[3]
- *            at most 1024 threads),
+ *            at most 512 threads),
  *   out[5] = x-direction transforms (row pairs) per workgroup of the
  *            compile-time x-FFT kernels (at most 512 threads and 160 KB of
  *            LDS per workgroup, counted with 16 elements a thread from 512

@@ -443,12 +443,12 @@ extern "C" monc_plan* monc_plan_create(int nx, int ny, int nz, double dx, double
   std::vector<double> lamy = modified_wavenumbers(ny, ny, dy);
   std::vector<double> twx = twiddles(nx), twy = twiddles(ny);
 
-  // one device blob for the tables: 7 FP64 vertical, the packed metrics,
+  // one device blob for the tables: 3 FP64 vertical, the packed metrics,
   // lamx, lamy, twiddles in the storage precision
   const size_t eb = elem_bytes(dtype);
   auto al = [](size_t x) { return (x + 255) / 256 * 256; };
   size_t off = 0;
-  const size_t o_v64 = off; off += al(7 * (size_t)nz * 8);
+  const size_t o_v64 = off; off += al(3 * (size_t)nz * 8);
   const size_t o_lev = off; off += al((size_t)kLev64 * nz * 8);
   const size_t o_levf = off; off += al((size_t)kLev32 * nz * 4);
   const size_t o_lx = off; off += al((size_t)h.nxh * 8);
@@ -459,8 +459,8 @@ extern "C" monc_plan* monc_plan_create(int nx, int ny, int nz, double dx, double
   const size_t tables_bytes = off;
   std::vector<unsigned char> blob(tables_bytes, 0);
   double* v64 = reinterpret_cast<double*>(blob.data() + o_v64);
-  const std::vector<double>* cols[7] = {&vt.rho0, &vt.rhow, &vt.rdz, &vt.rdzc, &vt.dz, &vt.ta, &vt.tc};
-  for (int t = 0; t < 7; ++t) std::memcpy(v64 + (size_t)t * nz, cols[t]->data(), (size_t)nz * 8);
+  const std::vector<double>* cols[3] = {&vt.rdz, &vt.rdzc, &vt.dz};
+  for (int t = 0; t < 3; ++t) std::memcpy(v64 + (size_t)t * nz, cols[t]->data(), (size_t)nz * 8);
   double* lev = reinterpret_cast<double*>(blob.data() + o_lev);
   float* levf = reinterpret_cast<float*>(blob.data() + o_levf);
   for (int k = 0; k < nz; ++k) {
@@ -530,13 +530,9 @@ extern "C" monc_plan* monc_plan_create(int nx, int ny, int nz, double dx, double
   }
   unsigned char* base = reinterpret_cast<unsigned char*>(pl->d_tables);
   const double* d64 = reinterpret_cast<const double*>(base + o_v64);
-  h.rho0 = d64;
-  h.rhow = d64 + nz;
-  h.rdz = d64 + 2 * (size_t)nz;
-  h.rdzc = d64 + 3 * (size_t)nz;
-  h.dz = d64 + 4 * (size_t)nz;
-  h.ta = d64 + 5 * (size_t)nz;
-  h.tc = d64 + 6 * (size_t)nz;
+  h.rdz = d64;
+  h.rdzc = d64 + nz;
+  h.dz = d64 + 2 * (size_t)nz;
   h.tra = reinterpret_cast<const double*>(base + o_tr);
   h.trc = h.tra + nz + kTriPmax;
   h.trr = h.trc + nz + kTriPmax;
@@ -896,8 +892,8 @@ static constexpr int kVarMaxIt = 10000;
 
 // Work vectors of one plan, carved from one allocation: r, d, q (FP64
 // fields), z (storage type), two partial-sum arrays, the scalars (status
-// row and one row per iteration), the vertical interpolation weights za, zb,
-// the preconditioner's device descriptor and its scaling field s (FP32).
+// row and one row per iteration), the vertical interpolation weights za, zb and
+// the preconditioner's device descriptor.
 struct VarWs {
   double *r, *d, *q, *part0, *part1, *scal, *za, *zb;
   void* z;

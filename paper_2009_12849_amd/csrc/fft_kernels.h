@@ -13,8 +13,8 @@
 //   grad     pressure-gradient correction u -= G p, w lid = 0
 //
 // The FFT phases exist twice: with the transform length fixed at compile
-// time (CtFft, for the lengths listed in kernels.h) and with a runtime length
-// (fft_lds) for every other 2^a 3^b length.
+// time (CtFft, for the lengths listed in kernels.h: 16 to 4096) and with a
+// runtime length (fft_lds) for every other 2^a 3^b length.
 //
 // Every kernel serves a group of members: blockIdx.x is mapped to a member
 // through LaunchArgs::block_start, and each member's sizes and tables come
@@ -709,7 +709,7 @@ __device__ __forceinline__ double xfwd_pair(MemberDesc d, IoPtrs io, int lb, int
 // The residual variant at lengths whose transforms share a wave and whose
 // stencil does not walk whole rows per wave (lengths that are not a multiple
 // of 64, such as 16-48, 96, 144, 288, or whose whole-wave workgroups would
-// pass 512 threads: 576, 1152, 2304) keeps its row contexts in vector
+// pass 512 threads: 1152, 1728, 2304, 3456) keeps its row contexts in vector
 // registers: about 172 registers, 2 waves per SIMD. A budget for 3 spills 2-6
 // registers and measured about 1 % faster where it applied before the
 // whole-row stencil; a budget for 5 waves at the longer lengths spills 16 and

@@ -1,4 +1,5 @@
-// Launchers of the projection kernels (kernels.hip).
+// Launchers of the projection kernels (kernels.hip, fft_inst.hip, tridiag.hip,
+// level.hip).
 #pragma once
 #include <stddef.h>
 
@@ -25,8 +26,8 @@ void init_level_attributes();    // the level kernels'
 #define MONC_CT_GROUP_5(X) X(36) X(128) X(324) X(768) X(1728) X(3456)
 #define MONC_CT_GROUP_6(X) X(48) X(144) X(384) X(864) X(1944) X(3888)
 #define MONC_CT_GROUP_7(X) X(54) X(162) X(432) X(972) X(2048) X(4096)
-// lengths with two y-FFT radix plans (8 or 16 elements per thread)
-// are those without a plan of their own (ct_plan_index < 0)
+// Lengths with two y-FFT radix plans (8 or 16 elements per thread) are those
+// without a plan of their own (ct_plan_index < 0).
 // One group's instances: false if the group does not hold the length.
 #define MONC_GROUP_DECL(K)                                                                                          \
   void init_fft_group_##K();                                                                                        \

@@ -25,8 +25,8 @@
 // A workgroup of kVarBlock threads takes a 2-D tile of a level, min(nx, 256)
 // wide, a few points per thread at stride kVarBlock in the tile, coalesced
 // along rows. The stencil kernels (divergence, operator; kVarStPts points a
-// thread) walk them up a group of kVarLevels levels
-// (blockIdx.y), keeping the column's values of the levels below and above in
+// thread) walk them up a group of kVarLevels levels (the divergence's is
+// blockIdx.y, the operator's follows var_operator_block), keeping the column's values of the levels below and above in
 // registers, so only the x and y neighbours come through the caches; the
 // pointwise kernels (kVarPts points a thread) take one level per workgroup (more, shorter
 // workgroups stream faster). Two points and two levels a stencil thread leave
@@ -68,8 +68,9 @@ __device__ __forceinline__ double block_sum(double x) {
   return s;
 }
 
-// One thread's points: NPTS points of a level at stride kVarBlock (horizontal offsets inside a level and their x and y neighbours, periodic),
-// revisited on each level of the workgroup's group of kVarLevels levels.
+// One thread's points: NPTS points of a level at stride kVarBlock (horizontal
+// offsets inside a level and their x and y neighbours, periodic), revisited on
+// each level of the workgroup's group of kVarLevels levels.
 template <int NPTS>
 struct Col {
   int h[NPTS], hw[NPTS], he[NPTS], hs[NPTS], hn[NPTS];

@@ -38,18 +38,16 @@ constexpr int kTriColMax = 256;
 // LDS doubles of a workgroup of P waves: the interface rows (5), the chunks'
 // last rows (4) and the interface solution (2), P x 64 each
 constexpr int tricol_lds(int P) { return 11 * P * 64; }
-// Threads per compile-time transform (shared by the kernels and the host's
-// launch shapes), and so the radix plan (16 elements per thread take radix-16
-// passes): along x sixteen elements each from length 512 on, eight below;
-// along y sixteen from length 2048 on, so that a 1024-thread workgroup still
-// holds several columns of the longest transforms, eight below (lengths of
-// kCtPlans aside).
+// Threads per compile-time transform, shared by the kernels and the host's
+// launch shapes, and so the radix plan (sixteen elements a thread take radix-16
+// passes, eight radix-8 passes): kCtPlans, else ct_threads_x_n and ct_threads_y_n.
+//
 // Lengths with a factor 3 that have a radix plan of their own: threads per
 // transform and the radices, along x and y alike. Radices 6, 9, 12, 16 and 18
-// leave two passes up to 324 points and three up to 3888 (an LDS round trip
-// and two barriers each), and the threads are chosen so that the passes'
-// butterflies fill them: a thread holds 6 to 18 values, 24 where the last pass
-// is a third idle. The runtime-length kernels, which hold their butterflies in
+// leave two passes up to 324 points and three above, four at 2187 (an LDS round
+// trip and two barriers each), and the threads are chosen so that the passes'
+// butterflies fill them where one count can: a thread holds 6 to 18 values, 20 at
+// 1296 and 24 at 3888, whose last pass leaves some of its last round idle. The runtime-length kernels, which hold their butterflies in
 // scratch memory and read the fields point by point, took 573 us for a whole
 // 432 x 288 x 75 FP64 projection and 473 us for a 243 x 324 x 61 mixed one
 // against 311 and 210 us.
@@ -99,8 +97,8 @@ constexpr int ct_plan_index(int n) {  // its place in kCtPlans, or -1
 }
 //
 // Along x, in storage type of eb bytes: eight elements a thread (radix-8 passes),
-// sixteen (radix-16 passes, one exchange through LDS fewer) from length 768 on in
-// FP32 and from 2049 on in FP64, whose transforms (16 bytes a value, 160 KB a CU)
+// sixteen (radix-16 passes, one exchange through LDS fewer) above length 768 in
+// FP32 and above 2048 in FP64, whose transforms (16 bytes a value, 160 KB a CU)
 // leave room for ten waves of sixteen-element threads but twenty of eight-element
 // ones. The x kernels of a pass, sixteen -> eight elements a thread, us:
 // FP64 512^2 x 96 291 -> 259, 768^2 x 64 452 -> 386, 1024^2 x 96 1033 -> 1005,
@@ -124,7 +122,7 @@ constexpr int wave_transforms(int nt) {
 }
 // The residual's stencil phase at lengths whose transforms do not fill whole
 // waves, are a multiple of 64 points and fit whole waves in 512 threads (64,
-// 128, 192, 256, 384, 768, 1536) walks whole rows per wave (64 lanes x
+// 128, 192, 256, 384, 576, 768, 1536) walks whole rows per wave (64 lanes x
 // xres_chunk points: 4 where the length allows, else 2, else 1), so that each
 // wave handles one transform's rows at a time and its row contexts are
 // wave-uniform; its workgroups then hold whole waves.
@@ -203,16 +201,12 @@ struct MemberDesc {
   const double* lev;      // packed metrics (kLev64 doubles a level, 16-byte aligned)
   const float* levf;      // their FP32 copies (kLev32 floats a level)
   // FP64 vertical tables, all of length nz
-  const double* rho0;     // reference density at centres
-  const double* rhow;     // density on the top face of cell k (0 at k = nz-1)
   const double* rdz;      // 1/dz_k
   const double* rdzc;     // 1/dzc_k (0 at k = nz-1)
   const double* dz;       // dz_k (gauge weights)
-  const double* ta;       // tridiagonal sub-diagonal a_k (a_0 = 0)
-  const double* tc;       // tridiagonal super-diagonal c_k (c_{nz-1} = 0)
   // The tridiagonal solver's rows, kTriPmax past nz: row k of the column with
   // eigenvalue lam reads tra_k P_{k-1} - (tra_k + trc_k + trr_k lam) P_k +
-  // trc_k P_{k+1}. Rows past nz read P_k - P_{k-1} = 0 (tra 1, trc 0, trr 0):
+  // trc_k P_{k+1} (tra_0 = 0, trc_{nz-1} = 0). Rows past nz read P_k - P_{k-1} = 0 (tra 1, trc 0, trr 0):
   // nonsingular for every lam, and the lid (c_{nz-1} = 0) keeps them out of
   // the real rows, so a lane's rows need no range checks.
   const double* tra;
@@ -229,7 +223,8 @@ struct MemberDesc {
   int triP;               // tridiagonal lanes per column (power of 2)
   int tris;               // rows per lane (>= 2)
   int tricw;              // columns per workgroup (blockDim / triP)
-  int tcwaves;            // waves of the wave-per-chunk kernel (0: more than kTriColMax levels)
+  int tcwaves;            // waves of the wave-per-chunk kernel (0: FP64 storage, or tricol_shape's rule
+                          // picks the lanes-per-column kernel)
   int tcrows;             // its rows per wave
   int ptk;                // levels per (level, row pair) tile of the stencil kernels (1 = row order)
   int ptj;                // row pairs per such tile of the x-forward kernels (8 to 64)

@@ -34,10 +34,6 @@ struct Row5 {
 
 __device__ __forceinline__ double shfl_d(double v, int src) { return __shfl(v, src); }
 
-__device__ __forceinline__ Row5 shfl_row(const Row5& r, int src) {
-  return Row5{shfl_d(r.a, src), shfl_d(r.b, src), shfl_d(r.c, src), shfl_d(r.x, src), shfl_d(r.y, src)};
-}
-
 // 1/x in FP64: the hardware reciprocal refined by one Newton step (error
 // about one ulp; the solve does not need the correctly rounded quotient)
 __device__ __forceinline__ double rcp64(double x) {

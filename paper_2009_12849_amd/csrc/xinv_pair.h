@@ -10,9 +10,10 @@
     // FP32 with column blocks at least 2 wide: bins m, m+1 (m even) of a row
     // are adjacent and 16-byte aligned in memory, so a lane loads both with
     // one access (half the load instructions). Pairs m = 0, 2, .. up to nx/2
-    // over NT threads; the slot after bin nx/2 (a padding slot of the row's
-    // last block: nx/2 + 1 is odd, the padded row length a multiple of 8) is
-    // read and dropped. Loads first and unconditional, as below.
+    // over NT threads. Where nx/2 is even the slot after bin nx/2 is read and
+    // dropped (nx/2 + 1 is then odd and the padded row length a multiple of 8,
+    // so it is a padding slot of the row's last block). Loads first and
+    // unconditional, as below.
     typedef T t4 __attribute__((ext_vector_type(4)));
     constexpr int NP = N / 4 + 1;  // pairs (m even, m <= N/2)
     constexpr int RND2 = (NP + NT - 1) / NT;

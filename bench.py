@@ -120,12 +120,12 @@ def strip_comments(src):
 
 
 def kernel_source_hash():
-    """Hash of every kernel source, comments and layout aside (a counter
-    summary taken on other code is stale; one taken before a comment changed
-    is not)."""
+    """Hash of every kernel source and of the launch shapes and plan
+    arithmetic beside them, comments and layout aside (a counter summary taken
+    on other code is stale; one taken before a comment changed is not)."""
     h = hashlib.sha256()
     for name in sorted(os.listdir(KERNEL_DIR)):
-        if name.endswith((".hip", ".h")):
+        if name.endswith((".hip", ".h", ".cpp")):
             with open(os.path.join(KERNEL_DIR, name), encoding="utf-8") as fh:
                 h.update(name.encode() + b"\0" + strip_comments(fh.read()).encode())
     return h.hexdigest()[:16]

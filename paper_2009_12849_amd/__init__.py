@@ -331,7 +331,8 @@ def stream_probe(kind: str, bufs, stream=None):
 
 
 def project_batched(plans: Sequence[Plan], us, vs, ws, ps, stream=None):
-    """Project every member in one graph launch (see include/monc.h)."""
+    """Project every member: grouped launches the first time over these plans and
+    tensors, one graph launch from then on (see include/monc.h)."""
     n = len(plans)
     VP = ctypes.c_void_p * n
     hs = VP(*[pl.handle for pl in plans])

@@ -367,7 +367,9 @@ int monc_stream_probe(int kind, void* a, void* b, void* c, void* d, size_t bytes
  *            MONC_EINVAL. */
 int monc_plan_params(const monc_plan* plan, int* out);
 /* Set them from in[MONC_NPARAMS] (values are checked; 0 keeps the current
- * value). Synchronises the device. */
+ * value; lanes and columns of the column solve that were never set stay
+ * automatic, and the automatic lanes make room for a column count that is).
+ * Synchronises the device. */
 int monc_plan_set_params(monc_plan* plan, const int* in);
 
 #ifdef __cplusplus

@@ -179,27 +179,19 @@ static int configure_tiles(monc_plan* pl, int ex, int ey, int ymt, int triP, int
   ymt = std::max(1, std::min(ymt, mt_cap));
   const int nxh = pl->nx / 2 + 1;
   ymt = std::min(ymt, pow2_floor(nxh) * 2);
-  // tridiagonal lanes per column: sixteen (one DPP row, the cheapest exchange)
-  // where that leaves 2 to 10 rows a lane, four up to 16 levels, more lanes above
-  // 160. Against the fewest lanes of at most 6 rows, us (FP64): 32^3 7.7 -> 6.6 and
-  // 128^2 x 40 10.8 -> 9.5 (8 -> 16 lanes), 256^2 x 128 36.5 -> 28.7 (32 -> 16), 128 x
-  // 128 x 256 23.6 -> 20.4 (64 -> 32); but 1024 x 512 x 16 26 with four, 34 with 16.
+  // tridiagonal lanes per column and columns per workgroup (0 = automatic)
   if (triP <= 0) triP = pl->triP;
-  if (triP <= 0) {
-    triP = pl->nz <= 4 ? 1 : pl->nz <= 16 ? 4 : 16;
-    while ((pl->nz + triP - 1) / triP > 10 && triP < kTriPmax) triP *= 2;
-  }
-  if (triP & (triP - 1) || triP > kTriPmax)
-    return fail(MONC_EINVAL, "tridiagonal lanes per column must be a power of 2 <= %d (got %d)", kTriPmax, triP);
-  const int s = tri_rows(pl->nz, triP);
-  if (s == 0)
-    return fail(MONC_EINVAL, "%d lanes leave %d rows per lane (max %d)", triP, (pl->nz + triP - 1) / triP, kTriSmax);
-  // tridiagonal tile: columns per workgroup (0 = automatic)
   if (tricw <= 0) tricw = pl->tricw;
-  const int cw = tricw > 0 ? tricw : tri_columns(pl->ny, nxh, triP);
-  if (cw & (cw - 1) || cw * triP > 512)
+  const int lanes = triP > 0 ? triP : tri_lanes(pl->nz, tricw);
+  if (lanes & (lanes - 1) || lanes > kTriPmax)
+    return fail(MONC_EINVAL, "tridiagonal lanes per column must be a power of 2 <= %d (got %d)", kTriPmax, lanes);
+  const int s = tri_rows(pl->nz, lanes);
+  if (s == 0)
+    return fail(MONC_EINVAL, "%d lanes leave %d rows per lane (max %d)", lanes, (pl->nz + lanes - 1) / lanes, kTriSmax);
+  const int cw = tricw > 0 ? tricw : tri_columns(pl->ny, nxh, lanes);
+  if (cw & (cw - 1) || cw * lanes > 512)
     return fail(MONC_EINVAL, "tridiagonal columns per workgroup must be a power of 2 with %d lanes <= 512 threads (got %d)",
-                triP, cw);
+                lanes, cw);
   // x transforms per workgroup of the compile-time x kernels (default:
   // x_transforms); at most 512 threads and 160 KB of LDS
   if (xpw <= 0) xpw = pl->xpw;
@@ -237,7 +229,7 @@ static int configure_tiles(monc_plan* pl, int ex, int ey, int ymt, int triP, int
   h.fx = fx;
   h.fy = fy;
   h.ymt = ymt;
-  h.triP = triP;
+  h.triP = lanes;
   h.tris = s;
   h.tricw = cw;
   h.tcwaves = h.tcrows = 0;
@@ -1627,7 +1619,7 @@ extern "C" int monc_plan_params(const monc_plan* pl, int* out) {
   out[0] = pl->ex;
   out[1] = pl->ey;
   out[2] = pl->ymt;
-  out[3] = pl->triP;
+  out[3] = pl->h.triP;
   out[4] = pl->h.tricw;
   out[5] = pl->h.xpw;
   out[6] = pl->h.yept;
@@ -1690,7 +1682,7 @@ static int tune_plan(monc_plan* pl, void* stream) {
     for (int k = 0; k < MONC_K_COUNT; ++k) cost += ms[k];
     return MONC_OK;
   };
-  int best[MONC_NPARAMS] = {pl->ex, pl->ey, pl->ymt, pl->triP, pl->h.tricw, pl->h.xpw, pl->h.yept};
+  int best[MONC_NPARAMS] = {pl->ex, pl->ey, pl->ymt, pl->h.triP, pl->h.tricw, pl->h.xpw, pl->h.yept};
   {
     double whole = 0.0;
     const int r = measure(best, (1u << MONC_K_COUNT) - 1, whole);

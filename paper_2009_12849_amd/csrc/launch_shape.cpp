@@ -182,6 +182,20 @@ int tri_rows(int nz, int P) {
   return 0;
 }
 
+// Sixteen lanes (one DPP row, the cheapest exchange) where that leaves 2 to 10
+// rows a lane, four up to 16 levels, more lanes above 160. Against the fewest
+// lanes of at most 6 rows, us (FP64): 32^3 7.7 -> 6.6 and 128^2 x 40 10.8 -> 9.5 (8
+// -> 16 lanes), 256^2 x 128 36.5 -> 28.7 (32 -> 16), 128 x 128 x 256 23.6 -> 20.4 (64
+// -> 32); but 1024 x 512 x 16 26 with four, 34 with 16.
+// A column count beside them is taken where those fewest lanes leave it room in
+// 512 threads, and then with them where the others do not.
+int tri_lanes(int nz, int columns) {
+  int few = 1, lanes = nz <= 4 ? 1 : nz <= 16 ? 4 : 16;
+  while ((nz + few - 1) / few > 6 && few < kTriPmax) few *= 2;
+  while ((nz + lanes - 1) / lanes > 10 && lanes < kTriPmax) lanes *= 2;
+  return (long long)columns * std::max(few, lanes) > 512 ? few : lanes;
+}
+
 // 256 threads, four waves, so that five workgroups fit a CU at ~100 registers per
 // lane; half that where it leaves fewer than four workgroups a CU: 128^2 x 128 FP64
 // 16.0 -> 15.4 us, but 1024^2 x 64 FP32 129 -> 185

@@ -49,7 +49,9 @@ std::vector<std::vector<int>> deal_chains(const std::vector<const MemberDesc*>& 
 // Rows per lane of the lanes-per-column tridiagonal kernel for nz rows on P lanes:
 // the smallest compiled row count (2..8, 10, 12, 16) that covers them, 0 if none.
 int tri_rows(int nz, int P);
-// Its automatic columns per workgroup with P lanes a column.
+// Its automatic lanes per column beside a column count asked for (0: none), and
+// its automatic columns per workgroup with P lanes a column.
+int tri_lanes(int nz, int columns);
 int tri_columns(int ny, int nxh, int P);
 // Its tiles that the autotuner times: every lane count of at least two rows a lane
 // with its automatic columns, then for the lanes chosen the column counts.

@@ -838,6 +838,33 @@ def test_plan_rejects_bad_tridiagonal_tiles(params):
     assert plan.params == before
 
 
+@pytest.mark.parametrize("nz", [1, 5, 6, 7, 16, 20, 32, 33, 48, 64, 96, 97, 130, 161, 200, 300])
+def test_columns_asked_for_without_lanes(nz):
+    # a column count beside automatic lanes (0) is taken exactly where the fewest
+    # lanes of at most 6 rows each (or 64) leave it room in 512 threads, whatever
+    # lanes the default is; a refusal leaves the plan as it was
+    few = 1
+    while -(-nz // few) > 6 and few < 64:
+        few *= 2
+    g, u, v, w = _case((32, 6, nz), 33)
+    ref = oracle.project(u, v, w, g.dx, g.dy, g.dz, g.rho0)
+    for cols in (1, 2, 4, 8, 16, 32, 64, 128, 256, 512):
+        plan = monc.Plan.from_grid(g, "f64")
+        before = plan.params
+        if cols * few > 512:
+            with pytest.raises(monc.MoncError, match="512 threads"):
+                plan.params = [0, 0, 0, 0, cols]
+            assert plan.params == before
+        else:
+            plan.params = [0, 0, 0, 0, cols]
+            assert plan.params[4] == cols and plan.params[3] * cols <= 512
+            print(f"case columns without lanes nz={nz} {plan.params}", flush=True)
+            out = run_gpu(g, u, v, w, plan=plan)
+            errs = field_errors(out, ref, u, v, w)
+            assert max(errs[:3]) <= TOL64 and errs[3] <= p_tolerance(g), (cols, errs)
+        plan.close()
+
+
 def test_autotune_keeps_results():
     g, u, v, w = _case((64, 48, 40), 20)
     plan = monc.Plan.from_grid(g, "f64")

@@ -182,7 +182,7 @@ static int configure_tiles(monc_plan* pl, int ex, int ey, int ymt, int triP, int
   // tridiagonal lanes per column and columns per workgroup (0 = automatic)
   if (triP <= 0) triP = pl->triP;
   if (tricw <= 0) tricw = pl->tricw;
-  const int lanes = triP > 0 ? triP : tri_lanes(pl->nz, tricw);
+  const int lanes = triP > 0 ? triP : tri_lanes(pl->nz, tricw, pl->dtype == MONC_FP64);
   if (lanes & (lanes - 1) || lanes > kTriPmax)
     return fail(MONC_EINVAL, "tridiagonal lanes per column must be a power of 2 <= %d (got %d)", kTriPmax, lanes);
   const int s = tri_rows(pl->nz, lanes);

@@ -184,15 +184,23 @@ int tri_rows(int nz, int P) {
 
 // Sixteen lanes (one DPP row, the cheapest exchange) where that leaves 2 to 10
 // rows a lane, four up to 16 levels, more lanes above 160. Against the fewest
-// lanes of at most 6 rows, us (FP64): 32^3 7.7 -> 6.6 and 128^2 x 40 10.8 -> 9.5 (8
-// -> 16 lanes), 256^2 x 128 36.5 -> 28.7 (32 -> 16), 128 x 128 x 256 23.6 -> 20.4 (64
-// -> 32); but 1024 x 512 x 16 26 with four, 34 with 16.
-// A column count beside them is taken where those fewest lanes leave it room in
+// lanes of at most 6 rows, us (FP64): 256^2 x 128 36.5 -> 28.7 (32 -> 16), 128 x 128
+// x 256 23.6 -> 20.4 (64 -> 32); but 1024 x 512 x 16 26 with four, 34 with 16.
+// FP64 storage takes no more than those fewest: each lane ends the cyclic
+// reduction with a division of its own, which in a nearly singular column (a
+// horizontally long domain's lowest wavenumbers) puts an error of its own on each
+// lane's part of the column, where the rows inside a lane follow from one another.
+// The error of w against 64-bit sums, the default lanes with and without that
+// bound (2-norm): 64 x 1024 x 8 4.0e-14 / 6.0e-13, 108 x 1024 x 24 4.6e-14 / 3.9e-13,
+// 256 x 24 x 32 1.5e-14 / 4.7e-14 (u 5.9e-15 / 4.4e-14); the calls cost 32^3 22.2 / 21.7
+// us, 128^2 x 40 42.7 / 41.7, 1024^2 x 32 971 / 975, 1024 x 512 x 8 128 / 132.
+// A column count beside them is taken where the fewest lanes leave it room in
 // 512 threads, and then with them where the others do not.
-int tri_lanes(int nz, int columns) {
+int tri_lanes(int nz, int columns, bool fp64) {
   int few = 1, lanes = nz <= 4 ? 1 : nz <= 16 ? 4 : 16;
   while ((nz + few - 1) / few > 6 && few < kTriPmax) few *= 2;
   while ((nz + lanes - 1) / lanes > 10 && lanes < kTriPmax) lanes *= 2;
+  if (fp64) lanes = std::min(lanes, few);
   return (long long)columns * std::max(few, lanes) > 512 ? few : lanes;
 }
 

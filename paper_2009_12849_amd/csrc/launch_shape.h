@@ -51,7 +51,7 @@ std::vector<std::vector<int>> deal_chains(const std::vector<const MemberDesc*>& 
 int tri_rows(int nz, int P);
 // Its automatic lanes per column beside a column count asked for (0: none), and
 // its automatic columns per workgroup with P lanes a column.
-int tri_lanes(int nz, int columns);
+int tri_lanes(int nz, int columns, bool fp64);
 int tri_columns(int ny, int nxh, int P);
 // Its tiles that the autotuner times: every lane count of at least two rows a lane
 // with its automatic columns, then for the lanes chosen the column counts.

@@ -106,6 +106,12 @@ static void chains() {
   std::printf("\n");
 }
 
+// l nz columns fp64: the automatic lanes
+static void lanes() {
+  int nz, columns, fp64;
+  if (std::scanf("%d %d %d", &nz, &columns, &fp64) == 3) std::printf("l %d\n", tri_lanes(nz, columns, fp64 != 0));
+}
+
 int main() {
   char what[32];
   while (std::scanf("%31s", what) == 1) {
@@ -113,6 +119,7 @@ int main() {
     if (!std::strcmp(what, "b")) batch_shapes();
     if (!std::strcmp(what, "t")) tri_tiles();
     if (!std::strcmp(what, "c")) chains();
+    if (!std::strcmp(what, "l")) lanes();
   }
   return 0;
 }
@@ -242,3 +249,24 @@ def test_chains_of_a_batch(ask, most):
         points = [sum(b[i][0] * b[i][1] * b[i][2] for i in c) for c in chains]
         largest = max(sum(g[0] * g[1] * g[2] for g in b if g[:2] == p) for p in pairs)
         assert max(points) - min(points) <= largest
+
+
+def fewest_lanes(nz):
+    few = 1
+    while -(-nz // few) > 6 and few < 64:
+        few *= 2
+    return few
+
+
+def test_automatic_lanes(ask):
+    """FP64 storage takes no more lanes a column than the fewest that leave at most
+    six rows each (more put more of the elimination into the cyclic reduction,
+    whose error in nearly singular columns is larger); a column count beside
+    automatic lanes fits 512 threads with them wherever it does with those."""
+    cases = [(nz, c, f) for nz in range(1, 1025) for c in (0, 1, 8, 32, 64, 128, 512) for f in (0, 1)]
+    for (nz, c, f), r in zip(cases, ask([f"l {nz} {c} {f}" for nz, c, f in cases])):
+        lanes, few = int(r[1]), fewest_lanes(nz)
+        assert lanes in (1, 2, 4, 8, 16, 32, 64) and -(-nz // lanes) <= 16, (nz, c, f, lanes)
+        if f:
+            assert lanes <= few, (nz, c, lanes, few)
+        assert (c * lanes <= 512) == (c * few <= 512), (nz, c, f, lanes, few)

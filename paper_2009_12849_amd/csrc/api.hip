@@ -486,6 +486,8 @@ extern "C" monc_plan* monc_plan_create(int nx, int ny, int nz, double dx, double
 
   // device side
   std::call_once(g_attr_once, [] { init_kernel_attributes(); });
+  init_fft_attributes(nx);
+  init_fft_attributes(ny);
   if (hipGetDevice(&pl->device) != hipSuccess) {
     fail(MONC_EHIP, "hipGetDevice failed (no usable HIP device)");
     return nullptr;

@@ -7,8 +7,10 @@
 
 namespace monc {
 
-// Raise the dynamic-LDS limit of every kernel to the CU's 160 KB.
+// Raise the dynamic-LDS limit of the kernels to the CU's 160 KB: of all but the
+// compile-time FFT ones, and of those of length n (once per group of lengths).
 void init_kernel_attributes();
+void init_fft_attributes(int n);
 void init_tridiag_attributes();  // the tridiagonal kernels' part of it
 void init_level_attributes();    // the level kernels'
 

@@ -2,6 +2,8 @@
 // the FFT kernels' launches to the instances of fft_inst.hip.
 #include <hip/hip_runtime.h>
 
+#include <mutex>
+
 #include "fft_kernels.h"
 #include "launch.h"
 
@@ -205,12 +207,26 @@ __global__ void __launch_bounds__(256) k_grad(LaunchArgs a) {
 // ---------------------------------------------------------------------------
 // host-side launchers
 // ---------------------------------------------------------------------------
+// A group's limits are set, and its code is loaded, when the first plan with one
+// of its lengths is made: setting all of them took 33 of the 85 ms of a process's
+// first plan.
+void init_fft_attributes(int n) {
+#define MONC_CASE(N) case N:
+#define MONC_GROUP_INIT(K)                      \
+  switch (n) {                                  \
+    MONC_CT_GROUP_##K(MONC_CASE) {              \
+      static std::once_flag once;               \
+      std::call_once(once, init_fft_group_##K); \
+    }                                           \
+  }
+  MONC_FFT_GROUPS(MONC_GROUP_INIT)
+#undef MONC_GROUP_INIT
+#undef MONC_CASE
+}
+
 void init_kernel_attributes() {
   init_tridiag_attributes();
   init_level_attributes();
-#define MONC_GROUP_INIT(K) init_fft_group_##K();
-  MONC_FFT_GROUPS(MONC_GROUP_INIT)
-#undef MONC_GROUP_INIT
   set_lds_limit(k_xfwd_gen<double, 0>);
   set_lds_limit(k_xfwd_gen<float, 0>);
   set_lds_limit(k_xfwd_gen<float, 1>);

@@ -708,6 +708,42 @@ def test_batched_rejects_mixed_dtypes():
         monc.project_batched([p64, p32], [a[0], b[0]], [a[1], b[1]], [a[2], b[2]], [a[3], b[3]])
 
 
+@pytest.mark.parametrize("dtype", ["f64", "mixed"])
+def test_lengths_of_later_plans_have_their_lds(dtype):
+    # plans made one after the other in a process of their own, of lengths whose
+    # kernels are set up apart and whose widest tiles take more than 64 KB of LDS
+    # (x: 4 x 2048 or 2 x 4096 points; y: 8 columns of 1024 in FP64 and more)
+    import subprocess
+    import sys
+    code = """
+import numpy as np, torch, oracle, synth, paper_2009_12849_amd as monc
+from tests.tolerances import TOL64, TOL_MIXED
+dtype = "%s"
+for i, (nx, ny, params) in enumerate([(2048, 4, [0, 0, 0, 0, 0, 4]), (4, 1024, [0, 0, 8]), (4096, 2, [0, 0, 0, 0, 0, 2]),
+                                      (6, 1536, [0, 0, 5]), (3888, 3, []), (2, 2916, [0, 0, 8])]):
+    print("case later lengths", nx, ny, dtype, flush=True)
+    rng = np.random.default_rng(2200 + i)
+    g = synth.random_grid(rng, nx, ny, 3, stretch=(1.0, 1.02), dx=25.0, dy=25.0)
+    f = synth.random_fields(rng, g)
+    plan = monc.Plan.from_grid(g, dtype)
+    if params:
+        plan.params = params
+    t = [torch.from_numpy(a).cuda().to(plan.torch_dtype) for a in f]
+    base = [x.cpu().numpy().astype(np.float64) for x in t]
+    t.append(torch.empty_like(t[0]))
+    plan.project(*t)
+    torch.cuda.synchronize()
+    ref = oracle.project(*base, g.dx, g.dy, g.dz, g.rho0)
+    scale = max(np.abs(b).max() for b in base)
+    err = max(np.abs(t[k].cpu().numpy() - ref[k]).max() for k in range(3)) / scale
+    assert err <= (4 * TOL64 if dtype == "f64" else TOL_MIXED), (nx, ny, err)
+print("all done", flush=True)
+""" % dtype
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=100)
+    print(r.stdout, flush=True)
+    assert r.returncode == 0 and "all done" in r.stdout, r.stdout + r.stderr
+
+
 def test_plan_rejects_too_many_elements_per_thread():
     g, u, v, w = _case((96, 48, 16), 17)
     plan = monc.Plan.from_grid(g, "f64")
